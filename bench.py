@@ -304,7 +304,7 @@ def hbm_kernels(reps=20):
 def general_networks(steps=200):
     """Training steps/s of the example shape (2D L=8, 16 layers, batch 64, BF16) with other
     s/t networks from the parameter file's hidden_sizes / kernel_size / use_bn, on the
-    general-network kernels, beside the default network (hidden [8, 8], kernel 3); each
+    general kernels, beside the default network (hidden [8, 8], kernel 3); each
     eagerly and with forward + backward replayed from a captured HIP graph."""
     import torch
     import seeded_inputs as si

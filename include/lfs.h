@@ -64,8 +64,8 @@ typedef enum lfs_status {
 typedef enum lfs_precision { LFS_PLAIN_FP32 = 0, LFS_BF16_CONV = 1 } lfs_precision;
 
 /* Kernel family used for the flow.  AUTO picks the fused LDS-resident kernels
- * when the shape has one, else the generic kernels (same results up to
- * floating-point summation order). */
+ * when the shape has one, else the general kernels (GENERIC; same results up
+ * to floating-point summation order). */
 typedef enum lfs_algo { LFS_ALGO_AUTO = 0, LFS_ALGO_GENERIC = 1, LFS_ALGO_FUSED = 2 } lfs_algo;
 
 /* Flow architecture (paper Sec. 1, coupling-layer and composition equations;
@@ -91,9 +91,9 @@ typedef enum lfs_algo { LFS_ALGO_AUTO = 0, LFS_ALGO_GENERIC = 1, LFS_ALGO_FUSED 
  *              running statistics (lfs_flow_forward_bn); such a flow runs only
  *              through the _bn entry points
  * A network equal to the default (kernel 3, two hidden convolutions of 8, 16
- * or 32 channels, no batch norm) runs on the fused or generic kernels; any
- * other runs on the general-network kernels (LFS_ALGO_FUSED then reports
- * EUNSUPPORTED). */
+ * or 32 channels, no batch norm) runs on the fused or general kernels; any
+ * other runs on the general or the batch-norm kernels (LFS_ALGO_FUSED then
+ * reports EUNSUPPORTED). */
 #define LFS_MAX_HIDDEN 4
 typedef struct lfs_flow_desc {
   int32_t dim;
@@ -207,18 +207,23 @@ int32_t lfs_flow_forward(const lfs_flow_desc* desc, const float* params, int32_t
 
 /* lfs_flow_forward for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid allocation):
- * the same kernels and results, bit for bit, with the workspace taken from a
- * static device array of LFS_NOALLOC_SCRATCH_BYTES that the library holds on
+ * the same kernels and results, bit for bit (but see below), with the
+ * workspace taken from a static device array of LFS_NOALLOC_SCRATCH_BYTES that the library holds on
  * every GPU it runs on until the process ends (its address is looked up once
  * per device, on the first call with that device current).  The call allocates
  * and frees nothing.  Every call on one GPU shares that GPU's array: calls
  * that overlap on one GPU (different streams, or host threads) race and must
  * be serialised by the caller.  Nothing in the array needs to start at zero.
  * Arguments as lfs_flow_forward, without ws and ws_bytes.
- * Errors: as lfs_flow_forward; LFS_EWORKSPACE when the workspace this flow and
- * batch need (lfs_workspace_bytes(desc, B, 0)) exceeds LFS_NOALLOC_SCRATCH_BYTES
- * (the fused forwards need only their weight fragments, at most 85 KB per
- * layer, at any batch; the generic kernels' hidden activations grow with B). */
+ * Errors: as lfs_flow_forward; LFS_EWORKSPACE when LFS_NOALLOC_SCRATCH_BYTES
+ * cannot hold the fused forward's weight fragments (at most 85 KB per layer, at
+ * any batch) or, for the general kernels, two FP64 numbers per sample and the
+ * FP32 hidden activations of the whole batch (and the two output channels of a
+ * network other than the default one), whether or not they need that much.
+ * Where the general kernels' weight fragments of all layers do not fit beside
+ * what else they need, they are prepared convolution by convolution and the
+ * batch is processed in parts; small lattices then sum their convolutions in
+ * another order than lfs_flow_forward (equal to FP32 rounding). */
 #define LFS_NOALLOC_SCRATCH_BYTES ((size_t)8 << 20)
 int32_t lfs_flow_forward_noalloc(const lfs_flow_desc* desc, const float* params, int32_t B,
                                  const float* z, float* phi, double* logq, double* logdet,

@@ -85,23 +85,34 @@ int32_t make_geom(const lfs_flow_desc* d, FlowGeom* g) {
 namespace {
 
 // Kernel family of a validated geometry: fused (default network, a fused kernel
-// for the shape, algo not GENERIC), generic (default network) or general net.
-enum class Family { Fused, Generic, Net };
+// for the shape, algo not GENERIC), general, or the batch-norm kernels.
+enum class Family { Fused, General, BatchNorm };
 
 bool fused_ok(const FlowGeom& g, int bwd) { return g.net_default && fused_supported(g, bwd); }
 
 Family family(const FlowGeom& g, int bwd) {
-  if (!g.net_default) return Family::Net;
-  if (g.algo != LFS_ALGO_GENERIC && fused_supported(g, bwd)) return Family::Fused;
-  return Family::Generic;
+  if (g.bn) return Family::BatchNorm;
+  if (g.net_default && g.algo != LFS_ALGO_GENERIC && fused_supported(g, bwd)) return Family::Fused;
+  return Family::General;
 }
 
 size_t ws_bytes_of(const FlowGeom& g, int B, int bwd) {
   switch (family(g, bwd)) {
     case Family::Fused: return fused_ws_bytes(g, B, bwd);
-    case Family::Generic: return generic_ws_bytes(g, B, bwd);
+    case Family::General: return general_ws_bytes(g, B, bwd);
     default: return net_ws_bytes(g, B, bwd);
   }
+}
+
+// What lfs_flow_forward_noalloc holds against its scratch: the fused kernels' weight
+// fragments, or two numbers per sample and the hidden activations (and, in a network
+// other than the default one, the outputs) of the whole batch.
+size_t noalloc_bytes(const FlowGeom& g, int B) {
+  if (family(g, 0) == Family::Fused) return fused_ws_bytes(g, B, 0);
+  const size_t BV = (size_t)B * g.V;
+  size_t s = 2 * align_up(sizeof(double) * B);
+  for (int i = 0; i + (g.net_default ? 1 : 0) < g.n_conv; ++i) s += align_up(sizeof(float) * BV * g.cout[i]);
+  return s;
 }
 
 }  // namespace
@@ -154,14 +165,9 @@ extern "C" int32_t lfs_flow_forward(const lfs_flow_desc* desc, const float* para
   const size_t need = lfs::ws_bytes_of(g, B, 0);
   if (need > 0 && (!ws || ws_bytes < need)) return LFS_EWORKSPACE;
   hipStream_t st = (hipStream_t)stream;
-  switch (lfs::family(g, 0)) {
-    case lfs::Family::Fused:
-      return lfs::fused_forward(g, params, B, z, phi, logq, logdet, saved_x, nullptr, (char*)ws, st);
-    case lfs::Family::Generic:
-      return lfs::generic_forward(g, params, B, z, phi, logq, logdet, saved_x, (char*)ws, st);
-    default:
-      return lfs::net_forward(g, params, B, z, phi, logq, logdet, saved_x, (char*)ws, st);
-  }
+  if (lfs::family(g, 0) == lfs::Family::Fused)
+    return lfs::fused_forward(g, params, B, z, phi, logq, logdet, saved_x, nullptr, (char*)ws, st);
+  return lfs::general_forward(g, params, B, z, phi, logq, logdet, saved_x, (char*)ws, ws_bytes, st);
 }
 
 namespace lfs {
@@ -178,17 +184,9 @@ int32_t backward_plain(const lfs_flow_desc* desc, const FlowGeom& g, const float
   const size_t need = ws_bytes_of(g, B, 1);
   if (need > 0 && (!ws || ws_bytes < need)) return LFS_EWORKSPACE;
   hipStream_t st = (hipStream_t)stream;
-  switch (family(g, 1)) {
-    case Family::Fused:
-      return fused_backward(g, params, B, saved_x, saved_h, g_phi, g_logq, g_logq_vec, g_params,
-                            g_z, (char*)ws, st);
-    case Family::Generic:
-      return generic_backward(g, params, B, saved_x, g_phi, g_logq, g_logq_vec, g_params, g_z,
-                              (char*)ws, st);
-    default:
-      return net_backward(g, params, B, saved_x, g_phi, g_logq, g_logq_vec, g_params, g_z,
-                          (char*)ws, st);
-  }
+  if (family(g, 1) == Family::Fused)
+    return fused_backward(g, params, B, saved_x, saved_h, g_phi, g_logq, g_logq_vec, g_params, g_z, (char*)ws, st);
+  return general_backward(g, params, B, saved_x, g_phi, g_logq, g_logq_vec, g_params, g_z, (char*)ws, st);
 }
 
 }  // namespace
@@ -351,10 +349,13 @@ extern "C" int32_t lfs_flow_forward_noalloc(const lfs_flow_desc* desc, const flo
   if (B < 0 || g.bn) return LFS_EINVAL;
   if (desc->algo == LFS_ALGO_FUSED && !lfs::fused_ok(g, 0)) return LFS_EUNSUPPORTED;
   if (B == 0) return LFS_OK;
-  if (lfs::ws_bytes_of(g, B, 0) > LFS_NOALLOC_SCRATCH_BYTES) return LFS_EWORKSPACE;
+  if (lfs::noalloc_bytes(g, B) > LFS_NOALLOC_SCRATCH_BYTES) return LFS_EWORKSPACE;
   void* ws = nullptr;
   const int32_t sp = lfs::scratch_of_current_device(&ws);
   if (sp != LFS_OK) return sp;
-  return lfs_flow_forward(desc, params, B, z, phi, logq, logdet, saved_x, ws,
-                          LFS_NOALLOC_SCRATCH_BYTES, stream);
+  if (lfs::family(g, 0) == lfs::Family::Fused)
+    return lfs_flow_forward(desc, params, B, z, phi, logq, logdet, saved_x, ws, LFS_NOALLOC_SCRATCH_BYTES, stream);
+  if (!params || !z || !phi || !logq) return LFS_EINVAL;
+  return lfs::general_forward(g, params, B, z, phi, logq, logdet, saved_x, (char*)ws, LFS_NOALLOC_SCRATCH_BYTES,
+                              (hipStream_t)stream);
 }

@@ -1,0 +1,1134 @@
+// General flow kernels: every network without batch norm (any hidden_sizes, odd
+// kernel 1 .. 7; paper Sec. 1, coupling-layer equation) on every lattice, with
+// implicit-GEMM convolutions on the matrix cores (net_engine.hpp).
+//
+//   resident  samples whose field and activations fit the LDS: one workgroup per
+//             sample runs all layers in one launch (kg_forward), and the backward's
+//             recompute, affine backward and data gradients of a group of layers in
+//             one launch (kg_backward)
+//   staged    larger samples: one launch per convolution over the whole batch,
+//             activations in HBM (kg_staged)
+//
+// Which of the two runs depends on the shape alone, never on the batch, so a
+// sample's result does not depend on the batch it is in.  Either backward leaves
+// the hidden activations and the gradients of every convolution's output in HBM
+// for a group of layers, and one launch forms all their weight gradients
+// (kg_wgrad).
+//
+// Small samples are bound by latency: 64 samples of 64 sites keep 64 of the 256 CUs
+// busy with a chain of N n_conv dependent convolutions.  What counts is the time from
+// one barrier to the next, hence one launch for all layers instead of one per
+// convolution, fragments fetched a layer ahead, neighbours from a table and gathers
+// without branches.  Training step of the 2D L = 8 flow with hidden [16, 16, 16], 16
+// layers, batch 64, FP32: 3400 us with a launch per convolution and direct sums, 505 so
+// (forward 155, backward 274, weight gradients 56).  3D L = 12, hidden 16, 12 layers,
+// batch 50, FP32, where a sample does not fit: 47.1 -> 3.9 ms (a hidden convolution of
+// 86400 sites 41 us, its data gradient 22 us; direct sums: 294 and 257).
+#include <algorithm>
+#include <type_traits>
+
+#include "net_engine.hpp"
+
+namespace lfs {
+namespace {
+
+using namespace net;
+
+constexpr double kHalfLog2Pi = 0.91893853320467274178;
+constexpr size_t kLdsMax = 158 * 1024;
+
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// One thread per (layer, fragment, lane): fragments f0 .. f0 + count - 1 of every layer.
+template <int MODE>
+__global__ void __launch_bounds__(256) kg_prep(NetDev d, const float* __restrict__ params, int layers, int f0,
+                                               int count, u32x4* __restrict__ frags) {
+  const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (gid >= (int64_t)layers * count * 64) return;
+  const int lane = (int)(gid & 63);
+  const int64_t fl = gid >> 6;
+  const int layer = (int)(fl / count), f = f0 + (int)(fl - (int64_t)layer * count);
+  const bool tr = f >= d.frags_fwd;
+  int i = 0;
+  for (; i + 1 < d.n_conv; ++i)
+    if (f < (tr ? d.t[i + 1] : d.f[i + 1]).off) break;
+  const ConvDir& c = tr ? d.t[i] : d.f[i];
+  const int r = f - c.off, ct = r / c.per_ct();
+  frags[gid] = frag_entry<MODE>(d, params + (size_t)layer * d.P_layer, i, tr, ct, r - ct * c.per_ct() - 1, lane);
+}
+
+// Waves of a resident workgroup (small lattices split the K blocks of a unit over them).
+constexpr int kResWaves = 16;
+
+// LDS of a resident workgroup, byte offsets.
+struct ResLds {
+  int ps;                     // plane stride, floats (16 mod 64: the planes of the four lane
+                              // groups of one gather start in different banks)
+  int xs, gy, go, slot[LFS_MAX_HIDDEN], red, nbr, odd;
+  int frags[2];               // a layer's weight fragments (lf), see kg_forward and kg_backward
+  bool lf;
+  int total;
+};
+
+ResLds res_lds(const NetDev& d, bool bwd) {
+  ResLds r{};
+  const int V = d.lat.V;
+  r.ps = (4 * (V + 1) + 47) / 64 * 64 + 16;
+  int64_t off = 0;
+  auto take = [&](int64_t bytes) {
+    const int64_t o = off;
+    off += (bytes + 15) / 16 * 16;
+    return (int)std::min<int64_t>(o, 1 << 30);
+  };
+  r.xs = take(4ll * (V + 1));
+  if (bwd) {
+    r.gy = take(4ll * V);
+    r.go = take(4ll * r.ps);
+    for (int i = 0; i + 1 < d.n_conv; ++i) r.slot[i] = take(4ll * r.ps * cdiv(d.cout[i], 4));
+  } else {
+    int q = 0;
+    for (int i = 0; i + 1 < d.n_conv; ++i) q = std::max(q, cdiv(d.cout[i], 4));
+    const int a = take(4ll * r.ps * q), b = d.n_conv > 2 ? take(4ll * r.ps * q) : a;
+    for (int i = 0; i + 1 < d.n_conv; ++i) r.slot[i] = i & 1 ? b : a;
+  }
+  r.red = take(1024ll * kResWaves);
+  r.nbr = take(2ll * (d.T + 1) * V);
+  r.odd = take(4ll * (d.T + 1));
+  // fragments: two layers' in the forward, one layer's forward and transposed ones in the
+  // backward
+  const int64_t fr = off;
+  const int64_t f0 = d.frags_fwd * 1024ll, f1 = (bwd ? d.frags_all - d.frags_fwd : d.frags_fwd) * 1024ll;
+  r.lf = fr + f0 + f1 <= (int64_t)kLdsMax;
+  if (r.lf) {
+    r.frags[0] = take(f0);
+    r.frags[1] = take(f1);
+  }
+  r.total = (int)std::min<int64_t>(off, 1 << 30);
+  return r;
+}
+
+// Copies n fragments to LDS without passing through registers: 1 KB per instruction, lane
+// i's 16 bytes at the fragment's LDS address + 16 i.  Counts as vector-memory loads.
+__device__ __forceinline__ void copy_frags(const u32x4* src, unsigned char* dst, int n) {
+  typedef __attribute__((address_space(1))) void* gptr;
+  typedef __attribute__((address_space(3))) void* lptr;
+  const int lane = threadIdx.x & 63;
+  for (int k = fused::wave_id(); k < n; k += blockDim.x >> 6)
+    __builtin_amdgcn_global_load_lds((gptr)(src + (size_t)k * 64 + lane), (lptr)(dst + k * 1024), 16, 0, 0);
+}
+__device__ __forceinline__ void wait_copies() { __builtin_amdgcn_s_waitcnt(0x0F70); }  // vmcnt(0)
+
+// One convolution over (16-site tile, row tile) units: a wave per unit, or, where the
+// workgroup has several times more waves, four waves per unit (transposed and Bf16: also
+// two), each on its share of the K blocks (Tree: of the eight sums; Seq keeps its order and
+// is not split), joined through red.  reader(tile) gives the operand reader of the lane's
+// site, epi(tile, ct, acc) takes a unit's result.  Ends before any barrier that publishes
+// epi's stores.
+template <int MODE, bool TR, bool FIRST, bool LF, class Reader, class Epi>
+__device__ __forceinline__ void conv_pass(int tiles, const ConvDir& cd, const u32x4* frags, f32x4* red,
+                                          Reader&& reader, Epi&& epi) {
+  const int w = fused::wave_id(), nw = blockDim.x >> 6, lane = threadIdx.x & 63, j = lane >> 4;
+  const int nct = cd.nct, units = tiles * nct;
+  const ConvDir c = cd;
+  const Weights W{frags, c.per_ct(), lane};
+  constexpr bool TREE = MODE == kTree && !TR;
+  int ks = 1;
+  if constexpr (TREE)
+    ks = 4 * units <= nw ? 4 : 1;
+  else if constexpr (MODE != kSeq || TR)
+    while (ks < 4 && 2 * ks * units <= nw && 2 * ks <= c.nb) ks *= 2;
+  auto bias = [&](int ct) { return __builtin_bit_cast(f32x4, W.at(ct, -1)); };
+  if (ks == 1) {
+    for (int u = w; u < units; u += nw) {
+      const int tile = fdiv(u, c.dnct), ct = u - tile * nct;
+      const auto rd = reader(tile);
+      if constexpr (TREE)
+        epi(tile, ct, tree<FIRST, false>(rd, c, W, ct, j, 0) + bias(ct));
+      else
+        epi(tile, ct, chain<MODE, TR, FIRST, 2, !LF>(rd, c, W, ct, j, 0, c.nb, bias(ct)));
+    }
+    return;
+  }
+  const int kp = (w >= units) + (w >= 2 * units) + (w >= 3 * units) + (w >= 4 * units), u = w - kp * units;
+  const int tile = fdiv(u, c.dnct), ct = u - tile * nct;
+  f32x4 acc{0.f, 0.f, 0.f, 0.f};
+  if (kp < ks) {
+    const auto rd = reader(tile);
+    if constexpr (TREE) {
+      acc = tree<FIRST, true>(rd, c, W, ct, j, kp);
+    } else {
+      if (kp == 0) acc = bias(ct);
+      acc = chain<MODE, TR, FIRST, 2, !LF>(rd, c, W, ct, j, c.nb * kp / ks, c.nb * (kp + 1) / ks, acc);
+    }
+    if (kp > 0) red[((kp - 1) * units + u) * 64 + lane] = acc;
+  }
+  lds_barrier();
+  if (kp == 0) {
+    if constexpr (TREE) {
+      const f32x4 p1 = red[u * 64 + lane], p2 = red[(units + u) * 64 + lane], p3 = red[(2 * units + u) * 64 + lane];
+      acc = ((acc + p2) + (p1 + p3)) + bias(ct);
+    } else {
+      for (int p = 0; p + 1 < ks; ++p) acc += red[(p * units + u) * 64 + lane];
+    }
+    epi(tile, ct, acc);
+  }
+}
+
+// Tables of a resident workgroup, and the zero site after the field and every plane.
+template <int DIM>
+__device__ __forceinline__ void build_tables(const NetDev& d, const ResLds& S, unsigned char* smem, bool bwd) {
+  build_nbr<DIM>(d, reinterpret_cast<uint16_t*>(smem + S.nbr));
+  int* odd = reinterpret_cast<int*>(smem + S.odd);
+  for (int t = threadIdx.x; t <= d.T; t += blockDim.x) odd[t] = t < d.T ? (tap_entry<DIM>(d, t, 1) >> 12) & 1 : 0;
+  const int V = d.lat.V;
+  if (threadIdx.x == 0) reinterpret_cast<float*>(smem + S.xs)[V] = 0.f;
+  if (bwd && threadIdx.x < 4) reinterpret_cast<float*>(smem + S.go)[4 * V + threadIdx.x] = 0.f;
+  for (int i = 0; i + 1 < d.n_conv; ++i)
+    for (int k = threadIdx.x; k < (d.cout[i] + 3) / 4 * 4; k += blockDim.x)
+      reinterpret_cast<float*>(smem + S.slot[i])[(k >> 2) * S.ps + 4 * V + (k & 3)] = 0.f;
+}
+
+// The reader of input planes for site n.
+template <bool REV>
+__device__ __forceinline__ LdsPlanes<REV> lds_planes(const NetDev& d, const ResLds& S, const unsigned char* smem,
+                                                     const float* in, int n) {
+  return LdsPlanes<REV>{reinterpret_cast<const uint16_t*>(smem + S.nbr) + n, in, d.lat.V, S.ps, d.T};
+}
+
+// The hidden convolutions of one layer from the field xs into the slots.  store(i, plane,
+// site, values) also receives every quad of activation i.  frags: the layer's forward
+// fragments.
+template <int DIM, int MODE, bool LF, class Store>
+__device__ __forceinline__ void hidden_convs(const NetDev& d, const ResLds& S, unsigned char* smem,
+                                             const u32x4* frags, const float* xs, int fpar, Store&& store) {
+  const Lat& lat = d.lat;
+  const int lane = threadIdx.x & 63, j = lane >> 4, m = lane & 15;
+  f32x4* red = reinterpret_cast<f32x4*>(smem + S.red);
+  const int tiles = (lat.V + 15) >> 4;
+  for (int i = 0; i + 1 < d.n_conv; ++i) {
+    const ConvDir& c = d.f[i];
+    float* out = reinterpret_cast<float*>(smem + S.slot[i]);
+    const int rows = c.rows;
+    auto epi = [&](int tile, int ct, const f32x4& acc) {
+      const int n = tile * 16 + m, pl = ct * 4 + j;
+      if (n < lat.V && 4 * pl < rows) {
+        f32x4 v;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = masked(leaky(acc[r]), (4 * pl + r - rows) >> 31);
+        *reinterpret_cast<f32x4*>(out + pl * S.ps + 4 * n) = v;
+        store(i, pl, n, v);
+      }
+    };
+    if (i == 0) {
+      conv_pass<MODE, false, true, LF>(tiles, c, frags + c.off * 64, red, [&](int tile) {
+        const int n = min(tile * 16 + m, lat.V - 1);
+        return LdsField{reinterpret_cast<const uint16_t*>(smem + S.nbr) + n, xs, lat.V, d.T,
+                        parity_of<DIM>(site_of<DIM>(lat, n)) ^ fpar, reinterpret_cast<const int*>(smem + S.odd)};
+      }, epi);
+    } else {
+      const float* in = reinterpret_cast<const float*>(smem + S.slot[i - 1]);
+      conv_pass<MODE, false, false, LF>(tiles, c, frags + c.off * 64, red, [&](int tile) {
+        return lds_planes<false>(d, S, smem, in, min(tile * 16 + m, lat.V - 1));
+      }, epi);
+    }
+    lds_barrier();
+  }
+}
+
+// The last convolution at the active sites: f(a, site, o_0, o_1) for the a-th of them.
+template <int DIM, int MODE, bool LF, class F>
+__device__ __forceinline__ void last_conv(const NetDev& d, const ResLds& S, unsigned char* smem, const u32x4* frags,
+                                          int apar, F&& f) {
+  const Lat& lat = d.lat;
+  const int lane = threadIdx.x & 63, j = lane >> 4, m = lane & 15, i = d.n_conv - 1, half = lat.V / 2;
+  const ConvDir& c = d.f[i];
+  const float* in = reinterpret_cast<const float*>(smem + S.slot[i - 1]);
+  conv_pass<MODE, false, false, LF>((half + 15) >> 4, c, frags + c.off * 64, reinterpret_cast<f32x4*>(smem + S.red),
+                                    [&](int tile) {
+    return lds_planes<false>(d, S, smem, in, half_site<DIM>(lat, min(tile * 16 + m, half - 1), apar));
+  }, [&](int tile, int, const f32x4& acc) {
+    const int a = tile * 16 + m;
+    if (j == 0 && a < half) f(a, half_site<DIM>(lat, a, apar), acc[0], acc[1]);
+  });
+}
+
+// ---- resident forward ----------------------------------------------------------
+
+// LF: a layer's fragments are read from LDS, the next layer's copied there meanwhile.
+template <int DIM, int MODE, bool LF>
+__global__ void __launch_bounds__(64 * kResWaves) kg_forward(NetDev d, ResLds S, const u32x4* __restrict__ frags,
+                                                             int B, const float* z, float* phi,
+                                                             float* __restrict__ saved, double* __restrict__ logq,
+                                                             double* __restrict__ logdet) {
+  using R = std::conditional_t<MODE == kBf16, double, float>;
+  extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ R sh[16];
+  const int V = d.lat.V, F = d.frags_fwd;
+  float* xs = reinterpret_cast<float*>(smem + S.xs);
+  if constexpr (LF) copy_frags(frags, smem + S.frags[0], F);
+  build_tables<DIM>(d, S, smem, false);
+  const size_t BV = (size_t)B * V;
+  int cur = 0;
+  for (int b = blockIdx.x; b < B; b += gridDim.x) {
+    R zz = 0, ld = 0;
+    for (int n = threadIdx.x; n < V; n += blockDim.x) {
+      const float v = z[(size_t)b * V + n];
+      xs[n] = v;
+      if (saved) saved[(size_t)b * V + n] = v;
+      zz += (R)v * v;
+    }
+    if constexpr (LF) wait_copies();
+    lds_barrier();
+    for (int l = 0; l < d.N; ++l) {
+      const int fpar = (l + d.parity0) & 1;
+      const u32x4* fr;
+      if constexpr (LF) {
+        fr = reinterpret_cast<const u32x4*>(smem + S.frags[cur]);
+        cur ^= 1;
+        copy_frags(frags + (size_t)(l + 1 < d.N ? l + 1 : 0) * F * 64, smem + S.frags[cur], F);
+      } else {
+        fr = frags + (size_t)l * F * 64;
+      }
+      hidden_convs<DIM, MODE, LF>(d, S, smem, fr, xs, fpar, [](int, int, int, const f32x4&) {});
+      last_conv<DIM, MODE, LF>(d, S, smem, fr, fpar ^ 1, [&](int, int n, float o0, float o1) {
+        const float s = d.final_tanh ? tanhf(o0) : o0;
+        xs[n] = xs[n] * expf(s) + o1;
+        ld += (R)s;
+      });
+      if constexpr (LF) wait_copies();
+      lds_barrier();
+      if (saved) {
+        float* sv = saved + (size_t)(l + 1) * BV + (size_t)b * V;
+        for (int n = threadIdx.x; n < V; n += blockDim.x) sv[n] = xs[n];
+      }
+    }
+    for (int n = threadIdx.x; n < V; n += blockDim.x) phi[(size_t)b * V + n] = xs[n];
+    ld = block_sum(ld, sh);
+    zz = block_sum(zz, sh);
+    if (threadIdx.x == 0) {
+      const double logr = -0.5 * (double)zz - (double)V * kHalfLog2Pi;
+      logq[b] = logr - (double)ld;
+      if (logdet) logdet[b] = (double)ld;
+    }
+  }
+}
+
+// ---- resident backward ---------------------------------------------------------
+
+// A layer's activations and gradients in HBM for the weight gradients: planes of
+// [V][4] floats, per (layer of the group, sample): the hidden activations, the
+// gradients of the hidden convolutions' outputs in the same order, the gradient of
+// the last one's (one plane).
+__host__ __device__ inline int store_planes(const NetDev& d) { return 2 * d.hplanes + 1; }
+
+// Affine backward at an active site from o_0: g_o into (go0, g) and g_x.
+__device__ __forceinline__ void affine_bwd(int final_tanh, float o0, float x, float g, float gld, float& go0,
+                                           float& gx) {
+  const float s = final_tanh ? tanhf(o0) : o0;
+  const float es = expf(s);
+  const float gs = g * x * es + gld;
+  go0 = final_tanh ? gs * (1.f - s * s) : gs;
+  gx = g * es;
+}
+
+// Layers [l0, l1) of every sample, last to first: g_in is the cotangent of layer l1 - 1's
+// output, g_out receives that of layer l0's input.  LF: the layer's forward fragments
+// and its transposed ones each have a place in LDS; one is filled while the other is used.
+template <int DIM, int MODE, bool LF>
+__global__ void __launch_bounds__(64 * kResWaves) kg_backward(NetDev d, ResLds S, const u32x4* __restrict__ frags,
+                                                              int B, int l0, int l1, const float* __restrict__ saved,
+                                                              const float* g_in, float g_ld,
+                                                              const double* __restrict__ g_ld_vec, float* g_out,
+                                                              float* __restrict__ store) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const Lat& lat = d.lat;
+  const int V = lat.V, lane = threadIdx.x & 63, j = lane >> 4, m = lane & 15;
+  const int F = d.frags_fwd, FT = d.frags_all - F;
+  float* xs = reinterpret_cast<float*>(smem + S.xs);
+  float* gy = reinterpret_cast<float*>(smem + S.gy);
+  float* go = reinterpret_cast<float*>(smem + S.go);
+  f32x4* red = reinterpret_cast<f32x4*>(smem + S.red);
+  if constexpr (LF) copy_frags(frags + (size_t)(l1 - 1) * d.frags_all * 64, smem + S.frags[0], F);
+  build_tables<DIM>(d, S, smem, true);
+  const size_t BV = (size_t)B * V;
+  const int PL = store_planes(d), HP = d.hplanes;
+  for (int b = blockIdx.x; b < B; b += gridDim.x) {
+    const float gld = g_ld_vec ? (float)(-g_ld_vec[b]) : g_ld;
+    for (int n = threadIdx.x; n < V; n += blockDim.x) gy[n] = g_in[(size_t)b * V + n];
+    // a layer's field: the thread's first site is loaded a layer ahead
+    const float* xb = saved + (size_t)b * V;
+    const bool own = threadIdx.x < V;
+    float xpre = own ? xb[(size_t)(l1 - 1) * BV + threadIdx.x] : 0.f;
+    for (int l = l1 - 1; l >= l0; --l) {
+      const int fpar = (l + d.parity0) & 1, apar = fpar ^ 1;
+      float* st = store + ((size_t)(l - l0) * B + b) * PL * V * 4;
+      auto put = [&](int plane, int n, const f32x4& v) {
+        *reinterpret_cast<f32x4*>(st + ((size_t)plane * V + n) * 4) = v;
+      };
+      if (own) xs[threadIdx.x] = xpre;
+      for (int n = threadIdx.x + blockDim.x; n < V; n += blockDim.x) xs[n] = xb[(size_t)l * BV + n];
+      if constexpr (LF) wait_copies();
+      lds_barrier();
+      const u32x4 *ff, *ft;
+      if constexpr (LF) {
+        ff = reinterpret_cast<const u32x4*>(smem + S.frags[0]);
+        ft = reinterpret_cast<const u32x4*>(smem + S.frags[1]);
+        copy_frags(frags + ((size_t)l * d.frags_all + F) * 64, smem + S.frags[1], FT);
+      } else {
+        ff = frags + (size_t)l * d.frags_all * 64;
+        ft = ff + F * 64;
+      }
+      hidden_convs<DIM, MODE, LF>(d, S, smem, ff, xs, fpar,
+                                  [&](int i, int pl, int n, const f32x4& v) { put(d.hplane[i] + pl, n, v); });
+      last_conv<DIM, MODE, LF>(d, S, smem, ff, apar, [&](int a, int n, float o0, float) {
+        const int nf = half_site<DIM>(lat, a, fpar);
+        float go0, gx;
+        const float g = gy[n];
+        affine_bwd(d.final_tanh, o0, xs[n], g, gld, go0, gx);
+        gy[n] = gx;
+        const f32x4 v{go0, g, 0.f, 0.f}, zero{0.f, 0.f, 0.f, 0.f};
+        *reinterpret_cast<f32x4*>(go + 4 * n) = v;
+        *reinterpret_cast<f32x4*>(go + 4 * nf) = zero;
+        put(2 * HP, n, v);
+        put(2 * HP, nf, zero);
+      });
+      if constexpr (LF) wait_copies();
+      lds_barrier();
+      const int ln = l > l0 ? l - 1 : l1 - 1;
+      xpre = own ? xb[(size_t)ln * BV + threadIdx.x] : 0.f;
+      if constexpr (LF) copy_frags(frags + (size_t)ln * d.frags_all * 64, smem + S.frags[0], F);
+      // data gradients, last convolution to first; a hidden gradient takes the place of
+      // its activation
+      for (int i = d.n_conv - 1; i > 0; --i) {
+        const ConvDir& c = d.t[i];
+        const float* in = i + 1 == d.n_conv ? go : reinterpret_cast<const float*>(smem + S.slot[i]);
+        float* h = reinterpret_cast<float*>(smem + S.slot[i - 1]);
+        const int rows = c.rows;
+        conv_pass<MODE, true, false, LF>((V + 15) >> 4, c, ft + (c.off - F) * 64, red, [&](int tile) {
+          return lds_planes<true>(d, S, smem, in, min(tile * 16 + m, V - 1));
+        }, [&](int tile, int ct, const f32x4& acc) {
+          const int n = tile * 16 + m, pl = ct * 4 + j;
+          if (n < V && 4 * pl < rows) {
+            f32x4* p = reinterpret_cast<f32x4*>(h + pl * S.ps + 4 * n);
+            const f32x4 hv = *p;
+            f32x4 v;
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              v[r] = masked(acc[r] * leaky_grad_from_out(hv[r]), (4 * pl + r - rows) >> 31);
+            *p = v;
+            put(HP + d.hplane[i - 1] + pl, n, v);
+          }
+        });
+        lds_barrier();
+      }
+      {
+        const int half = V / 2;
+        const float* in = reinterpret_cast<const float*>(smem + S.slot[0]);
+        const ConvDir& c = d.t[0];
+        conv_pass<MODE, true, false, LF>((half + 15) >> 4, c, ft + (c.off - F) * 64, red, [&](int tile) {
+          return lds_planes<true>(d, S, smem, in, half_site<DIM>(lat, min(tile * 16 + m, half - 1), fpar));
+        }, [&](int tile, int, const f32x4& acc) {
+          const int a = tile * 16 + m;
+          if (j == 0 && a < half) gy[half_site<DIM>(lat, a, fpar)] += acc[0];
+        });
+      }
+      // the next layer's xs may be written at once: its readers are behind the barriers above
+    }
+    lds_barrier();
+    for (int n = threadIdx.x; n < V; n += blockDim.x) g_out[(size_t)b * V + n] = gy[n];
+    lds_barrier();
+  }
+  if constexpr (LF) wait_copies();  // none may land in the LDS of the next workgroup
+}
+
+// ---- staged kernels --------------------------------------------------------------
+
+// log r(z) per sample and the first field: saved[0], or phi (which may be z).
+template <typename R>
+__global__ void __launch_bounds__(256) kg_begin(int V, const float* z, float* x, double* __restrict__ logr) {
+  __shared__ R sh[16];
+  const int b = blockIdx.x;
+  R acc = 0;
+  for (int n = threadIdx.x; n < V; n += blockDim.x) {
+    const float v = z[(size_t)b * V + n];
+    if (x != z) x[(size_t)b * V + n] = v;
+    acc += (R)v * v;
+  }
+  acc = block_sum(acc, sh);
+  if (threadIdx.x == 0) logr[b] = -0.5 * (double)acc - (double)V * kHalfLog2Pi;
+}
+
+// log q = log r - sum of the sites' s sums (one block per sample).
+template <typename R>
+__global__ void __launch_bounds__(256) kg_end(int half, const R* __restrict__ ld, const double* __restrict__ logr,
+                                              double* __restrict__ logq, double* __restrict__ logdet) {
+  __shared__ R sh[16];
+  const int b = blockIdx.x;
+  R acc = 0;
+  for (int a = threadIdx.x; a < half; a += blockDim.x) acc += ld[(size_t)b * half + a];
+  acc = block_sum(acc, sh);
+  if (threadIdx.x == 0) {
+    logq[b] = logr[b] - (double)acc;
+    if (logdet) logdet[b] = (double)acc;
+  }
+}
+
+enum class Op { First, Hidden, Couple, Affine, Grad, GradField };
+
+struct StagedArgs {
+  int i, B, fpar, lds_frags;
+  int ct0, ct1;      // row tiles of this launch; frags are theirs
+  const float* in;   // planes of the input (sample stride in_ss floats), or the layer's field (i = 0 forward)
+  size_t in_ss;
+  float* out;        // planes of the output; Grad: over the gradients, h holds the activations
+  size_t out_ss;
+  const float* h;
+  size_t h_ss;
+  const float* x;    // Couple: the layer's field; Affine: likewise
+  float* xout;       // Couple: the next field (may be x); Affine: g_x
+  float* xout2;      // Couple: a second copy of the next field, or null
+  void* ld;          // Couple: per active site sums of s, [B][V / 2]
+  int first;         // Couple: the sums start here
+  const float* gy;   // Affine: the cotangent of the layer's output; GradField: unused
+  float gld;
+  const double* gld_vec;
+};
+
+// One convolution of one layer over the whole batch: a wave takes (sample, 16-site tile,
+// row tile) units in turn; its weights are staged in LDS where they fit.
+//   First      h = leaky(conv) of the masked field       all sites
+//   Hidden     h = leaky(conv)                          all sites
+//   Couple     the last convolution and the affine update   active sites
+//   Affine     the last convolution and its affine backward  active sites
+//   Grad       g_h = conv^T(g) leaky'(h)                all sites
+//   GradField  g_x += conv^T(g)                         frozen sites
+template <int DIM, int MODE, Op OP>
+__global__ void __launch_bounds__(256) kg_staged(NetDev d, StagedArgs A, const u32x4* frags) {
+  using R = std::conditional_t<MODE == kBf16, double, float>;
+  constexpr bool TR = OP == Op::Grad || OP == Op::GradField;
+  constexpr bool HALF = OP == Op::Couple || OP == Op::Affine || OP == Op::GradField;
+  extern __shared__ __align__(16) unsigned char smem[];
+  const Lat& lat = d.lat;
+  const ConvDir& c = TR ? d.t[A.i] : d.f[A.i];
+  const int V = lat.V, half = V / 2, lane = threadIdx.x & 63, j = lane >> 4, m = lane & 15;
+  int* tab = reinterpret_cast<int*>(smem);
+  build_tab<DIM>(d, TR ? -1 : 1, tab);
+  const int nct = A.ct1 - A.ct0;
+  Weights W{frags, c.per_ct(), lane};
+  if (A.lds_frags) {
+    u32x4* sf = reinterpret_cast<u32x4*>(smem + ((d.T + 1) * 4 + 15) / 16 * 16);
+    for (int k = threadIdx.x; k < nct * W.per_ct * 64; k += blockDim.x) sf[k] = frags[k];
+    W.frags = sf;
+  }
+  __syncthreads();
+  const int sites = HALF ? half : V, par = OP == Op::GradField ? A.fpar : A.fpar ^ 1;
+  const int tiles = (sites + 15) >> 4, per = tiles * nct;
+  const int64_t units = (int64_t)A.B * per;
+  for (int64_t u = (int64_t)blockIdx.x * 4 + fused::wave_id(); u < units; u += (int64_t)gridDim.x * 4) {
+    const int b = (int)(u / per), r = (int)(u - (int64_t)b * per), tile = nct == 1 ? r : r / nct, ct = r - tile * nct;
+    const int a = tile * 16 + m, ac = min(a, sites - 1);
+    const bool valid = a < sites;
+    const int n = HALF ? half_site<DIM>(lat, ac, par) : ac;
+    const Site<DIM> s = site_of<DIM>(lat, n);
+    const f32x4 bias = __builtin_bit_cast(f32x4, W.at(ct, -1));
+    f32x4 acc;
+    if constexpr (OP == Op::First) {
+      const FarField<DIM> rd{&lat, tab, A.in + (size_t)b * V, d.T, parity_of<DIM>(s) ^ A.fpar, s};
+      if constexpr (MODE == kTree)
+        acc = tree<true, false>(rd, c, W, ct, j, 0) + bias;
+      else
+        acc = chain<MODE, false, true, 1, true>(rd, c, W, ct, j, 0, c.nb, bias);
+    } else {
+      const FarPlanes<DIM> rd{&lat, tab, A.in + (size_t)b * A.in_ss, 4 * V, d.T, s};
+      if constexpr (MODE == kTree && !TR)
+        acc = tree<false, false>(rd, c, W, ct, j, 0) + bias;
+      else
+        acc = chain<MODE, TR, false, 4, true>(rd, c, W, ct, j, 0, c.nb, bias);
+    }
+    const int pl = (A.ct0 + ct) * 4 + j;
+    if constexpr (OP == Op::First || OP == Op::Hidden || OP == Op::Grad) {
+      if (valid && 4 * pl < c.rows) {
+        f32x4 v, hv{};
+        if (OP == Op::Grad) hv = *reinterpret_cast<const f32x4*>(A.h + (size_t)b * A.h_ss + ((size_t)pl * V + n) * 4);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          v[k] = masked(OP != Op::Grad ? leaky(acc[k]) : acc[k] * leaky_grad_from_out(hv[k]),
+                        (4 * pl + k - c.rows) >> 31);
+        *reinterpret_cast<f32x4*>(A.out + (size_t)b * A.out_ss + ((size_t)pl * V + n) * 4) = v;
+      }
+    } else if (valid && j == 0) {
+      const size_t o = (size_t)b * V + n;
+      if constexpr (OP == Op::GradField) {
+        A.xout[o] += acc[0];
+      } else {
+        const size_t of = (size_t)b * V + half_site<DIM>(lat, a, A.fpar);
+        if constexpr (OP == Op::Couple) {
+          const float sv = d.final_tanh ? tanhf(acc[0]) : acc[0];
+          const float xn = A.x[o] * expf(sv) + acc[1], xf = A.x[of];
+          A.xout[o] = xn;
+          if (A.xout != A.x) A.xout[of] = xf;
+          if (A.xout2) A.xout2[o] = xn, A.xout2[of] = xf;
+          R* ld = reinterpret_cast<R*>(A.ld) + (size_t)b * half + a;
+          *ld = A.first ? (R)sv : *ld + (R)sv;
+        } else {
+          float go0, gx;
+          const float g = A.gy[o];
+          affine_bwd(d.final_tanh, acc[0], A.x[o], g, A.gld_vec ? (float)(-A.gld_vec[b]) : A.gld, go0, gx);
+          A.xout[o] = gx;
+          A.xout[of] = A.gy[of];
+          float* go = A.out + (size_t)b * A.out_ss;
+          *reinterpret_cast<f32x4*>(go + 4 * n) = f32x4{go0, g, 0.f, 0.f};
+          *reinterpret_cast<f32x4*>(go + 4 * half_site<DIM>(lat, a, A.fpar)) = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+      }
+    }
+  }
+}
+
+// ---- weight gradients --------------------------------------------------------------
+
+// dW[co][ci][t] = sum over (sample, site) of g[n][co] u[n + delta_t][ci] as GEMMs over the
+// sites on v_mfma_f64_16x16x4_f64: products of FP32 values are exact and every sum is
+// FP64.  Rows are 16 channels of the operand read in place, columns 16 (tap, channel)
+// pairs of the other one, read displaced: u displaced (rows co), or, where that takes
+// fewer tiles (the last convolution, whose g has two channels), g displaced the other
+// way (rows ci).
+struct WgConv {
+  int swap;               // 1: rows are ci, columns (tap, co) with g displaced by -delta
+  int rows, ncols, cc;    // row channels, T * cc columns, channels per tap
+  int rt, groups;         // row tiles, groups of kWgCols column tiles
+  int gplane, uplane;     // first planes of g and u in the store (u of the first: the field)
+  int gseq, useq;         // their planes hold channels in Seq order
+  int job0;               // first job
+};
+constexpr int kWgCols = 3;   // column tiles of a wave (12 accumulator registers pairs each)
+constexpr int kWgUnroll = 4;
+struct WgArgs {
+  WgConv c[kMaxConv];
+  int jobs;               // per layer
+  int l0, layers, B, chunks;
+  int64_t per;            // (sample, site) terms per chunk, a multiple of 16
+};
+
+template <int DIM, bool BF16>
+__global__ void __launch_bounds__(256) kg_wgrad(NetDev d, WgArgs A, const float* __restrict__ store,
+                                                const float* __restrict__ saved, double* __restrict__ partial) {
+  typedef double f64x4 __attribute__((ext_vector_type(4)));
+  __shared__ double red[4][64][4];
+  __shared__ double redb[4][64];
+  const Lat& lat = d.lat;
+  const int V = lat.V, lane = threadIdx.x & 63, m = lane & 15, kk = lane >> 4, w = fused::wave_id();
+  const int ll = blockIdx.x / A.jobs, job = blockIdx.x - ll * A.jobs, layer = A.l0 + ll;
+  int i = 0;
+  while (i + 1 < d.n_conv && job >= A.c[i + 1].job0) ++i;
+  const WgConv& C = A.c[i];
+  const int r = job - C.job0, rt = r / C.groups, cg = r - rt * C.groups;
+  const int fpar = (layer + d.parity0) & 1, PL = store_planes(d);
+  // the lane's row channel and its (tap, channel) column of every column tile
+  const int row = rt * 16 + m;
+  const bool rok = row < C.rows;
+  const int rch = rok ? row : 0;
+  int ent[kWgCols], cch[kWgCols], coff[kWgCols];
+  bool cok[kWgCols];
+#pragma unroll
+  for (int q = 0; q < kWgCols; ++q) {
+    const int f = (cg * kWgCols + q) * 16 + m;
+    cok[q] = f < C.ncols;
+    const int tap = cok[q] ? f / C.cc : 0;
+    cch[q] = cok[q] ? f - tap * C.cc : 0;
+    ent[q] = tap_entry<DIM>(d, tap, C.swap ? -1 : 1);
+  }
+  const bool first = i == 0;
+  // operand offsets within a sample's store block; the first convolution's u is the field
+  int roff;
+  {
+    int pl, e;
+    place_of(C.swap ? C.useq : C.gseq, C.swap ? d.cin[i] : d.cout[i], rch, pl, e);
+    roff = ((C.swap ? C.uplane : C.gplane) + pl) * V * 4 + e;
+#pragma unroll
+    for (int q = 0; q < kWgCols; ++q) {
+      place_of(C.swap ? C.gseq : C.useq, C.swap ? d.cout[i] : d.cin[i], cch[q], pl, e);
+      coff[q] = ((C.swap ? C.gplane : C.uplane) + pl) * V * 4 + e;
+    }
+  }
+  const bool row_x = first && C.swap, col_x = first && !C.swap;
+  const int64_t terms = (int64_t)A.B * V, c0 = (int64_t)blockIdx.y * A.per, c1 = min(c0 + A.per, terms);
+  // each wave a quarter of the chunk, in steps of four terms (lane group kk: the kk-th)
+  const int64_t quarter = ((c1 - c0 + 15) / 16) * 4;
+  const int64_t w0 = min(c0 + w * quarter, c1), w1 = min(w0 + quarter, c1);
+  f64x4 acc[kWgCols];
+  double bias = 0.0;
+#pragma unroll
+  for (int q = 0; q < kWgCols; ++q) acc[q] = f64x4{0.0, 0.0, 0.0, 0.0};
+  const bool do_bias = cg == 0 && (!C.swap || rt == 0);
+  int b = (int)((w0 + kk) / V), n = (int)((w0 + kk) - (int64_t)b * V);
+  const float* sx = saved + (size_t)layer * terms;
+  for (int64_t t = w0; t < w1; t += 4 * kWgUnroll) {
+    float ra[kWgUnroll], cb[kWgUnroll][kWgCols];
+#pragma unroll
+    for (int u = 0; u < kWgUnroll; ++u) {
+      const bool ok = t + 4 * u + kk < w1;
+      const int bb = ok ? b : 0, nn = ok ? n : 0;
+      const float* sb = store + ((size_t)ll * A.B + bb) * PL * V * 4;
+      const Site<DIM> s = site_of<DIM>(lat, nn);
+      const int par = parity_of<DIM>(s);
+      float v;
+      if (row_x)
+        v = par == fpar ? sx[(size_t)bb * V + nn] : 0.f;
+      else
+        v = sb[roff + 4 * nn];
+      ra[u] = ok && rok ? v : 0.f;
+#pragma unroll
+      for (int q = 0; q < kWgCols; ++q) {
+        const int mm = nbr_site<DIM>(lat, s, ent[q]);
+        if (col_x)
+          v = ((par ^ (ent[q] >> 12)) & 1) == fpar ? sx[(size_t)bb * V + mm] : 0.f;
+        else
+          v = sb[coff[q] + 4 * mm];
+        cb[u][q] = ok && cok[q] ? v : 0.f;
+      }
+      n += 4;
+      while (n >= V) n -= V, ++b;
+    }
+#pragma unroll
+    for (int u = 0; u < kWgUnroll; ++u) {
+      if (do_bias) bias += (double)(C.swap ? cb[u][0] : ra[u]);
+      const double da = (double)opnd<BF16>(ra[u]);
+#pragma unroll
+      for (int q = 0; q < kWgCols; ++q)
+        acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(da, (double)opnd<BF16>(cb[u][q]), acc[q], 0, 0, 0);
+    }
+  }
+  double* out = partial + ((size_t)blockIdx.y * A.layers + ll) * d.P_layer;
+#pragma unroll
+  for (int q = 0; q < kWgCols; ++q) {
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 4; ++k) red[w][lane][k] = acc[q][k];
+    __syncthreads();
+    // thread (lane, w) sums register w of the four waves in order: row 4 w + lane / 16
+    const double v = ((red[0][lane][w] + red[1][lane][w]) + red[2][lane][w]) + red[3][lane][w];
+    const int rr = rt * 16 + 4 * w + kk;
+    if (rr < C.rows && cok[q]) {
+      const int f = (cg * kWgCols + q) * 16 + m, tap = f / C.cc, ch = f - tap * C.cc;
+      const int co = C.swap ? ch : rr, ci = C.swap ? rr : ch;
+      out[d.offW[i] + (co * d.cin[i] + ci) * d.T + tap] = v;
+    }
+  }
+  if (do_bias) {
+    redb[w][lane] = bias;
+    __syncthreads();
+    // rows: channel rt * 16 + m of the row operand; displaced g: the channels of tap 0
+    const int ch = C.swap ? cch[0] : row;
+    const bool ok = C.swap ? m < C.cc : rok;
+    if (w == 0 && kk == 0 && ok) {
+      double s = 0.0;
+      for (int ww = 0; ww < 4; ++ww)
+        for (int k = 0; k < 4; ++k) s += redb[ww][k * 16 + m];
+      out[d.offb[i] + ch] = s;
+    }
+  }
+}
+
+// g_params of the group's layers: the chunks' partials summed in order.
+__global__ void __launch_bounds__(256) kg_reduce(int n, int chunks, const double* __restrict__ partial,
+                                                 float* __restrict__ out) {
+  const int p = blockIdx.x * blockDim.x + threadIdx.x;
+  if (p >= n) return;
+  double acc = 0.0;
+  for (int c = 0; c < chunks; ++c) acc += partial[(size_t)c * n + p];
+  out[p] = (float)acc;
+}
+
+// g_z = g_x - g_logq z (d log r / dz = -z); g_logq per sample if g_logq_vec is given.
+__global__ void __launch_bounds__(256) kg_gz(int64_t n, const float* __restrict__ gx, const float* __restrict__ z,
+                                             float g_logq, const double* __restrict__ g_logq_vec, int64_t V,
+                                             float* __restrict__ gz) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const float gl = g_logq_vec ? (float)g_logq_vec[i / V] : g_logq;
+  gz[i] = gx[i] - gl * z[i];
+}
+
+// ---- host ------------------------------------------------------------------------
+
+inline unsigned blocks(int64_t n, int per = 256) { return (unsigned)((n + per - 1) / per); }
+
+// Whether a sample's forward (backward) state fits the LDS.
+// (the neighbour table holds 16-bit sites)
+bool resident(const NetDev& d, bool bwd) { return d.lat.V < 65536 && (size_t)res_lds(d, bwd).total <= kLdsMax; }
+
+size_t frag_bytes(const NetDev& d, bool bwd) {
+  return (size_t)d.N * (bwd ? d.frags_all : d.frags_fwd) * 1024;
+}
+
+// Layers whose activations and gradients are kept at once for the weight gradients: as
+// many as fit 192 MB (they then stay in the last-level cache between the two launches).
+int layer_group(const NetDev& d, int B) {
+  const size_t per = (size_t)B * store_planes(d) * d.lat.V * 16;
+  return (int)std::max<size_t>(1, std::min<size_t>(d.N, ((size_t)192 << 20) / per));
+}
+
+// Workgroups of the weight-gradient launch: enough chunks of the (sample, site) terms to
+// give every CU about four workgroups, each chunk at least 256 terms.
+struct WgPlan {
+  WgArgs a;
+  size_t partial_bytes;
+};
+WgPlan wgrad_plan(const NetDev& d, int B, int layers) {
+  WgPlan p{};
+  WgArgs& a = p.a;
+  const int n = d.n_conv;
+  int job = 0;
+  for (int i = 0; i < n; ++i) {
+    WgConv& c = a.c[i];
+    const int ci = d.cin[i], co = d.cout[i];
+    const int direct = cdiv(co, 16) * cdiv(cdiv(d.T * ci, 16), kWgCols);
+    const int swapped = cdiv(ci, 16) * cdiv(cdiv(d.T * co, 16), kWgCols);
+    c.swap = co <= 16 && swapped < direct;  // (co: the bias sums sit in one column tile)
+    c.rows = c.swap ? ci : co;
+    c.cc = c.swap ? co : ci;
+    c.ncols = d.T * c.cc;
+    c.rt = cdiv(c.rows, 16);
+    c.groups = cdiv(cdiv(c.ncols, 16), kWgCols);
+    c.gplane = i + 1 < n ? d.hplanes + d.hplane[i] : 2 * d.hplanes;
+    c.uplane = i > 0 ? d.hplane[i - 1] : 0;
+    c.gseq = d.mode == kSeq && i + 1 < n;
+    c.useq = d.mode == kSeq && i > 0;
+    c.job0 = job;
+    job += c.rt * c.groups;
+  }
+  a.jobs = job;
+  a.layers = layers;
+  a.B = B;
+  const int64_t terms = (int64_t)B * d.lat.V;
+  int64_t want = std::max<int64_t>(1, 1024 / ((int64_t)job * layers));
+  want = std::min<int64_t>(want, std::max<int64_t>(1, terms / 256));
+  a.per = ((terms + want - 1) / want + 15) / 16 * 16;
+  a.chunks = (int)((terms + a.per - 1) / a.per);
+  p.partial_bytes = sizeof(double) * (size_t)a.chunks * layers * d.P_layer;
+  return p;
+}
+
+struct BwdWs {
+  u32x4* frags;
+  float *gA, *gB, *store;
+  double* partial;
+};
+BwdWs carve_bwd(const NetDev& d, int B, char* base, size_t* total) {
+  BwdWs w{};
+  size_t off = 0;
+  auto take = [&](size_t bytes) {
+    char* p = base ? base + off : nullptr;
+    off += align_up(bytes);
+    return p;
+  };
+  const size_t BV = (size_t)B * d.lat.V;
+  const int group = layer_group(d, B);
+  w.frags = (u32x4*)take(frag_bytes(d, true));
+  w.gA = (float*)take(4 * BV);
+  w.gB = (float*)take(4 * BV);
+  w.store = (float*)take((size_t)group * B * store_planes(d) * d.lat.V * 16);
+  // the last group may be smaller and take more chunks
+  size_t pb = wgrad_plan(d, B, group).partial_bytes;
+  if (d.N % group) pb = std::max(pb, wgrad_plan(d, B, d.N % group).partial_bytes);
+  w.partial = (double*)take(pb);
+  *total = off;
+  return w;
+}
+
+// f(std::true_type) or f(std::false_type).
+template <class F>
+int32_t with_lf(bool lf, F&& f) {
+  return lf ? f(std::true_type{}) : f(std::false_type{});
+}
+
+template <int MODE>
+void prep(const NetDev& d, const float* params, int layers, int f0, int count, u32x4* frags, hipStream_t st) {
+  hipLaunchKernelGGL((kg_prep<MODE>), dim3(blocks((int64_t)layers * count * 64)), dim3(256), 0, st, d, params, layers,
+                     f0, count, frags);
+}
+
+// Where a staged convolution's fragments come from: prepared for all layers (count
+// per layer), or, with count = 0, prepared launch by launch into room bytes.
+struct FragSrc {
+  u32x4* buf;
+  int count;
+  size_t room;
+  const float* params;
+};
+
+template <int DIM, int MODE, Op OP>
+int32_t staged(const NetDev& d, StagedArgs a, int layer, const FragSrc& src, hipStream_t st) {
+  constexpr bool TR = OP == Op::Grad || OP == Op::GradField;
+  const ConvDir& c = TR ? d.t[a.i] : d.f[a.i];
+  constexpr auto k = kg_staged<DIM, MODE, OP>;
+  if (!set_lds_limit<k>(80 * 1024)) return LFS_EDEVICE;
+  const size_t one = (size_t)c.per_ct() * 1024;  // a row tile's fragments
+  const int step = src.count ? c.nct : (int)std::min<size_t>(c.nct, src.room / one);
+  if (step < 1) return LFS_EWORKSPACE;
+  for (int ct = 0; ct < c.nct; ct += step) {
+    a.ct0 = ct;
+    a.ct1 = std::min(ct + step, c.nct);
+    const int nct = a.ct1 - a.ct0;
+    const u32x4* frags = src.buf;
+    if (src.count)
+      frags += ((size_t)layer * src.count + c.off) * 64;
+    else
+      prep<MODE>(d, src.params + (size_t)layer * d.P_layer, 1, c.off + ct * c.per_ct(), nct * c.per_ct(), src.buf, st);
+    const int tab = ((d.T + 1) * 4 + 15) / 16 * 16;
+    a.lds_frags = tab + nct * one <= 72 * 1024;  // two workgroups per CU
+    const int lds = tab + (a.lds_frags ? (int)(nct * one) : 0);
+    const bool half = OP == Op::Couple || OP == Op::Affine || OP == Op::GradField;
+    const int64_t units = (int64_t)a.B * cdiv(half ? d.lat.V / 2 : d.lat.V, 16) * nct;
+    const int per_cu = std::max(1, std::min(8, 156 * 1024 / std::max(lds, 1)));
+    const unsigned grid = (unsigned)std::min<int64_t>((units + 3) / 4, (int64_t)num_cus() * per_cu);
+    hipLaunchKernelGGL(k, dim3(grid), dim3(256), lds, st, d, a, frags);
+  }
+  return LFS_OK;
+}
+
+#define LFS_TRY(x)                            \
+  do {                                        \
+    const int32_t s_ = (x);                   \
+    if (s_ != LFS_OK) return s_;              \
+  } while (0)
+
+// Bytes of the staged forward of B samples beside the fragments: log r, the log-det
+// sums of the active sites and the hidden activations (two sets of planes, the
+// convolutions alternating between them).
+struct StagedWs {
+  double* logr;
+  void* ld;
+  float* planes[2];
+  size_t bytes;
+};
+StagedWs staged_ws(const NetDev& d, int B, char* base) {
+  StagedWs w{};
+  size_t off = 0;
+  auto take = [&](size_t bytes) {
+    char* p = base ? base + off : nullptr;
+    off += align_up(bytes);
+    return p;
+  };
+  const size_t BV = (size_t)B * d.lat.V;
+  int q[2] = {0, 0};
+  for (int i = 0; i + 1 < d.n_conv; ++i) q[i & 1] = std::max(q[i & 1], cdiv(d.cout[i], 4));
+  w.logr = (double*)take(sizeof(double) * B);
+  w.ld = take(BV / 2 * (d.mode == kBf16 ? sizeof(double) : sizeof(float)));
+  for (int k = 0; k < 2; ++k) w.planes[k] = (float*)take(BV * 16 * q[k]);
+  w.bytes = off;
+  return w;
+}
+
+// The staged forward of samples [0, B) of arrays whose layers are BV_all floats apart.
+template <int DIM, int MODE>
+int32_t forward_staged(const FlowGeom& g, const NetDev& d, int B, const float* z, float* phi, double* logq,
+                       double* logdet, float* saved, size_t BV_all, const StagedWs& w, const FragSrc& src,
+                       hipStream_t st) {
+  using R = std::conditional_t<MODE == kBf16, double, float>;
+  const int V = g.V;
+  float* x = saved ? saved : phi;
+  hipLaunchKernelGGL((kg_begin<R>), dim3(B), dim3(256), 0, st, V, z, x, w.logr);
+  for (int l = 0; l < d.N; ++l) {
+    float* xn = saved ? saved + (size_t)(l + 1) * BV_all : phi;
+    StagedArgs a{};
+    a.B = B;
+    a.fpar = g.frozen_parity(l);
+    for (int i = 0; i < d.n_conv; ++i) {
+      a.i = i;
+      a.in = i == 0 ? x : w.planes[(i - 1) & 1];
+      a.in_ss = i == 0 ? 0 : (size_t)cdiv(d.cout[i - 1], 4) * V * 4;
+      if (i + 1 < d.n_conv) {
+        a.out = w.planes[i & 1];
+        a.out_ss = (size_t)cdiv(d.cout[i], 4) * V * 4;
+        LFS_TRY(i == 0 ? (staged<DIM, MODE, Op::First>(d, a, l, src, st))
+                       : (staged<DIM, MODE, Op::Hidden>(d, a, l, src, st)));
+      }
+    }
+    a.x = x;
+    a.xout = xn;
+    a.xout2 = saved && l + 1 == d.N ? phi : nullptr;
+    a.ld = w.ld;
+    a.first = l == 0;
+    LFS_TRY((staged<DIM, MODE, Op::Couple>(d, a, l, src, st)));
+    x = xn;
+  }
+  hipLaunchKernelGGL((kg_end<R>), dim3(B), dim3(256), 0, st, V / 2, reinterpret_cast<const R*>(w.ld), w.logr, logq,
+                     logdet);
+  return launch_status();
+}
+
+template <int DIM, int MODE>
+int32_t forward_impl(const FlowGeom& g, const float* params, int B, const float* z, float* phi, double* logq,
+                     double* logdet, float* saved, char* ws, size_t ws_bytes, hipStream_t st) {
+  const NetDev d = make_net(g);
+  const size_t fb = frag_bytes(d, false), BV = (size_t)B * g.V;
+  const bool res = resident(d, false);
+  if (ws_bytes >= fb + (res ? 0 : staged_ws(d, B, nullptr).bytes)) {
+    u32x4* frags = reinterpret_cast<u32x4*>(ws);
+    prep<MODE>(d, params, d.N, 0, d.frags_fwd, frags, st);
+    if (!res)
+      return forward_staged<DIM, MODE>(g, d, B, z, phi, logq, logdet, saved, BV, staged_ws(d, B, ws + fb),
+                                       FragSrc{frags, d.frags_fwd, fb, params}, st);
+    const ResLds S = res_lds(d, false);
+    return with_lf(S.lf, [&](auto lf) {
+      constexpr auto k = kg_forward<DIM, MODE, decltype(lf)::value>;
+      if (!set_lds_limit<k>(kLdsMax)) return (int32_t)LFS_EDEVICE;
+      hipLaunchKernelGGL(k, dim3((unsigned)std::min(B, num_cus())), dim3(64 * kResWaves), S.total, st, d, S, frags, B,
+                         z, phi, saved, logq, logdet);
+      return launch_status();
+    });
+  }
+  // a workspace without room for every layer's fragments (the static scratch): the staged
+  // kernels on as many samples at a time as leave room for a row tile's fragments
+  size_t one = 0;
+  for (int i = 0; i < d.n_conv; ++i) one = std::max(one, (size_t)d.f[i].per_ct() * 1024);
+  int step = B;
+  while (step > 1 && staged_ws(d, step, nullptr).bytes + one > ws_bytes) step = (step + 1) / 2;
+  const StagedWs w = staged_ws(d, step, ws);
+  if (w.bytes + one > ws_bytes) return LFS_EWORKSPACE;
+  const FragSrc src{reinterpret_cast<u32x4*>(ws + w.bytes), 0, ws_bytes - w.bytes, params};
+  for (int b = 0; b < B; b += step) {
+    const size_t o = (size_t)b * g.V;
+    LFS_TRY((forward_staged<DIM, MODE>(g, d, std::min(step, B - b), z + o, phi + o, logq + b,
+                                       logdet ? logdet + b : nullptr, saved ? saved + o : nullptr, BV, w, src, st)));
+  }
+  return LFS_OK;
+}
+
+template <int DIM, int MODE>
+int32_t backward_impl(const FlowGeom& g, const float* params, int B, const float* saved, const float* g_phi,
+                      double g_logq, const double* g_logq_vec, float* g_params, float* g_z, char* ws,
+                      hipStream_t st) {
+  const NetDev d = make_net(g);
+  const int V = g.V, PL = store_planes(d), HP = d.hplanes, group = layer_group(d, B);
+  const size_t BV = (size_t)B * V, ss = (size_t)PL * V * 4;
+  size_t total;
+  const BwdWs w = carve_bwd(d, B, ws, &total);
+  prep<MODE>(d, params, d.N, 0, d.frags_all, w.frags, st);
+  const FragSrc src{w.frags, d.frags_all, frag_bytes(d, true), params};
+  const bool res = resident(d, true);
+  const float* gy = g_phi;
+  float* bufs[2] = {w.gA, w.gB};
+  int which = 0;
+  for (int l1 = d.N; l1 > 0;) {
+    const int l0 = l1 > group ? l1 - group : 0;
+    if (res) {
+      const ResLds S = res_lds(d, true);
+      float* gx = bufs[which];
+      LFS_TRY(with_lf(S.lf, [&](auto lf) {
+        constexpr auto k = kg_backward<DIM, MODE, decltype(lf)::value>;
+        if (!set_lds_limit<k>(kLdsMax)) return (int32_t)LFS_EDEVICE;
+        hipLaunchKernelGGL(k, dim3((unsigned)std::min(B, num_cus())), dim3(64 * kResWaves), S.total, st, d, S, w.frags,
+                           B, l0, l1, saved, gy, (float)(-g_logq), g_logq_vec, gx, w.store);
+        return (int32_t)LFS_OK;
+      }));
+      gy = gx;
+      which ^= 1;
+    } else {
+      for (int l = l1 - 1; l >= l0; --l) {
+        float* gx = bufs[which];
+        float* st_l = w.store + (size_t)(l - l0) * B * ss;
+        auto plane = [&](int p) { return st_l + (size_t)p * V * 4; };
+        StagedArgs a{};
+        a.B = B;
+        a.fpar = g.frozen_parity(l);
+        a.in_ss = a.out_ss = a.h_ss = ss;
+        for (int i = 0; i + 1 < d.n_conv; ++i) {
+          a.i = i;
+          a.in = i == 0 ? saved + (size_t)l * BV : plane(d.hplane[i - 1]);
+          a.out = plane(d.hplane[i]);
+          LFS_TRY(i == 0 ? (staged<DIM, MODE, Op::First>(d, a, l, src, st))
+                         : (staged<DIM, MODE, Op::Hidden>(d, a, l, src, st)));
+        }
+        a.i = d.n_conv - 1;
+        a.in = plane(d.hplane[a.i - 1]);
+        a.out = plane(2 * HP);
+        a.x = saved + (size_t)l * BV;
+        a.xout = gx;
+        a.gy = gy;
+        a.gld = (float)(-g_logq);
+        a.gld_vec = g_logq_vec;
+        LFS_TRY((staged<DIM, MODE, Op::Affine>(d, a, l, src, st)));
+        for (int i = d.n_conv - 1; i > 0; --i) {
+          a.i = i;
+          a.in = i + 1 == d.n_conv ? plane(2 * HP) : plane(HP + d.hplane[i]);
+          a.out = plane(HP + d.hplane[i - 1]);
+          a.h = plane(d.hplane[i - 1]);
+          LFS_TRY((staged<DIM, MODE, Op::Grad>(d, a, l, src, st)));
+        }
+        a.i = 0;
+        a.in = plane(HP);
+        LFS_TRY((staged<DIM, MODE, Op::GradField>(d, a, l, src, st)));
+        gy = gx;
+        which ^= 1;
+      }
+    }
+    WgPlan p = wgrad_plan(d, B, l1 - l0);
+    p.a.l0 = l0;
+    hipLaunchKernelGGL((kg_wgrad<DIM, MODE == kBf16>), dim3((unsigned)(p.a.jobs * p.a.layers), (unsigned)p.a.chunks),
+                       dim3(256), 0, st, d, p.a, w.store, saved, w.partial);
+    const int n = p.a.layers * d.P_layer;
+    hipLaunchKernelGGL(kg_reduce, dim3(blocks(n)), dim3(256), 0, st, n, p.a.chunks, w.partial,
+                       g_params + (size_t)l0 * d.P_layer);
+    l1 = l0;
+  }
+  if (g_z)
+    hipLaunchKernelGGL(kg_gz, dim3(blocks((int64_t)BV)), dim3(256), 0, st, (int64_t)BV, gy, saved, (float)g_logq,
+                       g_logq_vec, (int64_t)V, g_z);
+  return launch_status();
+}
+
+}  // namespace
+
+// f(integral constants of the dimension and the mode).
+template <class F>
+static int32_t dispatch(const FlowGeom& g, F&& f) {
+  auto mode = [&](auto dim) {
+    if (g.bf16()) return f(dim, std::integral_constant<int, kBf16>{});
+    if (g.net_default) return f(dim, std::integral_constant<int, kSeq>{});
+    return f(dim, std::integral_constant<int, kTree>{});
+  };
+  return g.dim == 2 ? mode(std::integral_constant<int, 2>{}) : mode(std::integral_constant<int, 3>{});
+}
+
+// The kernels read and write the workspace 16 bytes at a time; a caller's may start
+// anywhere, so its first bytes up to the next 16-byte boundary are left unused.
+constexpr size_t kWsAlign = 16;
+static char* aligned_ws(char* ws, size_t* bytes) {
+  const size_t skip = (kWsAlign - (uintptr_t)ws % kWsAlign) % kWsAlign;
+  *bytes = *bytes > skip ? *bytes - skip : 0;
+  return ws + skip;
+}
+
+size_t general_ws_bytes(const FlowGeom& g, int B, int for_backward) {
+  const NetDev d = make_net(g);
+  if (!for_backward)
+    return kWsAlign + frag_bytes(d, false) + (resident(d, false) ? 0 : staged_ws(d, B, nullptr).bytes);
+  size_t total;
+  carve_bwd(d, B, nullptr, &total);
+  return kWsAlign + total;
+}
+
+int32_t general_forward(const FlowGeom& g, const float* params, int B, const float* z, float* phi, double* logq,
+                        double* logdet, float* saved, char* ws, size_t ws_bytes, hipStream_t st) {
+  ws = aligned_ws(ws, &ws_bytes);
+  return dispatch(g, [&](auto dim, auto mode) {
+    return forward_impl<decltype(dim)::value, decltype(mode)::value>(g, params, B, z, phi, logq, logdet, saved, ws,
+                                                                     ws_bytes, st);
+  });
+}
+
+int32_t general_backward(const FlowGeom& g, const float* params, int B, const float* saved, const float* g_phi,
+                         double g_logq, const double* g_logq_vec, float* g_params, float* g_z, char* ws,
+                         hipStream_t st) {
+  size_t unused = kWsAlign;
+  ws = aligned_ws(ws, &unused);
+  return dispatch(g, [&](auto dim, auto mode) {
+    return backward_impl<decltype(dim)::value, decltype(mode)::value>(g, params, B, saved, g_phi, g_logq, g_logq_vec,
+                                                                      g_params, g_z, ws, st);
+  });
+}
+
+}  // namespace lfs

@@ -753,17 +753,4 @@ int32_t net_backward_bn(const FlowGeom& g, const float* params, int B, const flo
                                             g_z, ws, st);
 }
 
-int32_t net_forward(const FlowGeom& g, const float* params, int B, const float* z, float* phi,
-                    double* logq, double* logdet, float* saved, char* ws, hipStream_t st) {
-  return net_forward_bn(g, params, B, z, phi, logq, logdet, saved, LFS_BN_BATCH, nullptr, 0.f, ws, st);
-}
-
-int32_t net_backward(const FlowGeom& g, const float* params, int B, const float* saved,
-                     const float* g_phi, double g_logq, const double* g_logq_vec, float* g_params,
-                     float* g_z, char* ws,
-                     hipStream_t st) {
-  return net_backward_bn(g, params, B, saved, g_phi, g_logq, g_logq_vec, LFS_BN_BATCH, nullptr, g_params,
-                         g_z, ws, st);
-}
-
 }  // namespace lfs

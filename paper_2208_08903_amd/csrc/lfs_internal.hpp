@@ -40,23 +40,18 @@ int32_t make_geom(const lfs_flow_desc* desc, FlowGeom* g);
 
 inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 
-// Generic kernels: any supported (dim, L, C), activations staged in HBM.
-size_t generic_ws_bytes(const FlowGeom& g, int B, int for_backward);
-int32_t generic_forward(const FlowGeom& g, const float* params, int B, const float* z, float* phi,
-                        double* logq, double* logdet, float* saved, char* ws, hipStream_t st);
-int32_t generic_backward(const FlowGeom& g, const float* params, int B, const float* saved,
+// General kernels: any network without batch norm on any supported lattice.  A forward
+// workspace smaller than general_ws_bytes is used as far as it goes (LFS_EWORKSPACE
+// where not even one sample fits).
+size_t general_ws_bytes(const FlowGeom& g, int B, int for_backward);
+int32_t general_forward(const FlowGeom& g, const float* params, int B, const float* z, float* phi,
+                        double* logq, double* logdet, float* saved, char* ws, size_t ws_bytes, hipStream_t st);
+int32_t general_backward(const FlowGeom& g, const float* params, int B, const float* saved,
                          const float* g_phi, double g_logq, const double* g_logq_vec, float* g_params,
-                         float* g_z, char* ws,
-                         hipStream_t st);
+                         float* g_z, char* ws, hipStream_t st);
 
-// General-network kernels: any hidden_sizes / odd kernel, activations in HBM.
+// Batch-norm flows: direct convolutions, activations in HBM.
 size_t net_ws_bytes(const FlowGeom& g, int B, int for_backward);
-int32_t net_forward(const FlowGeom& g, const float* params, int B, const float* z, float* phi,
-                    double* logq, double* logdet, float* saved, char* ws, hipStream_t st);
-int32_t net_backward(const FlowGeom& g, const float* params, int B, const float* saved,
-                     const float* g_phi, double g_logq, const double* g_logq_vec, float* g_params,
-                     float* g_z, char* ws,
-                     hipStream_t st);
 // Batch-norm variants (g.bn): bn_mode lfs_bn_mode; stats per the statistics
 // layout (running statistics, updated in batch mode if not null).
 int32_t net_forward_bn(const FlowGeom& g, const float* params, int B, const float* z, float* phi,

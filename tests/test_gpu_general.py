@@ -1,0 +1,70 @@
+"""The general kernels at the sizes where they can go wrong, against the FP64 oracle with
+the tolerances of the default network's tests: kernels wider than the lattice, several
+row tiles with channels that are no multiple of four, fragments too large for the LDS,
+samples too large for it (one launch per convolution), several layer groups, and the
+allocation-free forward whose scratch has no room for all fragments."""
+import numpy as np
+import pytest
+import torch
+
+import seeded_inputs as si
+from oracle import flow as of
+from paper_2208_08903_amd import lfs
+
+from .gpu_util import dev, host, run_forward
+from .test_gpu_parity import _check_backward, _check_forward
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # dim, L, N, kernel, hidden_sizes, B
+    (2, 2, 2, 7, (5,), 3),            # every tap wraps more than once
+    (2, 6, 2, 3, (20, 33), 2),        # two and three row tiles, ragged channels
+    (2, 10, 1, 3, (64, 2, 17), 2),
+    (3, 4, 2, 5, (24, 24), 2),        # a layer's fragments exceed the LDS
+    (2, 34, 2, 3, (16, 16), 2),       # a sample's state exceeds the LDS
+    (3, 10, 2, 3, (32, 8), 3),
+    (2, 8, 17, 3, (12, 12), 5),       # odd number of layers
+]
+
+
+def _case(dim, L, N, K, hs, B, precision):
+    desc = lfs.make_desc(dim, L, N, 0, precision=precision, kernel=K, hidden_sizes=hs)
+    params = si.flow_params(dim, N, 0, seed=900 + L + K, w_std=0.05, b_std=0.05, kernel=K, hidden_sizes=hs)
+    z = si.normal_fields(700 + L, B, L ** dim)
+    return desc, params, z, of.FlowShape(dim, L, N, 0, kernel=K, hidden_sizes=hs)
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_general_forward_backward(case):
+    print(f"general kernels {case}", flush=True)
+    desc, params, z, fs = _case(*case, lfs.LFS_PLAIN_FP32)
+    out, _ = _check_forward(desc, params, z, fs, lfs.LFS_PLAIN_FP32)
+    _check_backward(desc, params, z, fs, out, lfs.LFS_PLAIN_FP32)
+
+
+@pytest.mark.parametrize("case", [CASES[1], CASES[4], CASES[5]])
+def test_general_forward_bf16(case):
+    print(f"general kernels, BF16, {case}", flush=True)
+    desc, params, z, fs = _case(*case, lfs.LFS_BF16_CONV)
+    _check_forward(desc, params, z, fs, lfs.LFS_BF16_CONV, rho=0.6)
+
+
+@pytest.mark.parametrize("B", [1, 7])
+def test_noalloc_without_room_for_fragments(B):
+    """343 taps of 64 x 64 channels: 5.5 MB of fragments per convolution in 8 MiB of scratch."""
+    desc, params, z, fs = _case(3, 4, 2, 7, (64, 64), B, lfs.LFS_PLAIN_FP32)
+    assert lfs.workspace_bytes(desc, B, False) > lfs.NOALLOC_SCRATCH_BYTES
+    ref = run_forward(desc, params, z)
+    phi = torch.full((B, 64), float("nan"), device="cuda")
+    logq = torch.full((B,), float("nan"), device="cuda", dtype=torch.float64)
+    saved = torch.full((3 * B * 64,), float("nan"), device="cuda")
+    lfs.flow_forward_noalloc(desc, dev(params, torch.float32), dev(z, torch.float32), phi, logq, None, saved)
+    torch.cuda.synchronize()
+    p, r = host(phi), host(ref["phi"])
+    bound = 1e-5 * (343 / 9) * (1 + np.abs(r))
+    assert np.all(np.abs(p - r) <= bound)
+    assert np.all(np.abs(host(logq) - host(ref["logq"])) <= 1e-4 * 64)
+    s = host(saved).reshape(3, B, 64)
+    np.testing.assert_array_equal(s[0], z)
+    np.testing.assert_array_equal(s[2], p)
