@@ -13,8 +13,7 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / kWave;
-constexpr int kAcChunk = 2048;   // series elements per autocovariance workgroup
-constexpr int kAcMaxLag = 8192;  // (chunk + lags) FP64 values staged in LDS: <= 80 KB
+constexpr int kAcMaxLag = 8192;  // lags + 1 FP64 quotients in LDS: 64 KB
 
 // Sum over the workgroup: lanes by butterfly, then the waves in index order.
 // Every thread of the workgroup must call it; all receive the sum.
@@ -26,18 +25,6 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
   double s = 0.0;
 #pragma unroll
   for (int w = 0; w < kWaves; ++w) s += red[w];
-  return s;
-}
-
-__device__ __forceinline__ double block_max(double v, double* red) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, kWave));
-  __syncthreads();
-  if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = v;
-  __syncthreads();
-  double s = red[0];
-#pragma unroll
-  for (int w = 1; w < kWaves; ++w) s = fmax(s, red[w]);
   return s;
 }
 
@@ -92,15 +79,18 @@ __device__ __forceinline__ int64_t series_at(const int64_t* index, int64_t n, in
   return index ? index[(size_t)s * n + k] : k;
 }
 
-// Series mean (strided per-thread sums, then block_sum), and whether any index
-// falls outside [0, ldx).
-__global__ void __launch_bounds__(kThreads) k_ac_mean(int64_t n, const double* __restrict__ x, int64_t ldx,
-                                                     const int64_t* __restrict__ index,
-                                                     double* __restrict__ mean, int32_t* __restrict__ bad) {
+// Sum of one of the nsum segments of series s, and whether any of its indices falls
+// outside [0, ldx).  Segments rather than one workgroup per series: its gathers are bound
+// by latency (65536 elements in one workgroup took 48 us).
+__global__ void __launch_bounds__(kThreads) k_ac_sums(int64_t n, int64_t per, const double* __restrict__ x,
+                                                     int64_t ldx, const int64_t* __restrict__ index,
+                                                     double* __restrict__ sums, int32_t* __restrict__ bad) {
   __shared__ double red[kWaves];
-  const int s = blockIdx.x;
+  const int s = blockIdx.y, o = blockIdx.y * gridDim.x + blockIdx.x;
+  const int64_t k1 = std::min<int64_t>(n, (blockIdx.x + 1) * per);
   double acc = 0.0, nbad = 0.0;
-  for (int64_t k = threadIdx.x; k < n; k += kThreads) {
+#pragma unroll 4
+  for (int64_t k = blockIdx.x * per + threadIdx.x; k < k1; k += kThreads) {
     const int64_t j = series_at(index, n, s, k);
     if (j < 0 || j >= ldx) {
       nbad += 1.0;
@@ -111,71 +101,129 @@ __global__ void __launch_bounds__(kThreads) k_ac_mean(int64_t n, const double* _
   acc = block_sum(acc, red);
   nbad = block_sum(nbad, red);
   if (threadIdx.x == 0) {
-    mean[s] = acc / (double)n;
-    bad[s] = nbad > 0.0;
+    sums[o] = acc;
+    bad[o] = nbad > 0.0;
   }
 }
 
-// Partial autocovariance sums of one chunk: elements i0 .. i0 + kAcChunk - 1
-// against i + t for every lag t <= T (deviations from the mean staged in LDS).
-__global__ void __launch_bounds__(kThreads) k_ac_partial(int64_t n, int T, const double* __restrict__ x,
-                                                        int64_t ldx, const int64_t* __restrict__ index,
-                                                        const double* __restrict__ mean,
+// Mean of a series from its segment sums (at most 64, one per lane, fixed butterfly);
+// bad: any segment has an index out of range.
+__device__ __forceinline__ double series_mean(int64_t n, int nsum, const double* sums, const int32_t* bad, bool& isbad) {
+  const int lane = threadIdx.x & (kWave - 1);
+  isbad = __ballot(lane < nsum && bad[lane] != 0) != 0;
+  return wave_sum(lane < nsum ? sums[lane] : 0.0) / (double)n;
+}
+
+// Partial autocovariance sums of one chunk of elements against i + t, for kThreads groups
+// of four consecutive lags: deviations from the mean in LDS, zeros past the series' end.
+// A thread slides over the chunk four elements at a time, so its 16 products take four
+// 16-byte LDS reads (two of them the same for the whole wave), where a thread per lag took
+// two 8-byte reads per product; chunks are short enough to give every CU work: 65536
+// elements, 2001 lags, 115 -> 16 us.
+__global__ void __launch_bounds__(kThreads) k_ac_partial(int64_t n, int T, int chunk, int nsum,
+                                                        const double* __restrict__ x, int64_t ldx,
+                                                        const int64_t* __restrict__ index,
+                                                        const double* __restrict__ sums,
                                                         const int32_t* __restrict__ bad,
                                                         double* __restrict__ partial) {
-  extern __shared__ double d[];  // [kAcChunk + T]
-  const int c = blockIdx.x, s = blockIdx.y, nchunk = gridDim.x;
-  const int64_t i0 = (int64_t)c * kAcChunk;
+  extern __shared__ __align__(16) double d[];  // [chunk + 4 kThreads + 4]
+  typedef double f64x2 __attribute__((ext_vector_type(2)));
+  const int c = blockIdx.x, s = blockIdx.y, nchunk = gridDim.x, t0 = (blockIdx.z * kThreads + threadIdx.x) * 4;
+  const int64_t i0 = (int64_t)c * chunk;
   double* out = partial + ((size_t)s * nchunk + c) * (T + 1);
-  if (bad[s]) {
-    for (int t = threadIdx.x; t <= T; t += kThreads) out[t] = 0.0;
+  bool isbad;
+  const double mu = series_mean(n, nsum, sums + (size_t)s * nsum, bad + (size_t)s * nsum, isbad);
+  if (isbad) {
+    for (int r = 0; r < 4; ++r)
+      if (t0 + r <= T) out[t0 + r] = 0.0;
     return;
   }
-  const int len = (int)std::min<int64_t>(kAcChunk + T, n - i0);
-  const double mu = mean[s];
-  for (int q = threadIdx.x; q < len; q += kThreads) d[q] = x[(size_t)s * ldx + series_at(index, n, s, i0 + q)] - mu;
-  __syncthreads();
-  const int iend = (int)std::min<int64_t>(kAcChunk, n - i0);
-  for (int t = threadIdx.x; t <= T; t += kThreads) {
-    // pairs (i, i + t) with i + t < n - i0
-    const int lim = (int)std::min<int64_t>(iend, n - i0 - t);
-    double acc = 0.0;
-    for (int i = 0; i < lim; ++i) acc += d[i] * d[i + t];
-    out[t] = acc;
+  // d[q]: element i0 + q for q < chunk, then element i0 + lag0 + q - chunk onwards, where
+  // lag0 is the workgroup's first lag
+  const int lag0 = blockIdx.z * kThreads * 4, span = chunk + 4 * kThreads + 4;
+  for (int q = threadIdx.x; q < chunk + span; q += kThreads) {
+    const int64_t k = i0 + (q < chunk ? q : lag0 + q - chunk);
+    d[q] = k < n ? x[(size_t)s * ldx + series_at(index, n, s, k)] - mu : 0.0;
   }
+  __syncthreads();
+  if (t0 > T) return;
+  const f64x2* a = reinterpret_cast<const f64x2*>(d);
+  const f64x2* b = reinterpret_cast<const f64x2*>(d + chunk + 4 * threadIdx.x);
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+  f64x2 b0 = b[0], b1 = b[1];
+#pragma unroll 2
+  for (int i = 0; i < chunk; i += 4) {
+    const f64x2 a0 = a[i / 2], a1 = a[i / 2 + 1], b2 = b[i / 2 + 2], b3 = b[i / 2 + 3];
+    const double av[4] = {a0[0], a0[1], a1[0], a1[1]};
+    const double bv[7] = {b0[0], b0[1], b1[0], b1[1], b2[0], b2[1], b3[0]};
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[r] += av[q] * bv[q + r];
+    b0 = b2;
+    b1 = b3;
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    if (t0 + r <= T) out[t0 + r] = acc[r];
 }
 
-// Gamma(t) = (chunk partials summed in chunk order) / (n - t), then the
-// Madras-Sokal window by one thread: tau = 1/2 + sum_{t=1}^{W} Gamma(t) / Gamma(0)
-// for W = 1, 2, ... until W >= c tau.
-__global__ void __launch_bounds__(kThreads) k_ac_final(int64_t n, int T, int nchunk, int w_max, double cwin,
+// Gamma(t) = (chunk partials summed in chunk order within each of four slices, the slices
+// in order) / (n - t): 64 lags per workgroup.
+__global__ void __launch_bounds__(kThreads) k_ac_gamma(int64_t n, int T, int nchunk, int w_max, int nsum,
                                                       const double* __restrict__ partial,
-                                                      const int32_t* __restrict__ bad, double* __restrict__ gamma,
-                                                      double* __restrict__ tau, int32_t* __restrict__ window,
-                                                      uint8_t* __restrict__ found, double* __restrict__ n_indep) {
-  extern __shared__ double g[];  // [T + 1]
-  const int s = blockIdx.x;
-  const bool isbad = bad[s] != 0;
-  const double nan = __builtin_nan("");
-  for (int t = threadIdx.x; t <= T; t += kThreads) {
-    double acc = 0.0;
-    for (int c = 0; c < nchunk; ++c) acc += partial[((size_t)s * nchunk + c) * (T + 1) + t];
-    g[t] = isbad ? nan : acc / (double)(n - t);
+                                                      const int32_t* __restrict__ bad, double* __restrict__ g,
+                                                      double* __restrict__ gamma) {
+  __shared__ double sh[kWaves][kWave];
+  const int s = blockIdx.y, lane = threadIdx.x & (kWave - 1), sl = threadIdx.x / kWave;
+  const int t = blockIdx.x * kWave + lane;
+  bool isbad = false;
+  for (int k = 0; k < nsum; ++k) isbad |= bad[(size_t)s * nsum + k] != 0;
+  double acc = 0.0;
+  if (t <= T) {
+    const int c1 = (int)((int64_t)nchunk * (sl + 1) / kWaves);
+#pragma unroll 8
+    for (int c = (int)((int64_t)nchunk * sl / kWaves); c < c1; ++c) acc += partial[((size_t)s * nchunk + c) * (T + 1) + t];
   }
+  sh[sl][lane] = acc;
   __syncthreads();
-  if (gamma)
-    for (int t = threadIdx.x; t <= w_max; t += kThreads) gamma[(size_t)s * (w_max + 1) + t] = t <= T ? g[t] : nan;
+  if (sl != 0) return;
+  const double nan = __builtin_nan("");
+  double v = sh[0][lane];
+#pragma unroll
+  for (int k = 1; k < kWaves; ++k) v += sh[k][lane];
+  v = isbad ? nan : v / (double)(n - t);
+  if (t <= T) g[(size_t)s * (T + 1) + t] = v;
+  if (gamma && t <= w_max) gamma[(size_t)s * (w_max + 1) + t] = t <= T ? v : nan;
+}
+
+// The Madras-Sokal window by one thread: tau = 1/2 + sum_{t=1}^{W} Gamma(t) / Gamma(0)
+// for W = 1, 2, ... until W >= c tau (the quotients formed by all threads).
+__global__ void __launch_bounds__(kThreads) k_ac_final(int64_t n, int T, double cwin, int nsum,
+                                                      const double* __restrict__ gin,
+                                                      const int32_t* __restrict__ bad, double* __restrict__ tau,
+                                                      int32_t* __restrict__ window, uint8_t* __restrict__ found,
+                                                      double* __restrict__ n_indep) {
+  extern __shared__ __align__(16) double rho[];  // [T + 1]
+  const int s = blockIdx.x;
+  const double* g = gin + (size_t)s * (T + 1);
+  const double g0 = g[0];
+  for (int t = threadIdx.x; t <= T; t += kThreads) rho[t] = g[t] / g0;
+  __syncthreads();
   if (threadIdx.x != 0) return;
+  bool isbad = false;
+  for (int k = 0; k < nsum; ++k) isbad |= bad[(size_t)s * nsum + k] != 0;
+  const double nan = __builtin_nan("");
   double tv = nan, ni = 0.0;
   int W = 0;
   uint8_t fo = 0;
   if (isbad) {
     W = -1;
     ni = nan;
-  } else if (g[0] != 0.0) {
+  } else if (g0 != 0.0) {
     tv = 0.5;
     for (W = 1; W <= T; ++W) {
-      tv += g[W] / g[0];
+      tv += rho[W];
       if ((double)W >= cwin * tv) {
         fo = 1;
         break;
@@ -190,37 +238,67 @@ __global__ void __launch_bounds__(kThreads) k_ac_final(int64_t n, int T, int nch
   if (n_indep) n_indep[s] = ni;
 }
 
-// Normalised ESS of series s: (sum e^{w - max})^2 / (n sum e^{2 (w - max)}).
-__global__ void __launch_bounds__(kThreads) k_ess(int64_t n, const double* __restrict__ logw, int64_t ldw,
-                                                 double* __restrict__ ess) {
-  __shared__ double red[kWaves];
+// Normalised ESS of series s: (sum e^{w - max})^2 / (n sum e^{2 (w - max)}).  One
+// workgroup per series (there is no workspace to combine several in): 1024 threads, eight
+// loads of each in flight (65536 log-weights: 72 -> 29 us against 256 threads loading one
+// at a time).
+__global__ void __launch_bounds__(1024) k_ess(int64_t n, const double* __restrict__ logw, int64_t ldw,
+                                              double* __restrict__ ess) {
+  constexpr int U = 8;
+  __shared__ double red[16];
   const double* w = logw + (size_t)blockIdx.x * ldw;
+  const int64_t step = blockDim.x;
   double mx = -HUGE_VAL;
-  for (int64_t k = threadIdx.x; k < n; k += kThreads) mx = fmax(mx, w[k]);
-  mx = block_max(mx, red);
-  double s1 = 0.0, s2 = 0.0;
-  for (int64_t k = threadIdx.x; k < n; k += kThreads) {
-    const double e = exp(w[k] - mx);
-    s1 += e;
-    s2 += e * e;
+  for (int64_t k = threadIdx.x; k < n; k += U * step) {
+    double v[U];
+#pragma unroll
+    for (int i = 0; i < U; ++i) v[i] = k + i * step < n ? w[k + i * step] : -HUGE_VAL;
+#pragma unroll
+    for (int i = 0; i < U; ++i) mx = fmax(mx, v[i]);
   }
-  s1 = block_sum(s1, red);
-  s2 = block_sum(s2, red);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, kWave));
+  if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = mx;
+  __syncthreads();
+  mx = red[0];
+  for (int i = 1; i < (int)(blockDim.x / kWave); ++i) mx = fmax(mx, red[i]);
+  double s1 = 0.0, s2 = 0.0;
+  for (int64_t k = threadIdx.x; k < n; k += U * step) {
+    double v[U];
+#pragma unroll
+    for (int i = 0; i < U; ++i) v[i] = k + i * step < n ? w[k + i * step] : -HUGE_VAL;
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      if (k + i * step >= n) break;
+      const double e = exp(v[i] - mx);
+      s1 += e;
+      s2 += e * e;
+    }
+  }
+  s1 = lfs::block_sum(s1, red);
+  s2 = lfs::block_sum(s2, red);
   if (threadIdx.x == 0) ess[blockIdx.x] = s1 * s1 / ((double)n * s2);
 }
 
 struct AcLayout {
-  int T, nchunk;
-  size_t off_bad, off_partial, total;
+  int T, chunk, nchunk, nsum;
+  int64_t per;  // elements of a segment sum
+  size_t off_bad, off_gamma, off_partial, total;
 };
 
 AcLayout ac_layout(int32_t n_series, int64_t n, int32_t w_max) {
   AcLayout a{};
   a.T = (int)std::min<int64_t>(w_max, n - 1);
-  a.nchunk = (int)((n + kAcChunk - 1) / kAcChunk);
+  // chunks of 512 elements (128 workgroups times the lag groups at 65536), of 2048 in longer
+  // series, which fill the chip anyway
+  a.chunk = n <= 131072 ? 512 : 2048;
+  a.nchunk = (int)((n + a.chunk - 1) / a.chunk);
+  a.nsum = (int)std::min<int64_t>(kWave, (n + 1023) / 1024);
+  a.per = (n + a.nsum - 1) / a.nsum;
   const auto up = [](size_t b) { return (b + 255) / 256 * 256; };
-  a.off_bad = up((size_t)n_series * sizeof(double));
-  a.off_partial = a.off_bad + up((size_t)n_series * sizeof(int32_t));
+  a.off_bad = up((size_t)n_series * a.nsum * sizeof(double));
+  a.off_gamma = a.off_bad + up((size_t)n_series * a.nsum * sizeof(int32_t));
+  a.off_partial = a.off_gamma + up((size_t)n_series * (a.T + 1) * sizeof(double));
   a.total = a.off_partial + up((size_t)n_series * a.nchunk * (a.T + 1) * sizeof(double));
   return a;
 }
@@ -267,27 +345,29 @@ extern "C" int32_t lfs_autocorr(int32_t n_series, int64_t n, const double* x, in
   LFS_RETURN_IF(ws_bytes < a.total, LFS_EWORKSPACE);
   LFS_RETURN_IF(a.nchunk > (1 << 30), LFS_EUNSUPPORTED);
   char* base = static_cast<char*>(ws);
-  double* mean = reinterpret_cast<double*>(base);
+  double* sums = reinterpret_cast<double*>(base);
   int32_t* bad = reinterpret_cast<int32_t*>(base + a.off_bad);
+  double* g = reinterpret_cast<double*>(base + a.off_gamma);
   double* partial = reinterpret_cast<double*>(base + a.off_partial);
-  const size_t shm_partial = (size_t)(lfs::kAcChunk + a.T) * sizeof(double);
-  if (shm_partial > 64 * 1024 &&
-      hipFuncSetAttribute(reinterpret_cast<const void*>(lfs::k_ac_partial),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm_partial) != hipSuccess)
-    return LFS_EDEVICE;
+  const size_t shm_partial = (size_t)(2 * a.chunk + 4 * lfs::kThreads + 4) * sizeof(double);
+  const size_t shm_final = (size_t)(a.T + 1) * sizeof(double);
+  if (!lfs::set_lds_limit<lfs::k_ac_final>((lfs::kAcMaxLag + 1) * sizeof(double))) return LFS_EDEVICE;
   hipStream_t st = (hipStream_t)stream;
-  hipLaunchKernelGGL(lfs::k_ac_mean, dim3(n_series), dim3(lfs::kThreads), 0, st, n, x, ldx, index, mean, bad);
-  hipLaunchKernelGGL(lfs::k_ac_partial, dim3(a.nchunk, n_series), dim3(lfs::kThreads), shm_partial, st, n, a.T, x, ldx, index, mean, bad,
-                     partial);
-  hipLaunchKernelGGL(lfs::k_ac_final, dim3(n_series), dim3(lfs::kThreads), (size_t)(a.T + 1) * sizeof(double),
-                     st, n, a.T, a.nchunk, w_max, c, partial, bad, gamma, tau, window, found, n_indep);
+  hipLaunchKernelGGL(lfs::k_ac_sums, dim3(a.nsum, n_series), dim3(lfs::kThreads), 0, st, n, a.per, x, ldx, index, sums,
+                     bad);
+  hipLaunchKernelGGL(lfs::k_ac_partial, dim3(a.nchunk, n_series, a.T / (4 * lfs::kThreads) + 1), dim3(lfs::kThreads),
+                     shm_partial, st, n, a.T, a.chunk, a.nsum, x, ldx, index, sums, bad, partial);
+  hipLaunchKernelGGL(lfs::k_ac_gamma, dim3((unsigned)std::max(a.T, gamma ? w_max : 0) / lfs::kWave + 1, n_series),
+                     dim3(lfs::kThreads), 0, st, n, a.T, a.nchunk, w_max, a.nsum, partial, bad, g, gamma);
+  hipLaunchKernelGGL(lfs::k_ac_final, dim3(n_series), dim3(lfs::kThreads), shm_final, st, n, a.T, c, a.nsum, g, bad,
+                     tau, window, found, n_indep);
   return lfs::launch_status();
 }
 
 extern "C" int32_t lfs_ess(int32_t n_series, int64_t n, const double* logw, int64_t ldw, double* ess,
                            void* stream) {
   LFS_RETURN_IF(n_series < 1 || n < 1 || ldw < n || !logw || !ess, LFS_EINVAL);
-  hipLaunchKernelGGL(lfs::k_ess, dim3(n_series), dim3(lfs::kThreads), 0, (hipStream_t)stream, n, logw, ldw,
+  hipLaunchKernelGGL(lfs::k_ess, dim3(n_series), dim3(1024), 0, (hipStream_t)stream, n, logw, ldw,
                      ess);
   return lfs::launch_status();
 }

@@ -1,0 +1,86 @@
+"""The chain and analysis kernels at the edges of their chunks, against the oracle: MH chains
+around the length from which two launches are used and around whole chunks of 64, with
+log-weights that compare in every way (infinities, NaN, ties, none and all accepted),
+continued over calls; autocorrelation around its chunks and lag groups.  Decisions are
+bit-exact; FP64 sums in another order: 1e-12 relative, as in the analysis tests."""
+import numpy as np
+import pytest
+import torch
+
+import seeded_inputs as si
+from oracle import analysis as an
+from oracle import mh as om
+from paper_2208_08903_amd import lfs
+
+from .gpu_util import dev, host
+
+pytestmark = pytest.mark.gpu
+
+
+def _weights(kind, n, seed):
+    w = si.logw_stream(seed, n, 1.0)
+    lu = si.log_uniforms(seed + 1, n)
+    if kind == "wild":
+        r = np.random.default_rng(seed + 2)
+        for v in (np.inf, -np.inf, np.nan, 0.0, -0.0):
+            w[r.integers(0, n, max(1, n // 40))] = v
+        lu[r.integers(0, n, max(1, n // 40))] = -np.inf
+    elif kind == "ties":
+        w = np.round(w * 2) / 2
+        lu = np.round(lu * 2) / 2
+    elif kind == "rising":
+        w = np.arange(n, dtype=np.float64)
+    elif kind == "falling":
+        w = -1e6 * np.arange(n, dtype=np.float64)
+    return w, lu
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 130, 511, 512, 513, 1024, 1300])
+@pytest.mark.parametrize("kind", ["normal", "wild", "ties", "rising", "falling"])
+def test_mh_chain_edges(n, kind):
+    print(f"mh chain n={n} {kind}", flush=True)
+    chains = 3
+    W, U = zip(*(_weights(kind, 2 * n, 50 + 10 * c) for c in range(chains)))
+    W, U = np.stack(W), np.stack(U)
+    state = lfs.new_chain_state(chains)
+    cur = np.empty((chains, 2 * n), np.int64)
+    acc = np.empty((chains, 2 * n), np.uint8)
+    for k in range(2):  # the chain goes on over two calls
+        sl = slice(k * n, (k + 1) * n)
+        c = torch.empty(chains, n, dtype=torch.int64, device="cuda")
+        a = torch.empty(chains, n, dtype=torch.uint8, device="cuda")
+        lfs.mh_chain(dev(W[:, sl], torch.float64), dev(U[:, sl], torch.float64), state, c, a)
+        cur[:, sl], acc[:, sl] = host(c), host(a)
+    st = lfs.decode_chain_state(state)
+    for i in range(chains):
+        with np.errstate(invalid="ignore"):
+            co, ao, _ = om.mh_chain(W[i], U[i])
+        np.testing.assert_array_equal(cur[i], co)
+        np.testing.assert_array_equal(acc[i], np.asarray(ao, np.uint8))
+        assert st[i]["n_seen"] == 2 * n and st[i]["n_acc"] == int(np.sum(ao)) - 1 and st[i]["idx_cur"] == co[-1]
+
+
+@pytest.mark.parametrize("n,w_max", [(511, 100), (512, 511), (513, 600), (1500, 1023), (2600, 1024), (5000, 2047),
+                                     (140000, 300)])
+def test_autocorr_edges(n, w_max):
+    print(f"autocorr n={n} w_max={w_max}", flush=True)
+    x = si.correlated_series(70, 2, n, 0.7)
+    gamma = torch.empty(2, w_max + 1, dtype=torch.float64, device="cuda")
+    tau = torch.empty(2, dtype=torch.float64, device="cuda")
+    lfs.autocorr(dev(x, torch.float64), w_max, 6.0, tau, gamma=gamma)
+    torch.cuda.synchronize()
+    g = host(gamma)
+    for s in range(2):
+        d = x[s] - x[s].mean()
+        T = min(w_max, n - 1)
+        for t in {0, 1, 3, 4, 7, T - 1, T} | ({255, 256, 1023, 1024} & set(range(T + 1))):
+            assert abs(g[s, t] - d[:n - t] @ d[t:] / (n - t)) <= 1e-12 * g[s, 0]
+        assert np.all(np.isnan(g[s, T + 1:]))
+
+
+@pytest.mark.parametrize("n", [1, 1023, 1024, 8191, 8192, 8193, 20000])
+def test_ess_edges(n):
+    w = si.logw_stream(80, n, 2.0) - 700.0
+    out = torch.empty(1, dtype=torch.float64, device="cuda")
+    lfs.ess(dev(w, torch.float64), out)
+    assert abs(float(out.item()) - an.ess(w)) <= 1e-12
