@@ -85,16 +85,62 @@ __device__ __forceinline__ float leaky(float a) {
 // LeakyReLU'(a) from its output h = leaky(a): sign(h) == sign(a), h == 0 iff a == 0.
 __device__ __forceinline__ float leaky_grad_from_out(float h) { return h >= 0.f ? 1.f : kLeakySlope; }
 
+// v + (v of lane ^ O), for the butterfly below.  Lane exchanges within a row of 16 are DPP
+// moves, those across rows the permlane swaps (of two copies of v each then holds one
+// half's values in both halves): about 20 cycles a step for FP32, where a shuffle through
+// the LDS crossbar takes about 130.
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_mov(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xf, 0xf, false);
+}
+template <int O>
+__device__ __forceinline__ void xor_pair(uint32_t v, uint32_t& a, uint32_t& b) {
+  static_assert(O == 32 || O == 16 || O == 8 || O == 4 || O == 2 || O == 1, "a power of two below the wave size");
+  if constexpr (O == 32) {
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    a = r[0];
+    b = r[1];
+  } else if constexpr (O == 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    a = r[0];
+    b = r[1];
+  } else {
+    a = v;
+    if constexpr (O == 8) b = dpp_mov<0x128>(v);               // row_ror:8
+    if constexpr (O == 4) b = dpp_mov<0x1B>(dpp_mov<0x141>(v));  // row_half_mirror (^7), quad_perm 3210 (^3)
+    if constexpr (O == 2) b = dpp_mov<0x4E>(v);                // quad_perm 2301
+    if constexpr (O == 1) b = dpp_mov<0xB1>(v);                // quad_perm 1032
+  }
+}
+template <int O>
+__device__ __forceinline__ float xor_add(float v) {
+  uint32_t a, b;
+  xor_pair<O>(__float_as_uint(v), a, b);
+  return __uint_as_float(a) + __uint_as_float(b);
+}
+template <int O>
+__device__ __forceinline__ double xor_add(double v) {
+  const uint64_t u = (uint64_t)__double_as_longlong(v);
+  uint32_t al, bl, ah, bh;
+  xor_pair<O>((uint32_t)u, al, bl);
+  xor_pair<O>((uint32_t)(u >> 32), ah, bh);
+  return __longlong_as_double((long long)((uint64_t)ah << 32 | al)) +
+         __longlong_as_double((long long)((uint64_t)bh << 32 | bl));
+}
+
 // Sum over the 64 lanes of a wavefront, fixed butterfly order (deterministic).
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-  return v;
+  v = xor_add<32>(v);
+  v = xor_add<16>(v);
+  v = xor_add<8>(v);
+  v = xor_add<4>(v);
+  v = xor_add<2>(v);
+  return xor_add<1>(v);
 }
 
 // Sum over a block (blockDim.x a multiple of 64, at most 1024).  `sh` holds 16 T.
-// Waves are combined in index order by thread 0, so the result is deterministic.
+// Every thread adds the waves' sums in index order, so the result is deterministic.
 template <typename T>
 __device__ __forceinline__ T block_sum(T v, T* sh) {
   v = wave_sum(v);
@@ -103,13 +149,13 @@ __device__ __forceinline__ T block_sum(T v, T* sh) {
   __syncthreads();
   if (lane == 0) sh[w] = v;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    T r = sh[0];
-    for (int i = 1; i < nw; ++i) r += sh[i];
-    sh[0] = r;
-  }
-  __syncthreads();
-  T r = sh[0];
+  T part[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) part[i] = sh[i];  // (sums past the last wave are not used)
+  T r = part[0];
+#pragma unroll
+  for (int i = 1; i < 16; ++i)
+    if (i < nw) r += part[i];
   __syncthreads();
   return r;
 }
