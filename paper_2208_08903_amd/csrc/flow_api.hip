@@ -100,7 +100,7 @@ size_t ws_bytes_of(const FlowGeom& g, int B, int bwd) {
   switch (family(g, bwd)) {
     case Family::Fused: return fused_ws_bytes(g, B, bwd);
     case Family::General: return general_ws_bytes(g, B, bwd);
-    default: return net_ws_bytes(g, B, bwd);
+    default: return bn_resident(g) ? bn_ws_bytes(g, B, bwd) : net_ws_bytes(g, B, bwd);
   }
 }
 
@@ -283,9 +283,10 @@ extern "C" int32_t lfs_flow_forward_bn(const lfs_flow_desc* desc, const float* p
   if (B == 0) return LFS_OK;
   if (!params || !z || !phi || !logq) return LFS_EINVAL;
   if (bn_mode == LFS_BN_RUNNING && !bn_stats) return LFS_EINVAL;
-  const size_t need = lfs::net_ws_bytes(g, B, 0);
+  const size_t need = lfs::ws_bytes_of(g, B, 0);
   if (!ws || ws_bytes < need) return LFS_EWORKSPACE;
-  return lfs::net_forward_bn(g, params, B, z, phi, logq, logdet, saved_x, bn_mode, bn_stats,
+  const auto run = lfs::bn_resident(g) ? lfs::bn_forward : lfs::net_forward_bn;
+  return run(g, params, B, z, phi, logq, logdet, saved_x, bn_mode, bn_stats,
                              (float)momentum, (char*)ws, (hipStream_t)stream);
 }
 
@@ -304,9 +305,10 @@ extern "C" int32_t lfs_flow_backward_bn(const lfs_flow_desc* desc, const float* 
   if (bn_mode != LFS_BN_BATCH && bn_mode != LFS_BN_RUNNING) return LFS_EINVAL;
   if (bn_mode == LFS_BN_RUNNING && !bn_stats) return LFS_EINVAL;
   if (desc->algo == LFS_ALGO_FUSED) return LFS_EUNSUPPORTED;
-  const size_t need = lfs::net_ws_bytes(g, B, 1);
+  const size_t need = lfs::ws_bytes_of(g, B, 1);
   if (!ws || ws_bytes < need) return LFS_EWORKSPACE;
-  return lfs::net_backward_bn(g, params, B, saved_x, g_phi, g_logq, g_logq_vec, bn_mode, bn_stats,
+  const auto run = lfs::bn_resident(g) ? lfs::bn_backward : lfs::net_backward_bn;
+  return run(g, params, B, saved_x, g_phi, g_logq, g_logq_vec, bn_mode, bn_stats,
                               g_params, g_z, (char*)ws, (hipStream_t)stream);
 }
 

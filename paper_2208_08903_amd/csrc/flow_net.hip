@@ -1,20 +1,14 @@
-// General s/t networks: the example parameter file's hidden_sizes and
-// kernel_size beyond the default two hidden convolutions of C channels with
-// kernel 3.  Per layer the network is conv(1 -> w_1) + LeakyReLU, ...,
-// conv(w_{n-1} -> w_n) + LeakyReLU, conv(w_n -> 2) with an odd kernel K per
-// axis (paper Sec. 1, coupling-layer equation; taps row-major over
-// {-K/2..K/2}^dim, axis 0 slowest).  Direct periodic convolutions with runtime
-// channel counts and the kernel size as a template parameter, kSplit lanes per
-// (sample, site, output channel), activations in HBM.  In BF16 mode every
-// convolution operand is rounded to BF16 and products are accumulated in FP32,
-// as in the other kernel families.
+// Batch-norm flows (the parameter file's use_bn) on lattices whose sample does not fit the
+// LDS: direct periodic convolutions with runtime channel counts and the kernel size as a
+// template parameter, kSplit lanes per (sample, site, output channel), activations in HBM.
+// In BF16 mode every convolution operand is rounded to BF16 and products are accumulated
+// in FP32, as in the other kernel families.
 //
-// Batch norm (the parameter file's use_bn): a hidden convolution's output a is
-// kept, its per-channel statistics are reduced over the batch and all sites in
-// FP64 with a fixed chunk order (two passes: the mean, then the squared
-// deviations), and h = leaky(gamma (a - mean) r + beta), r = 1/sqrt(var + eps),
-// is written next to it.  The backward turns g_y = g_h leaky'(y) into g_a with
-// the per-channel sums of g_y xhat and g_y.
+// A hidden convolution's output a is kept, its per-channel statistics are reduced over the
+// batch and all sites in FP64 with a fixed chunk order (two passes: the mean, then the
+// squared deviations), and h = leaky(gamma (a - mean) r + beta), r = 1/sqrt(var + eps),
+// is written next to it.  The backward turns g_y = g_h leaky'(y) into g_a with the
+// per-channel sums of g_y xhat and g_y.
 #include <type_traits>
 
 #include "lfs_common.hpp"

@@ -50,10 +50,18 @@ int32_t general_backward(const FlowGeom& g, const float* params, int B, const fl
                          const float* g_phi, double g_logq, const double* g_logq_vec, float* g_params,
                          float* g_z, char* ws, hipStream_t st);
 
-// Batch-norm flows: direct convolutions, activations in HBM.
+// Batch-norm flows whose sample fits the LDS; bn_mode lfs_bn_mode; stats per the
+// statistics layout (running statistics, updated in batch mode if not null).
+bool bn_resident(const FlowGeom& g);
+size_t bn_ws_bytes(const FlowGeom& g, int B, int for_backward);
+int32_t bn_forward(const FlowGeom& g, const float* params, int B, const float* z, float* phi, double* logq,
+                   double* logdet, float* saved, int bn_mode, float* stats, float momentum, char* ws, hipStream_t st);
+int32_t bn_backward(const FlowGeom& g, const float* params, int B, const float* saved, const float* g_phi,
+                    double g_logq, const double* g_logq_vec, int bn_mode, const float* stats, float* g_params,
+                    float* g_z, char* ws, hipStream_t st);
+
+// Batch-norm flows on larger lattices: direct convolutions, activations in HBM.
 size_t net_ws_bytes(const FlowGeom& g, int B, int for_backward);
-// Batch-norm variants (g.bn): bn_mode lfs_bn_mode; stats per the statistics
-// layout (running statistics, updated in batch mode if not null).
 int32_t net_forward_bn(const FlowGeom& g, const float* params, int B, const float* z, float* phi,
                        double* logq, double* logdet, float* saved, int bn_mode, float* stats,
                        float momentum, char* ws, hipStream_t st);

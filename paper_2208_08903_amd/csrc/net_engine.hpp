@@ -53,7 +53,7 @@ __device__ __forceinline__ int fdiv(int x, const Magic& g) {
 
 struct Lat {
   int L, V;
-  Magic dL, dLL, dH;  // L, L * L, L / 2
+  Magic dL, dLL, dH, dV;  // L, L * L, L / 2, V (lattices that live in LDS)
 };
 
 enum Mode { kSeq, kTree, kBf16 };
@@ -91,6 +91,8 @@ struct ConvDir {
 
 struct NetDev {
   int dim, N, n_conv, K, T, parity0, final_tanh, mode;
+  Magic dK;
+  int wide;  // K / 2 >= L: tap offsets need reducing modulo L
   Lat lat;
   int cin[kMaxConv], cout[kMaxConv];
   int offW[kMaxConv], offb[kMaxConv];
@@ -99,6 +101,8 @@ struct NetDev {
   int frags_fwd, frags_all;  // fragments per layer: forward only, both directions
   int hplane[kMaxConv];      // first plane of hidden activation i (hidden planes in order)
   int hplanes;               // planes of all hidden activations
+  int bn;                    // batch norm: gamma (beta at + cout) of hidden convolution i at offg[i]
+  int offg[LFS_MAX_HIDDEN];
 };
 
 inline NetDev make_net(const FlowGeom& g) {
@@ -108,11 +112,14 @@ inline NetDev make_net(const FlowGeom& g) {
   d.n_conv = g.n_conv;
   d.K = g.K;
   d.T = g.T;
+  d.dK = magic(g.K);
+  d.wide = g.K / 2 >= g.L;
   d.parity0 = g.parity0;
   d.final_tanh = g.final_tanh;
   d.mode = g.bf16() ? kBf16 : g.net_default ? kSeq : kTree;
-  d.lat = Lat{g.L, g.V, magic(g.L), magic(g.L * g.L), magic(g.L / 2)};
+  d.lat = Lat{g.L, g.V, magic(g.L), magic(g.L * g.L), magic(g.L / 2), magic(g.V)};
   d.P_layer = (int)g.P_layer;
+  d.bn = g.bn;
   int off = 0;
   for (int dir = 0; dir < 2; ++dir) {
     for (int i = 0; i < g.n_conv; ++i) {
@@ -142,6 +149,7 @@ inline NetDev make_net(const FlowGeom& g) {
     d.offb[i] = (int)g.offb[i];
     d.hplane[i] = d.hplanes;
     if (i + 1 < g.n_conv) d.hplanes += cdiv(g.cout[i], 4);
+    if (g.bn && i + 1 < g.n_conv) d.offg[i] = (int)g.offg[i];
   }
   return d;
 }
@@ -282,7 +290,9 @@ __device__ __forceinline__ int tap_entry(const NetDev& d, int tap, int sign) {
   int e = 0, p = 0, t = tap;
 #pragma unroll
   for (int mu = DIM - 1; mu >= 0; --mu) {
-    const int q = t / d.K, o = (t - q * d.K - (d.K >> 1)) % d.lat.L;
+    const int q = fdiv(t, d.dK);
+    int o = t - q * d.K - (d.K >> 1);
+    if (d.wide) o %= d.lat.L;
     e |= (sign * o + 8) << (4 * mu);
     p += o;
     t = q;
@@ -317,7 +327,7 @@ template <int DIM>
 __device__ __forceinline__ void build_nbr(const NetDev& d, uint16_t* nb) {
   const Lat& lat = d.lat;
   for (int k = threadIdx.x; k < (d.T + 1) * lat.V; k += blockDim.x) {
-    const int t = k / lat.V, n = k - t * lat.V;
+    const int t = fdiv(k, lat.dV), n = k - t * lat.V;
     nb[k] = (uint16_t)(t < d.T ? nbr_site<DIM>(lat, site_of<DIM>(lat, n), tap_entry<DIM>(d, t, 1)) : lat.V);
   }
 }

@@ -68,3 +68,25 @@ def test_noalloc_without_room_for_fragments(B):
     s = host(saved).reshape(3, B, 64)
     np.testing.assert_array_equal(s[0], z)
     np.testing.assert_array_equal(s[2], p)
+
+
+@pytest.mark.parametrize("L,hs,B", [(8, (20, 6), 9), (8, (8, 8), 300), (34, (16, 16), 2)])
+@pytest.mark.parametrize("mode", [lfs.BN_BATCH, lfs.BN_RUNNING])
+def test_batch_norm_shapes(L, hs, B, mode):
+    """Batch norm with several row tiles and ragged channels, with more samples than
+    workgroups, and with a sample too large for the LDS: the tolerances of the batch-norm
+    tests."""
+    from . import test_gpu_bn as bn
+    print(f"batch norm L={L} hidden={hs} B={B} mode={mode}", flush=True)
+    desc, params, z, stats, fs = bn._case(2, L, 2, 3, hs, B, lfs.LFS_PLAIN_FP32)
+    out = bn._forward(desc, params, z, mode, stats)
+    f = of.flow_forward(params.astype(np.float64), z.astype(np.float64), fs,
+                        bn_stats=None if mode == lfs.BN_BATCH else of.unpack_bn_stats(stats.astype(np.float64), fs))
+    ref = f["phi"].reshape(B, -1)
+    assert np.all(np.abs(host(out["phi"]) - ref) <= 1e-5 * (1 + np.abs(ref)))
+    g_phi = np.random.default_rng(4).standard_normal(z.shape).astype(np.float32)
+    gp, gz = bn._backward(desc, out, g_phi, 0.37, mode)
+    go, zo = of.flow_vjp(params.astype(np.float64), z.astype(np.float64), fs, g_phi.astype(np.float64), 0.37,
+                         bn_stats=None if mode == lfs.BN_BATCH else of.unpack_bn_stats(stats.astype(np.float64), fs))
+    assert np.linalg.norm(gp - go) <= 1e-4 * np.linalg.norm(go)
+    assert np.linalg.norm(gz - zo) <= 1e-4 * np.linalg.norm(zo)
