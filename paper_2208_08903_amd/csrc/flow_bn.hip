@@ -24,10 +24,10 @@ constexpr int kMaxC = 64;  // hidden_sizes entries are at most 64
 
 __device__ __forceinline__ float bn_xhat(float a, double mean, double r) { return (float)(((double)a - mean) * r); }
 
-// LDS of a workgroup, byte offsets: the field, the input and output planes of a
+// LDS of a workgroup, byte offsets: the masked field, the input and output planes of a
 // convolution, tables, per-channel numbers and the convolution's fragments (lf).
 struct BnLds {
-  int ps, xs, in, out, red, nbr, odd, st, ab, frags, total;
+  int ps, xs, in, out, red, nbr, st, ab, frags, total;
   bool lf;
 };
 BnLds bn_lds(const NetDev& d) {
@@ -49,8 +49,7 @@ BnLds bn_lds(const NetDev& d) {
   r.in = take(4ll * r.ps * q);
   r.out = take(4ll * r.ps * q);
   r.red = take(1024ll * kResWaves);
-  r.nbr = take(2ll * (d.T + 1) * V);
-  r.odd = take(4ll * (d.T + 1));
+  r.nbr = take(nbr_bytes(d.T, V));
   r.st = take(8ll * 6 * kMaxC);
   r.ab = take(4ll * 2 * kMaxC);
   r.lf = off + f * 1024ll <= (int64_t)kLdsMax;
@@ -62,8 +61,6 @@ BnLds bn_lds(const NetDev& d) {
 template <int DIM>
 __device__ __forceinline__ void bn_tables(const NetDev& d, const BnLds& S, unsigned char* smem) {
   build_nbr<DIM>(d, reinterpret_cast<uint16_t*>(smem + S.nbr));
-  int* odd = reinterpret_cast<int*>(smem + S.odd);
-  for (int t = threadIdx.x; t <= d.T; t += blockDim.x) odd[t] = t < d.T ? (tap_entry<DIM>(d, t, 1) >> 12) & 1 : 0;
   const int V = d.lat.V;
   if (threadIdx.x == 0) reinterpret_cast<float*>(smem + S.xs)[V] = 0.f;
   const int q = (S.out - S.in) / (4 * S.ps);
@@ -225,7 +222,8 @@ __global__ void __launch_bounds__(64 * kResWaves) kb_conv(NetDev d, BnLds S, BnC
     float* st = A.store + (size_t)b * A.ss;
     const float* xb = A.x + (size_t)b * V;
     if (A.i == 0) {
-      for (int n = threadIdx.x; n < V; n += blockDim.x) xs[n] = xb[n];
+      for (int n = threadIdx.x; n < V; n += blockDim.x)
+        xs[n] = masked(xb[n], (parity_of<DIM>(site_of<DIM>(lat, n)) ^ A.fpar) - 1);
     } else {
       for (int e = threadIdx.x; e < qin * V; e += blockDim.x) {
         const int q = fdiv(e, lat.dV), n = e - q * V;
@@ -255,13 +253,11 @@ __global__ void __launch_bounds__(64 * kResWaves) kb_conv(NetDev d, BnLds S, BnC
         }
       };
       if (A.i == 0) {
-        conv_pass<MODE, false, true, LF>((V + 15) >> 4, c, frags, red, [&](int tile) {
-          const int n = min(tile * 16 + m, V - 1);
-          return LdsField{nbr + n, xs, V, d.T, parity_of<DIM>(site_of<DIM>(lat, n)) ^ A.fpar,
-                          reinterpret_cast<const int*>(smem + S.odd)};
+        conv_pass<MODE, false>((V + 15) >> 4, c, frags, red, [&](int tile) {
+          return lds_field(d, nbr, xs, min(tile * 16 + m, V - 1));
         }, epi);
       } else {
-        conv_pass<MODE, false, false, LF>((V + 15) >> 4, c, frags, red, [&](int tile) {
+        conv_pass<MODE, false>((V + 15) >> 4, c, frags, red, [&](int tile) {
           return lds_planes<false>(d, nbr, S.ps, in, min(tile * 16 + m, V - 1));
         }, epi);
       }
@@ -292,7 +288,7 @@ __global__ void __launch_bounds__(64 * kResWaves) kb_conv(NetDev d, BnLds S, BnC
       const size_t o = (size_t)b * V;
       const int apar = A.fpar ^ 1;
       const float gld = KIND == Kind::Affine && A.gld_vec ? (float)(-A.gld_vec[b]) : A.gld;
-      conv_pass<MODE, false, false, LF>((half + 15) >> 4, c, frags, red, [&](int tile) {
+      conv_pass<MODE, false>((half + 15) >> 4, c, frags, red, [&](int tile) {
         return lds_planes<false>(d, nbr, S.ps, in, half_site<DIM>(lat, min(tile * 16 + m, half - 1), apar));
       }, [&](int tile, int, const f32x4& v) {
         const int a = tile * 16 + m;
@@ -444,14 +440,14 @@ __global__ void __launch_bounds__(64 * kResWaves) kb_grad(NetDev d, BnLds S, BnG
     lds_barrier();
     if constexpr (FIELD) {
       float* gx = A.gx + (size_t)b * V;
-      conv_pass<MODE, true, false, LF>((half + 15) >> 4, c, frags, red, [&](int tile) {
+      conv_pass<MODE, true>((half + 15) >> 4, c, frags, red, [&](int tile) {
         return lds_planes<true>(d, nbr, S.ps, in, half_site<DIM>(lat, min(tile * 16 + m, half - 1), A.fpar));
       }, [&](int tile, int, const f32x4& v) {
         const int a = tile * 16 + m;
         if (j == 0 && a < half) gx[half_site<DIM>(lat, a, A.fpar)] += v[0];
       });
     } else {
-      conv_pass<MODE, true, false, LF>((V + 15) >> 4, c, frags, red, [&](int tile) {
+      conv_pass<MODE, true>((V + 15) >> 4, c, frags, red, [&](int tile) {
         return lds_planes<true>(d, nbr, S.ps, in, min(tile * 16 + m, V - 1));
       }, [&](int tile, int ct, const f32x4& v) {
         const int n = tile * 16 + m, pl = ct * 4 + j;

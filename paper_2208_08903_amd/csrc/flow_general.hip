@@ -20,10 +20,10 @@
 // one barrier to the next, hence one launch for all layers instead of one per
 // convolution, fragments fetched a layer ahead, neighbours from a table and gathers
 // without branches.  Training step of the 2D L = 8 flow with hidden [16, 16, 16], 16
-// layers, batch 64, FP32: 3400 us with a launch per convolution and direct sums, 505 so
-// (forward 155, backward 274, weight gradients 56).  3D L = 12, hidden 16, 12 layers,
-// batch 50, FP32, where a sample does not fit: 47.1 -> 3.9 ms (a hidden convolution of
-// 86400 sites 41 us, its data gradient 22 us; direct sums: 294 and 257).
+// layers, batch 64, FP32: 3400 us with a launch per convolution and direct sums, 440 so
+// (forward 121, backward 246, weight gradients 55).  3D L = 12, hidden 16, 12 layers,
+// batch 50, FP32, where a sample does not fit: 47.1 -> 3.2 ms (a hidden convolution of
+// 86400 sites 25 us, its data gradient 24 us; direct sums: 294 and 257).
 #include "general_common.hpp"
 
 namespace lfs {
@@ -32,7 +32,7 @@ namespace {
 // LDS of a resident workgroup, byte offsets.
 struct ResLds {
   int ps;  // plane stride
-  int xs, gy, go, slot[LFS_MAX_HIDDEN], red, nbr, odd;
+  int xs, xm, gy, go, slot[LFS_MAX_HIDDEN], red, nbr;  // xm: the field at the frozen sites
   int frags[2];               // a layer's weight fragments (lf), see kg_forward and kg_backward
   bool lf;
   int total;
@@ -48,7 +48,8 @@ ResLds res_lds(const NetDev& d, bool bwd) {
     off += (bytes + 15) / 16 * 16;
     return (int)std::min<int64_t>(o, 1 << 30);
   };
-  r.xs = take(4ll * (V + 1));
+  r.xs = take(4ll * V);
+  r.xm = take(4ll * (V + 1));
   if (bwd) {
     r.gy = take(4ll * V);
     r.go = take(4ll * r.ps);
@@ -60,8 +61,7 @@ ResLds res_lds(const NetDev& d, bool bwd) {
     for (int i = 0; i + 1 < d.n_conv; ++i) r.slot[i] = i & 1 ? b : a;
   }
   r.red = take(1024ll * kResWaves);
-  r.nbr = take(2ll * (d.T + 1) * V);
-  r.odd = take(4ll * (d.T + 1));
+  r.nbr = take(nbr_bytes(d.T, V));
   // fragments: two layers' in the forward, one layer's forward and transposed ones in the
   // backward
   const int64_t fr = off;
@@ -79,22 +79,20 @@ ResLds res_lds(const NetDev& d, bool bwd) {
 template <int DIM>
 __device__ __forceinline__ void build_tables(const NetDev& d, const ResLds& S, unsigned char* smem, bool bwd) {
   build_nbr<DIM>(d, reinterpret_cast<uint16_t*>(smem + S.nbr));
-  int* odd = reinterpret_cast<int*>(smem + S.odd);
-  for (int t = threadIdx.x; t <= d.T; t += blockDim.x) odd[t] = t < d.T ? (tap_entry<DIM>(d, t, 1) >> 12) & 1 : 0;
   const int V = d.lat.V;
-  if (threadIdx.x == 0) reinterpret_cast<float*>(smem + S.xs)[V] = 0.f;
+  if (threadIdx.x == 0) reinterpret_cast<float*>(smem + S.xm)[V] = 0.f;
   if (bwd && threadIdx.x < 4) reinterpret_cast<float*>(smem + S.go)[4 * V + threadIdx.x] = 0.f;
   for (int i = 0; i + 1 < d.n_conv; ++i)
     for (int k = threadIdx.x; k < (d.cout[i] + 3) / 4 * 4; k += blockDim.x)
       reinterpret_cast<float*>(smem + S.slot[i])[(k >> 2) * S.ps + 4 * V + (k & 3)] = 0.f;
 }
 
-// The hidden convolutions of one layer from the field xs into the slots.  store(i, plane,
+// The hidden convolutions of one layer from the masked field into the slots.  store(i, plane,
 // site, values) also receives every quad of activation i.  frags: the layer's forward
 // fragments.
-template <int DIM, int MODE, bool LF, class Store>
+template <int MODE, class Store>
 __device__ __forceinline__ void hidden_convs(const NetDev& d, const ResLds& S, unsigned char* smem,
-                                             const u32x4* frags, const float* xs, int fpar, Store&& store) {
+                                             const u32x4* frags, Store&& store) {
   const Lat& lat = d.lat;
   const int lane = threadIdx.x & 63, j = lane >> 4, m = lane & 15;
   f32x4* red = reinterpret_cast<f32x4*>(smem + S.red);
@@ -115,14 +113,12 @@ __device__ __forceinline__ void hidden_convs(const NetDev& d, const ResLds& S, u
       }
     };
     if (i == 0) {
-      conv_pass<MODE, false, true, LF>(tiles, c, frags + c.off * 64, red, [&](int tile) {
-        const int n = min(tile * 16 + m, lat.V - 1);
-        return LdsField{nbr + n, xs, lat.V, d.T,
-                        parity_of<DIM>(site_of<DIM>(lat, n)) ^ fpar, reinterpret_cast<const int*>(smem + S.odd)};
+      conv_pass<MODE, false>(tiles, c, frags + c.off * 64, red, [&](int tile) {
+        return lds_field(d, nbr, reinterpret_cast<const float*>(smem + S.xm), min(tile * 16 + m, lat.V - 1));
       }, epi);
     } else {
       const float* in = reinterpret_cast<const float*>(smem + S.slot[i - 1]);
-      conv_pass<MODE, false, false, LF>(tiles, c, frags + c.off * 64, red, [&](int tile) {
+      conv_pass<MODE, false>(tiles, c, frags + c.off * 64, red, [&](int tile) {
         return lds_planes<false>(d, nbr, S.ps, in, min(tile * 16 + m, lat.V - 1));
       }, epi);
     }
@@ -131,7 +127,7 @@ __device__ __forceinline__ void hidden_convs(const NetDev& d, const ResLds& S, u
 }
 
 // The last convolution at the active sites: f(a, site, o_0, o_1) for the a-th of them.
-template <int DIM, int MODE, bool LF, class F>
+template <int DIM, int MODE, class F>
 __device__ __forceinline__ void last_conv(const NetDev& d, const ResLds& S, unsigned char* smem, const u32x4* frags,
                                           int apar, F&& f) {
   const Lat& lat = d.lat;
@@ -139,7 +135,7 @@ __device__ __forceinline__ void last_conv(const NetDev& d, const ResLds& S, unsi
   const ConvDir& c = d.f[i];
   const uint16_t* nbr = reinterpret_cast<const uint16_t*>(smem + S.nbr);
   const float* in = reinterpret_cast<const float*>(smem + S.slot[i - 1]);
-  conv_pass<MODE, false, false, LF>((half + 15) >> 4, c, frags + c.off * 64, reinterpret_cast<f32x4*>(smem + S.red),
+  conv_pass<MODE, false>((half + 15) >> 4, c, frags + c.off * 64, reinterpret_cast<f32x4*>(smem + S.red),
                                     [&](int tile) {
     return lds_planes<false>(d, nbr, S.ps, in, half_site<DIM>(lat, min(tile * 16 + m, half - 1), apar));
   }, [&](int tile, int, const f32x4& acc) {
@@ -161,6 +157,7 @@ __global__ void __launch_bounds__(64 * kResWaves) kg_forward(NetDev d, ResLds S,
   __shared__ R sh[16];
   const int V = d.lat.V, F = d.frags_fwd;
   float* xs = reinterpret_cast<float*>(smem + S.xs);
+  float* xm = reinterpret_cast<float*>(smem + S.xm);
   if constexpr (LF) copy_frags(frags, smem + S.frags[0], F);
   build_tables<DIM>(d, S, smem, false);
   const size_t BV = (size_t)B * V;
@@ -170,6 +167,7 @@ __global__ void __launch_bounds__(64 * kResWaves) kg_forward(NetDev d, ResLds S,
     for (int n = threadIdx.x; n < V; n += blockDim.x) {
       const float v = z[(size_t)b * V + n];
       xs[n] = v;
+      xm[n] = masked(v, (parity_of<DIM>(site_of<DIM>(d.lat, n)) ^ d.parity0) - 1);
       if (saved) saved[(size_t)b * V + n] = v;
       zz += (R)v * v;
     }
@@ -185,10 +183,13 @@ __global__ void __launch_bounds__(64 * kResWaves) kg_forward(NetDev d, ResLds S,
       } else {
         fr = frags + (size_t)l * F * 64;
       }
-      hidden_convs<DIM, MODE, LF>(d, S, smem, fr, xs, fpar, [](int, int, int, const f32x4&) {});
-      last_conv<DIM, MODE, LF>(d, S, smem, fr, fpar ^ 1, [&](int, int n, float o0, float o1) {
+      hidden_convs<MODE>(d, S, smem, fr, [](int, int, int, const f32x4&) {});
+      last_conv<DIM, MODE>(d, S, smem, fr, fpar ^ 1, [&](int a, int n, float o0, float o1) {
         const float s = d.final_tanh ? tanhf(o0) : o0;
-        xs[n] = xs[n] * expf(s) + o1;
+        const float xn = xs[n] * expf(s) + o1;
+        xs[n] = xn;
+        xm[n] = xn;  // frozen in the next layer, and its partner active
+        xm[half_site<DIM>(d.lat, a, fpar)] = 0.f;
         ld += (R)s;
       });
       if constexpr (LF) wait_copies();
@@ -231,6 +232,7 @@ __global__ void __launch_bounds__(64 * kResWaves) kg_backward(NetDev d, ResLds S
   const int V = lat.V, lane = threadIdx.x & 63, j = lane >> 4, m = lane & 15;
   const int F = d.frags_fwd, FT = d.frags_all - F;
   float* xs = reinterpret_cast<float*>(smem + S.xs);
+  float* xm = reinterpret_cast<float*>(smem + S.xm);
   float* gy = reinterpret_cast<float*>(smem + S.gy);
   float* go = reinterpret_cast<float*>(smem + S.go);
   const uint16_t* nbr = reinterpret_cast<const uint16_t*>(smem + S.nbr);
@@ -252,8 +254,12 @@ __global__ void __launch_bounds__(64 * kResWaves) kg_backward(NetDev d, ResLds S
       auto put = [&](int plane, int n, const f32x4& v) {
         *reinterpret_cast<f32x4*>(st + ((size_t)plane * V + n) * 4) = v;
       };
-      if (own) xs[threadIdx.x] = xpre;
-      for (int n = threadIdx.x + blockDim.x; n < V; n += blockDim.x) xs[n] = xb[(size_t)l * BV + n];
+      auto put_x = [&](int n, float v) {
+        xs[n] = v;
+        xm[n] = masked(v, (parity_of<DIM>(site_of<DIM>(lat, n)) ^ fpar) - 1);
+      };
+      if (own) put_x(threadIdx.x, xpre);
+      for (int n = threadIdx.x + blockDim.x; n < V; n += blockDim.x) put_x(n, xb[(size_t)l * BV + n]);
       if constexpr (LF) wait_copies();
       lds_barrier();
       const u32x4 *ff, *ft;
@@ -265,9 +271,8 @@ __global__ void __launch_bounds__(64 * kResWaves) kg_backward(NetDev d, ResLds S
         ff = frags + (size_t)l * d.frags_all * 64;
         ft = ff + F * 64;
       }
-      hidden_convs<DIM, MODE, LF>(d, S, smem, ff, xs, fpar,
-                                  [&](int i, int pl, int n, const f32x4& v) { put(d.hplane[i] + pl, n, v); });
-      last_conv<DIM, MODE, LF>(d, S, smem, ff, apar, [&](int a, int n, float o0, float) {
+      hidden_convs<MODE>(d, S, smem, ff, [&](int i, int pl, int n, const f32x4& v) { put(d.hplane[i] + pl, n, v); });
+      last_conv<DIM, MODE>(d, S, smem, ff, apar, [&](int a, int n, float o0, float) {
         const int nf = half_site<DIM>(lat, a, fpar);
         float go0, gx;
         const float g = gy[n];
@@ -291,7 +296,7 @@ __global__ void __launch_bounds__(64 * kResWaves) kg_backward(NetDev d, ResLds S
         const float* in = i + 1 == d.n_conv ? go : reinterpret_cast<const float*>(smem + S.slot[i]);
         float* h = reinterpret_cast<float*>(smem + S.slot[i - 1]);
         const int rows = c.rows;
-        conv_pass<MODE, true, false, LF>((V + 15) >> 4, c, ft + (c.off - F) * 64, red, [&](int tile) {
+        conv_pass<MODE, true>((V + 15) >> 4, c, ft + (c.off - F) * 64, red, [&](int tile) {
           return lds_planes<true>(d, nbr, S.ps, in, min(tile * 16 + m, V - 1));
         }, [&](int tile, int ct, const f32x4& acc) {
           const int n = tile * 16 + m, pl = ct * 4 + j;
@@ -312,7 +317,7 @@ __global__ void __launch_bounds__(64 * kResWaves) kg_backward(NetDev d, ResLds S
         const int half = V / 2;
         const float* in = reinterpret_cast<const float*>(smem + S.slot[0]);
         const ConvDir& c = d.t[0];
-        conv_pass<MODE, true, false, LF>((half + 15) >> 4, c, ft + (c.off - F) * 64, red, [&](int tile) {
+        conv_pass<MODE, true>((half + 15) >> 4, c, ft + (c.off - F) * 64, red, [&](int tile) {
           return lds_planes<true>(d, nbr, S.ps, in, half_site<DIM>(lat, min(tile * 16 + m, half - 1), fpar));
         }, [&](int tile, int, const f32x4& acc) {
           const int a = tile * 16 + m;
@@ -348,7 +353,7 @@ __global__ void __launch_bounds__(256) kg_end(int half, const R* __restrict__ ld
 enum class Op { First, Hidden, Couple, Affine, Grad, GradField };
 
 struct StagedArgs {
-  int i, B, fpar, lds_frags;
+  int i, B, fpar;
   int ct0, ct1;      // row tiles of this launch; frags are theirs
   const float* in;   // planes of the input (sample stride in_ss floats), or the layer's field (i = 0 forward)
   size_t in_ss;
@@ -366,57 +371,56 @@ struct StagedArgs {
   const double* gld_vec;
 };
 
-// One convolution of one layer over the whole batch: a wave takes (sample, 16-site tile,
-// row tile) units in turn; its weights are staged in LDS where they fit.
+// One convolution of one layer over the whole batch: a workgroup takes 64 sites and a row
+// tile, 16 sites a wave, of one sample after the other; the sites' neighbours and, where they
+// fit (LF), the weights are laid out in its LDS once.
 //   First      h = leaky(conv) of the masked field       all sites
 //   Hidden     h = leaky(conv)                          all sites
 //   Couple     the last convolution and the affine update   active sites
 //   Affine     the last convolution and its affine backward  active sites
 //   Grad       g_h = conv^T(g) leaky'(h)                all sites
 //   GradField  g_x += conv^T(g)                         frozen sites
-template <int DIM, int MODE, Op OP>
+template <int DIM, int MODE, Op OP, bool LF>
 __global__ void __launch_bounds__(256) kg_staged(NetDev d, StagedArgs A, const u32x4* frags) {
   using R = std::conditional_t<MODE == kBf16, double, float>;
   constexpr bool TR = OP == Op::Grad || OP == Op::GradField;
   constexpr bool HALF = OP == Op::Couple || OP == Op::Affine || OP == Op::GradField;
   extern __shared__ __align__(16) unsigned char smem[];
   const Lat& lat = d.lat;
-  const ConvDir& c = TR ? d.t[A.i] : d.f[A.i];
+  const ConvDir c = TR ? d.t[A.i] : d.f[A.i];
   const int V = lat.V, half = V / 2, lane = threadIdx.x & 63, j = lane >> 4, m = lane & 15;
-  int* tab = reinterpret_cast<int*>(smem);
-  build_tab<DIM>(d, TR ? -1 : 1, tab);
-  const int nct = A.ct1 - A.ct0;
-  Weights W{frags, c.per_ct(), lane};
-  if (A.lds_frags) {
-    u32x4* sf = reinterpret_cast<u32x4*>(smem + ((d.T + 1) * 4 + 15) / 16 * 16);
-    for (int k = threadIdx.x; k < nct * W.per_ct * 64; k += blockDim.x) sf[k] = frags[k];
-    W.frags = sf;
-  }
-  __syncthreads();
   const int sites = HALF ? half : V, par = OP == Op::GradField ? A.fpar : A.fpar ^ 1;
-  const int tiles = (sites + 15) >> 4, per = tiles * nct;
-  const int64_t units = (int64_t)A.B * per;
-  for (int64_t u = (int64_t)blockIdx.x * 4 + fused::wave_id(); u < units; u += (int64_t)gridDim.x * 4) {
-    const int b = (int)(u / per), r = (int)(u - (int64_t)b * per), tile = nct == 1 ? r : r / nct, ct = r - tile * nct;
-    const int a = tile * 16 + m, ac = min(a, sites - 1);
-    const bool valid = a < sites;
-    const int n = HALF ? half_site<DIM>(lat, ac, par) : ac;
-    const Site<DIM> s = site_of<DIM>(lat, n);
-    const f32x4 bias = __builtin_bit_cast(f32x4, W.at(ct, -1));
+  const int groups = (sites + kTileSites - 1) / kTileSites, group = blockIdx.x % groups;
+  auto site = [&](int k) {
+    const int a = min(group * kTileSites + k, sites - 1);
+    return HALF ? half_site<DIM>(lat, a, par) : a;
+  };
+  uint32_t* nbr = reinterpret_cast<uint32_t*>(smem);
+  const int ct = blockIdx.y, k16 = fused::wave_id() * 16 + m, a = group * kTileSites + k16, n = site(k16);
+  const bool valid = a < sites;
+  Weights W{frags + (size_t)ct * c.per_ct() * 64, c.per_ct(), lane};
+  if constexpr (LF) {
+    copy_frags(W.frags, smem + tile_table_bytes(d.T), W.per_ct);
+    W.frags = reinterpret_cast<const u32x4*>(smem + tile_table_bytes(d.T));
+  }
+  build_tile<DIM>(d, TR ? -1 : 1, OP == Op::First ? A.fpar : -1, nbr, site);
+  if constexpr (LF) wait_copies();
+  __syncthreads();
+  for (int b = blockIdx.x / groups; b < A.B; b += gridDim.x / groups) {
+    const f32x4 bias = __builtin_bit_cast(f32x4, W.at(0, -1));
     f32x4 acc;
-    if constexpr (OP == Op::First) {
-      const FarField<DIM> rd{&lat, tab, A.in + (size_t)b * V, d.T, parity_of<DIM>(s) ^ A.fpar, s};
-      if constexpr (MODE == kTree)
-        acc = tree<true, false>(rd, c, W, ct, j, 0) + bias;
-      else
-        acc = chain<MODE, false, true, 1, true>(rd, c, W, ct, j, 0, c.nb, bias);
-    } else {
-      const FarPlanes<DIM> rd{&lat, tab, A.in + (size_t)b * A.in_ss, 4 * V, d.T, s};
-      if constexpr (MODE == kTree && !TR)
-        acc = tree<false, false>(rd, c, W, ct, j, 0) + bias;
-      else
-        acc = chain<MODE, TR, false, 4, true>(rd, c, W, ct, j, 0, c.nb, bias);
-    }
+    auto conv = [&](const auto& rd) {
+      if constexpr (MODE == kTree) {
+        acc = tree<false>(rd, c, W, 0, j, 0);
+        if constexpr (!TR) acc += bias;
+      } else {
+        acc = chain<MODE, TR>(rd, c, W, 0, j, 0, c.nb, bias);
+      }
+    };
+    if constexpr (OP == Op::First)
+      conv(Field<false>{nbr + k16, A.in + (size_t)b * V, kTileSites, d.T});
+    else
+      conv(Planes<false, false>{nbr + k16, A.in + (size_t)b * A.in_ss, kTileSites, 4 * V, d.T});
     const int pl = (A.ct0 + ct) * 4 + j;
     if constexpr (OP == Op::First || OP == Op::Hidden || OP == Op::Grad) {
       if (valid && 4 * pl < c.rows) {
@@ -504,8 +508,6 @@ template <int DIM, int MODE, Op OP>
 int32_t staged(const NetDev& d, StagedArgs a, int layer, const FragSrc& src, hipStream_t st) {
   constexpr bool TR = OP == Op::Grad || OP == Op::GradField;
   const ConvDir& c = TR ? d.t[a.i] : d.f[a.i];
-  constexpr auto k = kg_staged<DIM, MODE, OP>;
-  if (!set_lds_limit<k>(80 * 1024)) return LFS_EDEVICE;
   const size_t one = (size_t)c.per_ct() * 1024;  // a row tile's fragments
   const int step = src.count ? c.nct : (int)std::min<size_t>(c.nct, src.room / one);
   if (step < 1) return LFS_EWORKSPACE;
@@ -518,14 +520,21 @@ int32_t staged(const NetDev& d, StagedArgs a, int layer, const FragSrc& src, hip
       frags += ((size_t)layer * src.count + c.off) * 64;
     else
       prep<MODE>(d, src.params + (size_t)layer * d.P_layer, 1, c.off + ct * c.per_ct(), nct * c.per_ct(), src.buf, st);
-    const int tab = ((d.T + 1) * 4 + 15) / 16 * 16;
-    a.lds_frags = tab + nct * one <= 72 * 1024;  // two workgroups per CU
-    const int lds = tab + (a.lds_frags ? (int)(nct * one) : 0);
+    const int tab = tile_table_bytes(d.T);
+    const bool lf = tab + one <= 78 * 1024;  // two workgroups per CU
+    const int lds = tab + (lf ? (int)one : 0);
     const bool half = OP == Op::Couple || OP == Op::Affine || OP == Op::GradField;
-    const int64_t units = (int64_t)a.B * cdiv(half ? d.lat.V / 2 : d.lat.V, 16) * nct;
-    const int per_cu = std::max(1, std::min(8, 156 * 1024 / std::max(lds, 1)));
-    const unsigned grid = (unsigned)std::min<int64_t>((units + 3) / 4, (int64_t)num_cus() * per_cu);
-    hipLaunchKernelGGL(k, dim3(grid), dim3(256), lds, st, d, a, frags);
+    // as many workgroups as the chip holds at once, each with an equal number of samples
+    const int groups = cdiv(half ? d.lat.V / 2 : d.lat.V, kTileSites);
+    const int64_t fit = (int64_t)num_cus() * std::min(6, 158 * 1024 / lds) / ((int64_t)groups * nct);
+    const int per = cdiv(a.B, (int)std::max<int64_t>(1, std::min<int64_t>(fit, a.B)));
+    const dim3 grid((unsigned)(groups * cdiv(a.B, per)), (unsigned)nct);
+    LFS_TRY(with_lf(lf, [&](auto l) {
+      constexpr auto k = kg_staged<DIM, MODE, OP, decltype(l)::value>;
+      if (!set_lds_limit<k>(kLdsMax)) return (int32_t)LFS_EDEVICE;
+      hipLaunchKernelGGL(k, grid, dim3(256), lds, st, d, a, frags);
+      return (int32_t)LFS_OK;
+    }));
   }
   return LFS_OK;
 }

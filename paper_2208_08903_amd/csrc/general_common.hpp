@@ -37,7 +37,7 @@ __global__ void __launch_bounds__(256) kg_prep(NetDev d, const float* __restrict
 }
 
 // Waves of a resident workgroup (small lattices split the K blocks of a unit over them).
-constexpr int kResWaves = 16;
+constexpr int kResWaves = 8;
 
 // Copies n fragments to LDS without passing through registers: 1 KB per instruction, lane
 // i's 16 bytes at the fragment's LDS address + 16 i.  Counts as vector-memory loads.
@@ -50,34 +50,35 @@ __device__ __forceinline__ void copy_frags(const u32x4* src, unsigned char* dst,
 }
 __device__ __forceinline__ void wait_copies() { __builtin_amdgcn_s_waitcnt(0x0F70); }  // vmcnt(0)
 
-// One convolution over (16-site tile, row tile) units: a wave per unit, or, where the
-// workgroup has several times more waves, four waves per unit (transposed and Bf16: also
-// two), each on its share of the K blocks (Tree: of the eight sums; Seq keeps its order and
-// is not split), joined through red.  reader(tile) gives the operand reader of the lane's
+// One convolution over (16-site tile, row tile) units: a wave per unit, or, where that leaves
+// SIMDs idle, four waves per unit (Bf16: also two, and two waves per SIMD), each on its share
+// of the K blocks (Tree: of the eight sums; Seq keeps its order and is not split), joined
+// through red.  A Tree unit per SIMD is faster whole: split, the four waves of a SIMD took
+// as long over its MFMAs and four times the LDS reads (two floats of each 32 bytes).  reader(tile) gives the operand reader of the lane's
 // site, epi(tile, ct, acc) takes a unit's result.  Ends before any barrier that publishes
 // epi's stores.
-template <int MODE, bool TR, bool FIRST, bool LF, class Reader, class Epi>
+template <int MODE, bool TR, class Reader, class Epi>
 __device__ __forceinline__ void conv_pass(int tiles, const ConvDir& cd, const u32x4* frags, f32x4* red,
                                           Reader&& reader, Epi&& epi) {
   const int w = fused::wave_id(), nw = blockDim.x >> 6, lane = threadIdx.x & 63, j = lane >> 4;
   const int nct = cd.nct, units = tiles * nct;
   const ConvDir c = cd;
   const Weights W{frags, c.per_ct(), lane};
-  constexpr bool TREE = MODE == kTree && !TR;
+  constexpr bool TREE = MODE == kTree;
   int ks = 1;
   if constexpr (TREE)
-    ks = 4 * units <= nw ? 4 : 1;
-  else if constexpr (MODE != kSeq || TR)
-    while (ks < 4 && 2 * ks * units <= nw && 2 * ks <= c.nb) ks *= 2;
+    ks = units < 4 && 4 * units <= nw ? 4 : 1;
+  else if constexpr (MODE == kBf16)
+    while (ks < 4 && 2 * ks * units <= 8 && 2 * ks <= c.nb) ks *= 2;
   auto bias = [&](int ct) { return __builtin_bit_cast(f32x4, W.at(ct, -1)); };
   if (ks == 1) {
     for (int u = w; u < units; u += nw) {
       const int tile = fdiv(u, c.dnct), ct = u - tile * nct;
       const auto rd = reader(tile);
       if constexpr (TREE)
-        epi(tile, ct, tree<FIRST, false>(rd, c, W, ct, j, 0) + bias(ct));
+        epi(tile, ct, TR ? tree<false>(rd, c, W, ct, j, 0) : tree<false>(rd, c, W, ct, j, 0) + bias(ct));
       else
-        epi(tile, ct, chain<MODE, TR, FIRST, 2, !LF>(rd, c, W, ct, j, 0, c.nb, bias(ct)));
+        epi(tile, ct, chain<MODE, TR>(rd, c, W, ct, j, 0, c.nb, bias(ct)));
     }
     return;
   }
@@ -87,10 +88,10 @@ __device__ __forceinline__ void conv_pass(int tiles, const ConvDir& cd, const u3
   if (kp < ks) {
     const auto rd = reader(tile);
     if constexpr (TREE) {
-      acc = tree<FIRST, true>(rd, c, W, ct, j, kp);
+      acc = tree<true>(rd, c, W, ct, j, kp);
     } else {
       if (kp == 0) acc = bias(ct);
-      acc = chain<MODE, TR, FIRST, 2, !LF>(rd, c, W, ct, j, c.nb * kp / ks, c.nb * (kp + 1) / ks, acc);
+      acc = chain<MODE, TR>(rd, c, W, ct, j, c.nb * kp / ks, c.nb * (kp + 1) / ks, acc);
     }
     if (kp > 0) red[((kp - 1) * units + u) * 64 + lane] = acc;
   }
@@ -98,7 +99,8 @@ __device__ __forceinline__ void conv_pass(int tiles, const ConvDir& cd, const u3
   if (kp == 0) {
     if constexpr (TREE) {
       const f32x4 p1 = red[u * 64 + lane], p2 = red[(units + u) * 64 + lane], p3 = red[(2 * units + u) * 64 + lane];
-      acc = ((acc + p2) + (p1 + p3)) + bias(ct);
+      acc = (acc + p2) + (p1 + p3);
+      if constexpr (!TR) acc += bias(ct);
     } else {
       for (int p = 0; p + 1 < ks; ++p) acc += red[(p * units + u) * 64 + lane];
     }
@@ -108,9 +110,14 @@ __device__ __forceinline__ void conv_pass(int tiles, const ConvDir& cd, const u3
 
 // The reader of input planes at `in` (stride ps floats) for site n, neighbour table nbr.
 template <bool REV>
-__device__ __forceinline__ LdsPlanes<REV> lds_planes(const NetDev& d, const uint16_t* nbr, int ps, const float* in,
+__device__ __forceinline__ Planes<REV, true> lds_planes(const NetDev& d, const uint16_t* nbr, int ps, const float* in,
                                                      int n) {
-  return LdsPlanes<REV>{nbr + n, in, d.lat.V, ps, d.T};
+  return Planes<REV, true>{nbr + d.lat.V + n, in, d.lat.V, ps, d.T};
+}
+
+// The reader of the masked field xm for site n.
+__device__ __forceinline__ Field<true> lds_field(const NetDev& d, const uint16_t* nbr, const float* xm, int n) {
+  return Field<true>{nbr + d.lat.V + n, xm, d.lat.V, d.T};
 }
 
 // Plane stride in LDS, floats: the site after the last one is kept at zero, and 16 mod 64

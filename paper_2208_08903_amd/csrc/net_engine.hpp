@@ -6,21 +6,23 @@
 // 4n .. 4n + 3 (channels past the width are stored as zeros), so sixteen lanes reading
 // one quad of sixteen sites touch consecutive bytes.
 //
-// Order of a forward convolution's sum.  v_mfma_f32_16x16x4_f32 adds its four products
-// to the accumulator one after the other, each by a fused multiply-add (k = 0 first), so
-// the order of a sum is what the fragments make it:
-//   Seq   (FP32, the default network) bias, then taps, channels fastest, one at a time
+// Order of a convolution's sum, in both directions.  v_mfma_f32_16x16x4_f32 adds its four
+// products to the accumulator one after the other, each by a fused multiply-add (k = 0
+// first), so the order of a sum is what the fragments make it:
+//   Seq   (FP32, the default network) bias, then taps, channels fastest, one at a time (the
+//         last one's transpose: tap by tap, its two products added to each other first)
 //   Tree  (FP32, any other) eight sums over the (tap, channel) pairs q = 0, 1, .. with
 //         q mod 8 = 0 .. 7, added as ((0+4) + (2+6)) + ((1+5) + (3+7)), then the bias
 //   Bf16  v_mfma_f32_16x16x32_bf16 on operands rounded as they are gathered
 // The first two are the orders that direct convolutions (one thread, or eight lanes, per
 // output) have, so the fields, and with them the signs the backward's LeakyReLU sees, are
-// those of such kernels bit for bit.  Data gradients have no order to keep: FP32 takes four
-// sums, one per MFMA of a block.
+// those of such kernels bit for bit, and the data gradients too: an optimizer step that
+// follows gradients a bit away moves the parameters, and in the next step an activation next
+// to zero may change its sign.
 //
-// A K block is what a lane group's operand loads bring: 16 k in Seq and in the transposed
-// convolutions, 32 in Tree and Bf16.  Seq needs channels j, 4 + j, 8 + j, .. of one tap in
-// lane group j, so with it planes hold channels in that order (chan_of).
+// A K block is what a lane group's operand loads bring: 16 k in Seq, 32 in Tree and Bf16.
+// Seq needs channels j, 4 + j, 8 + j, .. of one tap in lane group j, so with it planes hold
+// channels in that order (chan_of).
 #pragma once
 
 #include "fused_common.hpp"
@@ -83,6 +85,7 @@ struct ConvDir {
   Magic dnct;
   int ck, nq;      // channels of K and quads per tap
   Magic dnq, dck;
+  int dq, rq;      // quads a lane advances per block (8, or 4), as taps and planes
   int nb, fpb;     // K blocks, fragments (1 KB) per block
   int off;         // first fragment of the layer's fragments; per row tile nb fpb + 1 of
                    // them, the first holding the bias (zeros when transposed)
@@ -132,10 +135,13 @@ inline NetDev make_net(const FlowGeom& g) {
       const bool first = dir == 0 && i == 0;
       c.nq = first ? 1 : cdiv(c.ck, 4);
       c.dnq = magic(c.nq);
-      c.fpb = dir == 0 && d.mode == kTree ? 2 : 1;
+      c.fpb = d.mode == kTree ? 2 : 1;
       // Tree runs over the (tap, channel) pairs themselves, the others over quads
       const int quads = first ? cdiv(g.T, 4) : g.T * c.nq;
-      c.nb = dir == 0 && d.mode == kTree ? cdiv(g.T * c.ck, 32) : cdiv(quads, d.mode == kBf16 ? 8 : 4);
+      c.nb = d.mode == kTree ? cdiv(g.T * c.ck, 32) : cdiv(quads, d.mode == kBf16 ? 8 : 4);
+      const int inc = d.mode == kSeq ? 4 : 8;
+      c.dq = inc / c.nq;
+      c.rq = inc % c.nq;
       c.off = off;
       off += c.nct * c.per_ct();
     }
@@ -167,20 +173,24 @@ __device__ __forceinline__ float w_at(const NetDev& d, const float* pl, int i, b
   const ConvDir& c = tr ? d.t[i] : d.f[i];
   if (row >= c.rows) return 0.f;
   int tap, ch;
-  if (!tr && MODE == kTree) {
+  if (MODE == kTree) {
     const int q = 8 * (4 * (f >> 1) + j) + 4 * (f & 1) + r;
     tap = q / c.ck;
     ch = q - tap * c.ck;
   } else if (!tr && i == 0) {
     tap = MODE == kSeq ? 16 * f + 4 * r + j : 4 * (4 * f + j) + r;  // (Bf16: f counts quads of four groups)
     ch = 0;
-  } else if (!tr && MODE == kSeq && c.ck == 8) {
+  } else if (tr && MODE == kSeq && i + 1 == d.n_conv) {  // Seq: output 1, then output 0 of tap 4 f + r
+    if (j > 1) return 0.f;
+    tap = 4 * f + r;
+    ch = 1 - j;
+  } else if (MODE == kSeq && c.ck == 8) {
     tap = 2 * f + (r >> 1);
     ch = 4 * (r & 1) + j;
   } else {
     const int q = 4 * f + j;
     tap = q / c.nq;
-    ch = chan_of(MODE == kSeq && (tr ? i + 1 < d.n_conv : true), c.ck, q - tap * c.nq, r);
+    ch = chan_of(MODE == kSeq, c.ck, q - tap * c.nq, r);
   }
   if (tap >= d.T || ch >= c.ck) return 0.f;
   const int rc = row_chan(d, i, tr, row);
@@ -279,11 +289,8 @@ __device__ __forceinline__ int wrap_c(int c, int L) {
   return (int)min(v, v - (uint32_t)L);
 }
 
-// Tap table entry: offsets + 8 in 4-bit fields (axis 0 lowest; reduced modulo L, so that
-// one wrap each way is enough for kernels wider than the lattice), the parity of |delta|_1
-// in bit 12, bit 31 set past the last tap (whose operand is the site's own value, replaced
-// by zero).
-constexpr int kTabPad = (int)0x80000000;
+// A tap's offsets + 8 in 4-bit fields (axis 0 lowest; reduced modulo L, so that one wrap each
+// way is enough for kernels wider than the lattice) and the parity of |delta|_1 in bit 12.
 
 template <int DIM>
 __device__ __forceinline__ int tap_entry(const NetDev& d, int tap, int sign) {
@@ -301,11 +308,6 @@ __device__ __forceinline__ int tap_entry(const NetDev& d, int tap, int sign) {
 }
 
 template <int DIM>
-__device__ __forceinline__ int site_entry() {
-  return DIM == 2 ? 0x88 : 0x888;  // no offset
-}
-
-template <int DIM>
 __device__ __forceinline__ int nbr_site(const Lat& a, const Site<DIM>& s, int e) {
   int r = wrap_c(s.c[0] + (e & 15) - 8, a.L);
   r = r * a.L + wrap_c(s.c[1] + ((e >> 4) & 15) - 8, a.L);
@@ -313,22 +315,17 @@ __device__ __forceinline__ int nbr_site(const Lat& a, const Site<DIM>& s, int e)
   return r;
 }
 
-// Tap table of the lattice into LDS: entry t for the site n + sign delta_t, then padding.
-template <int DIM>
-__device__ __forceinline__ void build_tab(const NetDev& d, int sign, int* tab) {
-  for (int t = threadIdx.x; t <= d.T; t += blockDim.x)
-    tab[t] = t < d.T ? tap_entry<DIM>(d, t, sign) : site_entry<DIM>() | kTabPad;
-}
-
-// Neighbour table in LDS, for samples that live there: site n + delta_t at [t][n], and a
-// row T of entries V, the zero site that follows every plane and the field.  The
-// transposed convolution's neighbour n - delta_t is row T - 1 - t.
+// Neighbour table in LDS, for samples that live there: site n + delta_t in row t, and one
+// row of V before and after: V is the zero site that follows the field and every plane,
+// which the quads past a convolution's last one read, also in reverse order (the transposed
+// convolution's neighbour n - delta_t is in row T - 1 - t).
+inline int64_t nbr_bytes(int T, int V) { return 2ll * (T + 2) * V; }
 template <int DIM>
 __device__ __forceinline__ void build_nbr(const NetDev& d, uint16_t* nb) {
   const Lat& lat = d.lat;
-  for (int k = threadIdx.x; k < (d.T + 1) * lat.V; k += blockDim.x) {
-    const int t = fdiv(k, lat.dV), n = k - t * lat.V;
-    nb[k] = (uint16_t)(t < d.T ? nbr_site<DIM>(lat, site_of<DIM>(lat, n), tap_entry<DIM>(d, t, 1)) : lat.V);
+  for (int k = threadIdx.x; k < (d.T + 2) * lat.V; k += blockDim.x) {
+    const int r = fdiv(k, lat.dV), n = k - r * lat.V, t = r - 1;
+    nb[k] = (uint16_t)(t >= 0 && t < d.T ? nbr_site<DIM>(lat, site_of<DIM>(lat, n), tap_entry<DIM>(d, t, 1)) : lat.V);
   }
 }
 
@@ -336,248 +333,403 @@ __device__ __forceinline__ void build_nbr(const NetDev& d, uint16_t* nb) {
 // value).
 __device__ __forceinline__ float masked(float v, int mask) { return __uint_as_float(__float_as_uint(v) & (uint32_t)mask); }
 
-// ---- operand readers ---------------------------------------------------------------
-// A reader gives the operands of the lane's site: val(t, pl, e) element e of plane pl at tap
-// t (the field: pl = e = 0), quad(t, pl) and pair(t, pl, h) whole and half planes.  Taps at
-// or past T read zeros.
+// For samples beyond the LDS, the neighbours n + sign delta_t of kTileSites sites: site k's in
+// column k, tap t's in row t, then a row for the quads past the end.  Entries that read zero
+// have the top bit set: that row's and, for a field (frozen parity fpar; -1: a plane), the
+// active sites'.  site(k) is the k-th site.
+constexpr int kTileSites = 64;
+constexpr uint32_t kZero = 0x80000000u;
+__host__ __device__ inline int tile_table_bytes(int T) { return 4 * (T + 1) * kTileSites; }
+template <int DIM, class S>
+__device__ __forceinline__ void build_tile(const NetDev& d, int sign, int fpar, uint32_t* nb, S&& site) {
+  const int k = threadIdx.x % kTileSites, n = site(k);
+  const Site<DIM> s = site_of<DIM>(d.lat, n);
+  const int flip = parity_of<DIM>(s) ^ fpar;
+  for (int t = fused::wave_id(); t <= d.T; t += blockDim.x / kTileSites) {  // a wave per tap
+    uint32_t v = (uint32_t)n | kZero;
+    if (t < d.T) {
+      const int e = tap_entry<DIM>(d, t, sign);
+      v = (uint32_t)nbr_site<DIM>(d.lat, s, e);
+      if (fpar >= 0 && ((flip ^ (e >> 12)) & 1)) v |= kZero;
+    }
+    nb[t * kTileSites + k] = v;
+  }
+}
 
-// Beyond the LDS: neighbours by arithmetic (tab: build_tab), planes ps floats apart.
-template <int DIM>
-struct FarPlanes {
-  const Lat* lat;
-  const int* tab;
-  const float* base;
-  int ps, T;
-  Site<DIM> s;
-  __device__ __forceinline__ float val(int t, int pl, int e) const {
-    const int x = tab[min(t, T)];
-    return masked(base[pl * ps + 4 * nbr_site<DIM>(*lat, s, x) + e], ~(x >> 31));
+// ---- convolutions ------------------------------------------------------------------
+// Operands are gathered through a table of neighbours in LDS: of a whole sample that lives
+// there (LDS: 16-bit entries, one table for all taps and both directions, zeros kept behind
+// the field and the planes), or of a tile of a larger one (32-bit entries, a table per
+// launch).  A lane's quads are a fixed number of taps and planes apart from block to block,
+// so its place is stepped instead of formed by a division per quad (with a division and 12
+// instructions of wrapping per quad, width 16: a hidden convolution of an 8 x 8 sample took
+// 6500 clocks against the 1280 of its MFMAs, one of 50 samples of 12^3 41 us; now 3500 and
+// 25 us).
+
+// An operand's place: plane (from its element on) and table entry.  What it reads beyond the
+// LDS goes through kept() before it is used, and not before: masked where it is loaded, every
+// block waited for the loads of the blocks ahead.
+template <bool LDS>
+struct At {
+  const float* plane;
+  uint32_t site;
+  __device__ __forceinline__ const float* get() const {
+    if constexpr (LDS) return plane + 4 * site;
+    return plane + 4 * (size_t)(site & ~kZero);
   }
-  __device__ __forceinline__ f32x4 quad(int t, int pl) const {
-    const int x = tab[min(t, T)];
-    f32x4 v = *reinterpret_cast<const f32x4*>(base + pl * ps + 4 * nbr_site<DIM>(*lat, s, x));
-#pragma unroll
-    for (int r = 0; r < 4; ++r) v[r] = masked(v[r], ~(x >> 31));
-    return v;
-  }
-  __device__ __forceinline__ f32x2 pair(int t, int pl, int h) const {
-    const int x = tab[min(t, T)];
-    f32x2 v = *reinterpret_cast<const f32x2*>(base + pl * ps + 4 * nbr_site<DIM>(*lat, s, x) + 2 * h);
-#pragma unroll
-    for (int r = 0; r < 2; ++r) v[r] = masked(v[r], ~(x >> 31));
-    return v;
-  }
+  __device__ __forceinline__ f32x4 quad() const { return *reinterpret_cast<const f32x4*>(get()); }
+  __device__ __forceinline__ f32x2 pair() const { return *reinterpret_cast<const f32x2*>(get()); }
 };
+template <bool LDS>
+__device__ __forceinline__ float kept(float v, uint32_t site) {
+  return LDS ? v : masked(v, ~((int)site >> 31));
+}
+template <bool LDS>
+__device__ __forceinline__ f32x4 kept(f32x4 v, uint32_t site) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) v[r] = kept<LDS>(v[r], site);
+  return v;
+}
 
-template <int DIM>
-struct FarField {
-  const Lat* lat;
-  const int* tab;
-  const float* x;
-  int T, flip;  // flip: the site's parity ^ the frozen parity
-  Site<DIM> s;
-  __device__ __forceinline__ float val(int t, int, int) const {
-    const int e = tab[min(t, T)];
-    return masked(x[nbr_site<DIM>(*lat, s, e)], ~(e >> 31) & (((flip ^ (e >> 12)) & 1) - 1));
-  }
-};
-
-// In LDS: neighbours from the table (nb: the site's column; row T: the zero site that
-// follows every plane and the field).  REV: n - delta_t.
-template <bool REV>
-struct LdsPlanes {
-  const uint16_t* nb;
+// The reader of planes `base` (stride ps floats) for the lane's site; nb: the site's column
+// of the table at tap 0, rows V entries long.  REV (LDS only): n - delta_t.
+template <bool REV, bool LDS>
+struct Planes {
+  using Entry = std::conditional_t<LDS, uint16_t, uint32_t>;
+  using Place = At<LDS>;
+  static constexpr bool rev = REV, lds = LDS;
+  const Entry* nb;
   const float* base;
   int V, ps, T;
-  __device__ __forceinline__ const float* at(int t, int pl) const {
-    const int row = REV ? (t < T ? T - 1 - t : T) : min(t, T);
-    return base + pl * ps + 4 * nb[row * V];
-  }
-  __device__ __forceinline__ float val(int t, int pl, int e) const { return at(t, pl)[e]; }
-  __device__ __forceinline__ f32x4 quad(int t, int pl) const { return *reinterpret_cast<const f32x4*>(at(t, pl)); }
-  __device__ __forceinline__ f32x2 pair(int t, int pl, int h) const {
-    return *reinterpret_cast<const f32x2*>(at(t, pl) + 2 * h);
-  }
 };
 
-struct LdsField {
-  const uint16_t* nb;
-  const float* x;
-  int V, T, flip;
-  const int* odd;  // per tap, the parity of |delta|_1 (0 past the last)
-  __device__ __forceinline__ float val(int t, int, int) const {
-    const int r = min(t, T), m = nb[r * V];
-    return x[(odd[r] ^ flip) ? V : m];  // an active site reads the zero that follows the field
-  }
-};
-
-// The four channels (FIRST: taps) of quad q of a convolution's K.
-template <bool FIRST, class R>
-__device__ __forceinline__ f32x4 quad_of(const R& rd, const ConvDir& c, int q) {
-  if constexpr (FIRST) {
-    return f32x4{rd.val(4 * q, 0, 0), rd.val(4 * q + 1, 0, 0), rd.val(4 * q + 2, 0, 0), rd.val(4 * q + 3, 0, 0)};
-  } else {
+template <bool REV, bool LDS>
+struct Walk {
+  using Entry = typename Planes<REV, LDS>::Entry;
+  const Entry* row;
+  const Entry* end;  // the row that reads zero
+  const float* plane;
+  int pl, nq, up, over, rq, ps;  // up: table step of dq taps; over: of one tap
+  __device__ __forceinline__ Walk(const Planes<REV, LDS>& r, const ConvDir& c, int q) {
     const int t = fdiv(q, c.dnq);
-    return rd.quad(t, q - t * c.nq);
+    pl = q - __mul24(t, c.nq);
+    row = r.nb + __mul24(REV ? r.T - 1 - t : t, r.V);
+    end = r.nb + (REV ? -1 : r.T) * r.V;
+    plane = r.base + pl * r.ps;
+    over = REV ? -r.V : r.V;
+    up = c.dq * over;
+    nq = c.nq;
+    rq = c.rq;
+    ps = r.ps;
   }
+  __device__ __forceinline__ At<LDS> next() {
+    const At<LDS> at{plane, *((REV ? row < end : row > end) ? end : row)};
+    row += up;
+    if (rq != 0) {  // uniform
+      pl += rq;
+      const bool carry = pl >= nq;
+      pl -= carry ? nq : 0;
+      plane += (carry ? rq - nq : rq) * ps;
+      row += carry ? over : 0;
+    }
+    return at;
+  }
+};
+
+// The reader of the masked field (zero at the active sites and past the end).
+template <bool LDS>
+struct Field {
+  static constexpr bool lds = LDS;
+  using Entry = typename Planes<false, LDS>::Entry;
+  const Entry* nb;
+  const float* x;
+  int V, T;
+  __device__ __forceinline__ uint32_t find(int t) const { return nb[__mul24(min(t, T), V)]; }
+  __device__ __forceinline__ float get(uint32_t e) const { return x[LDS ? e : e & ~kZero]; }
+};
+template <class R>
+struct IsField : std::false_type {};
+template <bool LDS>
+struct IsField<Field<LDS>> : std::true_type {};
+
+// The place of (tap, channel) pair q of planes whose width is no multiple of four.
+template <bool REV, bool LDS>
+__device__ __forceinline__ At<LDS> pair_at(const Planes<REV, LDS>& r, const ConvDir& c, int q) {
+  const int t = fdiv(q, c.dck), ch = q - __mul24(t, c.ck), row = REV ? max(r.T - 1 - t, -1) : min(t, r.T);
+  return {r.base + (ch >> 2) * r.ps + (ch & 3), r.nb[row * r.V]};
 }
 
-// The lane's operand of block b: lane group j of a transposed convolution (FP32) or of a
-// Seq one.
-template <int MODE, bool TR, bool FIRST, class R>
-__device__ __forceinline__ u32x4 operand(const R& rd, const ConvDir& c, int j, int b) {
-  if constexpr (MODE == kBf16) {
-    const f32x4 u = quad_of<FIRST>(rd, c, 8 * b + 2 * j), v = quad_of<FIRST>(rd, c, 8 * b + 2 * j + 1);
-    return u32x4{pack_bf16(u[0], u[1]), pack_bf16(u[2], u[3]), pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
-  } else if constexpr (!TR && FIRST) {  // Seq: taps 16 b + 4 r + j
-    return __builtin_bit_cast(u32x4, f32x4{rd.val(16 * b + j, 0, 0), rd.val(16 * b + 4 + j, 0, 0),
-                                           rd.val(16 * b + 8 + j, 0, 0), rd.val(16 * b + 12 + j, 0, 0)});
+// K blocks [b0, b1): find(b) looks places up, fetch(b, what find gave) reads operands, mul
+// multiplies them.  In LDS (AHEAD = 0) the three are one block apart, so neither of the two
+// latencies stands between a block's MFMAs and the next one's; beyond it AHEAD blocks are
+// found and fetched together, before the AHEAD ones before them are multiplied: a block's
+// MFMAs take 128 clocks, its gather from the L2 several times that (width 16, 50 samples of
+// 12^3: 31 us with the loads of one block in flight, 25 us with four).  Past the end the last block is found and fetched again (a walk meets the zero
+// row) and not multiplied.
+template <int AHEAD, class Find, class Fetch, class Mul>
+__device__ __forceinline__ void walk_blocks(int b0, int b1, Find&& find, Fetch&& fetch, Mul&& mul) {
+  const int last = b1 - 1;
+  if constexpr (AHEAD == 0) {
+    auto f = find(b0);
+    auto v = fetch(b0, f);
+    f = find(min(b0 + 1, last));
+    for (int b = b0; b < b1; ++b) {
+      const auto vn = fetch(min(b + 1, last), f);
+      f = find(min(b + 2, last));
+      mul(v);
+      v = vn;
+    }
   } else {
-    if constexpr (!TR)
-      if (c.ck == 8) {  // Seq: channels j and 4 + j of taps 2 b and 2 b + 1
-        const f32x2 u = rd.pair(2 * b, j >> 1, j & 1), v = rd.pair(2 * b + 1, j >> 1, j & 1);
-        return __builtin_bit_cast(u32x4, f32x4{u[0], u[1], v[0], v[1]});
+    decltype(find(0)) f[AHEAD];
+    decltype(fetch(0, f[0])) v[AHEAD], vn[AHEAD];
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) f[u] = find(min(b0 + u, last));
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) v[u] = fetch(min(b0 + u, last), f[u]);
+    for (int b = b0; b < b1; b += AHEAD) {
+      if (b + AHEAD < b1) {
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) f[u] = find(min(b + AHEAD + u, last));
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) vn[u] = fetch(min(b + AHEAD + u, last), f[u]);
       }
-    return __builtin_bit_cast(u32x4, quad_of<false>(rd, c, 4 * b + j));
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u)
+        if (u == 0 || b + u < b1) mul(v[u]);
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u) v[u] = vn[u];
+    }
   }
 }
 
-// ---- accumulation chains -----------------------------------------------------------
+// A lane's index the compiler knows nothing of: what is derived from it in a branch stays
+// there, instead of being set up for every branch ahead of the loop over units.
+__device__ __forceinline__ int opaque(int j) {
+  asm volatile("" : "+v"(j));
+  return j;
+}
 
-// Sum over K blocks [b0, b1) on top of init: transposed, Seq and Bf16 convolutions.  U
-// blocks' operands are in flight; PIPE: the next U are fetched while the current ones are
-// multiplied (operands from beyond the LDS).  kmax: channels of a one-quad convolution
-// (MFMA r of a block takes channel r of every lane group's quad; past them all is zero).
-template <int MODE, bool TR, bool FIRST, int U, bool PIPE, class R>
-__device__ __forceinline__ f32x4 chain(const R& rd, const ConvDir& c, const Weights& W, int ct, int j, int b0, int b1,
+// init + the sum over K blocks [b0, b1): Seq and Bf16 convolutions.
+template <int MODE, bool TR, class R>
+__device__ __forceinline__ f32x4 chain(const R& rd, const ConvDir& c, const Weights& W, int ct, int j0, int b0, int b1,
                                        const f32x4& init) {
-  constexpr bool FOUR = MODE != kBf16 && TR;  // four sums
-  f32x4 s[FOUR ? 4 : 1];
-  s[0] = init;
-  if constexpr (FOUR) s[1] = s[2] = s[3] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int kmax = TR && c.nq == 1 ? c.ck : 4, last = b1 - 1;
-  auto mul = [&](const u32x4& a, const u32x4& b) {
-    if constexpr (MODE == kBf16) {
-      s[0] = fused::mfma(fused::as_bf16x8(a), fused::as_bf16x8(b), s[0]);
-    } else {
+  constexpr bool L = R::lds;
+  constexpr int AHEAD = L ? 0 : 4;
+  f32x4 s = init;
+  auto mul = [&](const u32x4& a, const f32x4& b) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        if (r < 2 || r < kmax)
-          s[FOUR ? r : 0] = fused::mfma(__uint_as_float(a[r]), __uint_as_float(b[r]), s[FOUR ? r : 0]);
-    }
+    for (int r = 0; r < 4; ++r) s = fused::mfma(__uint_as_float(a[r]), b[r], s);
   };
-  u32x4 a[U], b[U];
-  if constexpr (!PIPE) {
-    for (int k = b0; k < b1; k += U) {
+  auto mul16 = [&](const u32x4& a, const f32x4& u, const f32x4& v) {
+    const u32x4 b{pack_bf16(u[0], u[1]), pack_bf16(u[2], u[3]), pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+    s = fused::mfma(fused::as_bf16x8(a), fused::as_bf16x8(b), s);
+  };
+  const int j = opaque(j0);
+  if constexpr (IsField<R>::value) {
+    constexpr int NS = MODE == kBf16 ? 8 : 4;
+    struct Sites {
+      uint32_t n[NS];
+    };
+    struct Op {
+      u32x4 a;
+      float v[NS];
+      Sites f;
+    };
+    walk_blocks<AHEAD>(b0, b1, [&](int b) {
+      Sites f;
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int q = min(k + u, last);
-        a[u] = W.at(ct, q);
-        b[u] = operand<MODE, TR, FIRST>(rd, c, j, q);
-      }
+      for (int r = 0; r < NS; ++r) f.n[r] = rd.find(MODE == kSeq ? 16 * b + 4 * r + j : 32 * b + 8 * j + r);
+      return f;
+    }, [&](int b, const Sites& f) {
+      Op o{W.at(ct, b), {}, f};
 #pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (k + u < b1) mul(a[u], b[u]);
-    }
+      for (int r = 0; r < NS; ++r) o.v[r] = rd.get(f.n[r]);
+      return o;
+    }, [&](const Op& o) {
+      f32x4 v[NS / 4];
+#pragma unroll
+      for (int r = 0; r < NS; ++r) v[r / 4][r % 4] = kept<L>(o.v[r], o.f.n[r]);
+      if constexpr (MODE == kBf16) mul16(o.a, v[0], v[1]);
+      else mul(o.a, v[0]);
+    });
   } else {
+    using P = typename R::Place;
+    if constexpr (MODE == kBf16) {
+      struct Two {
+        P u, v;
+      };
+      struct Op {
+        u32x4 a;
+        f32x4 u, v;
+        uint32_t nu, nv;
+      };
+      Walk w0(rd, c, 8 * b0 + 2 * j), w1(rd, c, 8 * b0 + 2 * j + 1);
+      walk_blocks<AHEAD>(b0, b1, [&](int) { return Two{w0.next(), w1.next()}; }, [&](int b, const Two& f) {
+        return Op{W.at(ct, b), f.u.quad(), f.v.quad(), f.u.site, f.v.site};
+      }, [&](const Op& o) { mul16(o.a, kept<L>(o.u, o.nu), kept<L>(o.v, o.nv)); });
+    } else if (TR && c.ck == 2) {
+      // The last convolution's transpose, a tap's two products rounded together before they
+      // are added: W_1 g_1, then W_0 g_0 + that by lane groups 0 and 1 of one MFMA per tap.
+      struct Four {
+        P at[4];
+      };
+      struct Op {
+        u32x4 a;
+        float v[4];
+        uint32_t n[4];
+      };
+      const int e = 1 - (j & 1);
+      walk_blocks<AHEAD>(b0, b1, [&](int b) {
+        Four f;
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int q = min(b0 + u, last);
-      a[u] = W.at(ct, q);
-      b[u] = operand<MODE, TR, FIRST>(rd, c, j, q);
-    }
-    for (int k = b0; k < b1; k += U) {
-      u32x4 an[U], bn[U];
+        for (int r = 0; r < 4; ++r) f.at[r] = pair_at(rd, c, 2 * (4 * b + r) + e);
+        return f;
+      }, [&](int b, const Four& f) {
+        Op o{W.at(ct, b), {}, {}};
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int q = min(k + U + u, last);
-        an[u] = W.at(ct, q);
-        bn[u] = operand<MODE, TR, FIRST>(rd, c, j, q);
-      }
+        for (int r = 0; r < 4; ++r) {
+          o.v[r] = *f.at[r].get();
+          o.n[r] = f.at[r].site;
+        }
+        return o;
+      }, [&](const Op& o) {
+        f32x4 p[4];
 #pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (k + u < b1) mul(a[u], b[u]);
+        for (int r = 0; r < 4; ++r)
+          p[r] = fused::mfma(__uint_as_float(o.a[r]), masked(kept<L>(o.v[r], o.n[r]), (j - 2) >> 31),
+                             f32x4{0.f, 0.f, 0.f, 0.f});
 #pragma unroll
-      for (int u = 0; u < U; ++u) a[u] = an[u], b[u] = bn[u];
+        for (int r = 0; r < 4; ++r) s += p[r];
+      });
+    } else if (c.ck == 8) {
+      // channels j and 4 + j of taps 2 b and 2 b + 1
+      struct Two {
+        P u, v;
+      };
+      struct Op {
+        u32x4 a;
+        f32x2 u, v;
+        uint32_t nv;
+      };
+      using E = typename R::Entry;
+      const float* p = rd.base + (j >> 1) * rd.ps + 2 * (j & 1);
+      const int step = R::rev ? -rd.V : rd.V;
+      const E* first = rd.nb + (R::rev ? rd.T - 1 : 0) * rd.V;
+      walk_blocks<AHEAD>(b0, b1, [&](int b) {
+        const E* row = first + 2 * b * step;
+        return Two{{p, row[0]}, {p, row[step]}};
+      }, [&](int b, const Two& f) { return Op{W.at(ct, b), f.u.pair(), f.v.pair(), f.v.site}; },
+      [&](const Op& o) {  // (tap 2 b is never past the last)
+        mul(o.a, f32x4{o.u[0], o.u[1], kept<L>(o.v[0], o.nv), kept<L>(o.v[1], o.nv)});
+      });
+    } else {
+      struct Op {
+        u32x4 a;
+        f32x4 v;
+        uint32_t n;
+      };
+      Walk w(rd, c, 4 * b0 + j);
+      walk_blocks<AHEAD>(b0, b1, [&](int) { return w.next(); }, [&](int b, const P& f) {
+        return Op{W.at(ct, b), f.quad(), f.site};
+      }, [&](const Op& o) { mul(o.a, kept<L>(o.v, o.n)); });
     }
   }
-  if constexpr (FOUR) return (s[0] + s[1]) + (s[2] + s[3]);
-  return s[0];
+  return s;
 }
 
-// The eight elements of lane group j of Tree block b: (tap, channel) pairs 8 (4 b + j) ..
-// + 7, as two quads (h = 0, 1), or element e of quad h.
-template <bool FIRST, class R>
-__device__ __forceinline__ f32x4 tree_quad(const R& rd, const ConvDir& c, int j, int b, int h) {
-  const int Q = 2 * (4 * b + j) + h;
-  if constexpr (FIRST) {
-    return quad_of<true>(rd, c, Q);
-  } else if ((c.ck & 3) == 0) {
-    return quad_of<false>(rd, c, Q);
-  } else {  // quads that straddle taps
-    f32x4 v;
+// Tree convolution without its bias.  SPLIT (in LDS): the sums part and part + 4 only, two
+// scalars of a block's eight per lane.
+template <bool SPLIT, class R>
+__device__ __forceinline__ f32x4 tree(const R& rd, const ConvDir& c, const Weights& W, int ct, int j0, int part) {
+  constexpr bool L = R::lds;
+  constexpr int NS = SPLIT ? 2 : 8, AHEAD = L ? 0 : 2;
+  f32x4 s[NS];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int t = fdiv(4 * Q + r, c.dck), ch = 4 * Q + r - t * c.ck;
-      v[r] = rd.val(t, ch >> 2, ch & 3);
+  for (int e = 0; e < NS; ++e) s[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+  struct A {
+    float a[NS];
+  };
+  auto weights = [&](int b) {
+    A o;
+    if constexpr (SPLIT) {
+      o.a[0] = W.elem(ct, 2 * b, part);
+      o.a[1] = W.elem(ct, 2 * b + 1, part);
+    } else {
+      const u32x4 a0 = W.at(ct, 2 * b), a1 = W.at(ct, 2 * b + 1);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) o.a[e] = __uint_as_float(e < 4 ? a0[e & 3] : a1[e & 3]);
     }
-    return v;
-  }
-}
-template <bool FIRST, class R>
-__device__ __forceinline__ float tree_elem(const R& rd, const ConvDir& c, int j, int b, int h, int e) {
-  const int q = 8 * (4 * b + j) + 4 * h + e;
-  if constexpr (FIRST) {
-    return rd.val(q, 0, 0);
+    return o;
+  };
+  struct Sites {
+    uint32_t n[NS];
+  };
+  struct Op {
+    A w;
+    float v[NS];
+    Sites f;
+  };
+  auto mul = [&](const Op& o) {
+#pragma unroll
+    for (int e = 0; e < NS; ++e) s[e] = fused::mfma(o.w.a[e], kept<L>(o.v[e], o.f.n[e]), s[e]);
+  };
+  const int j = opaque(j0);
+  auto pair = [&](int b, int e) { return 32 * b + 8 * j + (SPLIT ? part + 4 * e : e); };
+  if constexpr (IsField<R>::value) {
+    walk_blocks<AHEAD>(0, c.nb, [&](int b) {
+      Sites f;
+#pragma unroll
+      for (int e = 0; e < NS; ++e) f.n[e] = rd.find(pair(b, e));
+      return f;
+    }, [&](int b, const Sites& f) {
+      Op o{weights(b), {}, f};
+#pragma unroll
+      for (int e = 0; e < NS; ++e) o.v[e] = rd.get(f.n[e]);
+      return o;
+    }, mul);
   } else {
-    const int t = fdiv(q, c.dck), ch = q - t * c.ck;
-    return rd.val(t, ch >> 2, ch & 3);
-  }
-}
-
-// Tree convolution without its bias; SPLIT: only the sums part and part + 4 (the other
-// parts are other waves', see tree_join).
-template <bool FIRST, bool SPLIT, class R>
-__device__ __forceinline__ f32x4 tree(const R& rd, const ConvDir& c, const Weights& W, int ct, int j, int part) {
-  const f32x4 zero{0.f, 0.f, 0.f, 0.f};
-  if constexpr (SPLIT) {
-    f32x4 s0 = zero, s1 = zero;
-    for (int b0 = 0; b0 < c.nb; b0 += 2) {
-      float a[2][2], v[2][2];
+    using P = typename R::Place;
+    if ((c.ck & 3) != 0) {
+      struct Ats {
+        P at[NS];
+      };
+      walk_blocks<AHEAD>(0, c.nb, [&](int b) {
+        Ats f;
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int b = min(b0 + u, c.nb - 1);
+        for (int e = 0; e < NS; ++e) f.at[e] = pair_at(rd, c, pair(b, e));
+        return f;
+      }, [&](int b, const Ats& f) {
+        Op o{weights(b), {}, {}};
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          a[u][h] = W.elem(ct, 2 * b + h, part);
-          v[u][h] = tree_elem<FIRST>(rd, c, j, b, h, part);
+        for (int e = 0; e < NS; ++e) {
+          o.v[e] = *f.at[e].get();
+          o.f.n[e] = f.at[e].site;
         }
-      }
+        return o;
+      }, mul);
+    } else {
+      struct Two {
+        P u, v;
+      };
+      Walk w0(rd, c, 2 * j), w1(rd, c, 2 * j + 1);
+      walk_blocks<AHEAD>(0, c.nb, [&](int) { return Two{w0.next(), w1.next()}; }, [&](int b, const Two& f) {
+        Op o{weights(b), {}, {}};
+        if constexpr (SPLIT) {
+          o.v[0] = f.u.get()[part];
+          o.v[1] = f.v.get()[part];
+        } else {
+          const f32x4 u0 = f.u.quad(), u1 = f.v.quad();
 #pragma unroll
-      for (int u = 0; u < 2; ++u)
-        if (b0 + u < c.nb) {
-          s0 = fused::mfma(a[u][0], v[u][0], s0);
-          s1 = fused::mfma(a[u][1], v[u][1], s1);
+          for (int e = 0; e < 8; ++e) o.v[e] = e < 4 ? u0[e & 3] : u1[e & 3];
         }
+#pragma unroll
+        for (int e = 0; e < NS; ++e) o.f.n[e] = 2 * e < NS ? f.u.site : f.v.site;
+        return o;
+      }, mul);
     }
-    return s0 + s1;
-  } else {
-    f32x4 s[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) s[e] = zero;
-    for (int b = 0; b < c.nb; ++b) {
-      u32x4 a[2];
-      f32x4 v[2];
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        a[h] = W.at(ct, 2 * b + h);
-        v[h] = tree_quad<FIRST>(rd, c, j, b, h);
-      }
-#pragma unroll
-      for (int e = 0; e < 8; ++e) s[e] = fused::mfma(__uint_as_float(a[e >> 2][e & 3]), v[e >> 2][e & 3], s[e]);
-    }
-    return ((s[0] + s[4]) + (s[2] + s[6])) + ((s[1] + s[5]) + (s[3] + s[7]));
   }
+  if constexpr (SPLIT) return s[0] + s[1];
+  else return ((s[0] + s[4]) + (s[2] + s[6])) + ((s[1] + s[5]) + (s[3] + s[7]));
 }
 
 }  // namespace net
