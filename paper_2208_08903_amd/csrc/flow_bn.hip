@@ -14,7 +14,7 @@
 //
 // Statistics are FP64: per sample the sum and the squared deviations from the sample's
 // own mean, merged by count (Chan, Golub and LeVeque's update) in a fixed order.
-#include "general_common.hpp"
+#include "general_wgrad.hpp"
 
 namespace lfs {
 namespace {
@@ -694,7 +694,7 @@ int32_t backward_impl(const FlowGeom& g, const float* params, int B, const float
       gy = gx;
       which ^= 1;
     }
-    run_wgrad<DIM, MODE>(d, B, l0, l1 - l0, PL, w.store, saved, w.partial, g_params, st);
+    LFS_TRY((run_wgrad<DIM, MODE>(d, B, l0, l1 - l0, PL, w.store, saved, w.partial, g_params, st)));
     l1 = l0;
   }
   if (g_z)

@@ -24,7 +24,7 @@
 // (forward 121, backward 246, weight gradients 55).  3D L = 12, hidden 16, 12 layers,
 // batch 50, FP32, where a sample does not fit: 47.1 -> 3.2 ms (a hidden convolution of
 // 86400 sites 25 us, its data gradient 24 us; direct sums: 294 and 257).
-#include "general_common.hpp"
+#include "general_wgrad.hpp"
 
 namespace lfs {
 namespace {
@@ -710,7 +710,7 @@ int32_t backward_impl(const FlowGeom& g, const float* params, int B, const float
         which ^= 1;
       }
     }
-    run_wgrad<DIM, MODE>(d, B, l0, l1 - l0, PL, w.store, saved, w.partial, g_params, st);
+    LFS_TRY((run_wgrad<DIM, MODE>(d, B, l0, l1 - l0, PL, w.store, saved, w.partial, g_params, st)));
     l1 = l0;
   }
   if (g_z)

@@ -307,6 +307,7 @@ __global__ void __launch_bounds__(256) kg_reduce(NetDev d, int n, int chunks, co
       if (r >= d.offg[i] && r < d.offg[i] + 2 * d.cout[i]) return;
   }
   double acc = 0.0;
+#pragma unroll 8
   for (int c = 0; c < chunks; ++c) acc += partial[(size_t)c * n + p];
   out[p] = (float)acc;
 }
@@ -385,33 +386,13 @@ void prep(const NetDev& d, const float* params, int layers, int f0, int count, u
     if (s_ != LFS_OK) return s_;              \
   } while (0)
 
-// Weight gradients of layers [l0, l0 + layers) from their store into g_params.
-template <int DIM, int MODE>
-void run_wgrad(const NetDev& d, int B, int l0, int layers, int planes, const float* store, const float* saved,
-               double* partial, float* g_params, hipStream_t st) {
-  WgPlan p = wgrad_plan(d, B, layers, planes);
-  p.a.l0 = l0;
-  hipLaunchKernelGGL((kg_wgrad<DIM, MODE == kBf16>), dim3((unsigned)(p.a.jobs * layers), (unsigned)p.a.chunks),
-                     dim3(256), 0, st, d, p.a, store, saved, partial);
-  const int n = layers * d.P_layer;
-  hipLaunchKernelGGL(kg_reduce, dim3(blocks(n)), dim3(256), 0, st, d, n, p.a.chunks, partial,
-                     g_params + (size_t)l0 * d.P_layer);
-}
-
 // Layers whose activations and gradients are kept at once for the weight gradients: as
-// many as fit 192 MB (they then stay in the last-level cache between the two launches).
+// many as fit 320 MB.  (50 samples of 12^3, 12 layers in one weight-gradient launch or in two
+// of 192 MB each, which the last-level cache holds: 591 us or 626.)
 int layer_group(const NetDev& d, int B, int planes) {
   const size_t per = (size_t)B * planes * d.lat.V * 16;
-  return (int)std::max<size_t>(1, std::min<size_t>(d.N, ((size_t)192 << 20) / per));
+  return (int)std::max<size_t>(1, std::min<size_t>(d.N, ((size_t)320 << 20) / per));
 }
-// Bytes of the partial sums of groups of `group` layers (the last one may be smaller and
-// take more chunks).
-size_t partial_bytes(const NetDev& d, int B, int group, int planes) {
-  size_t pb = wgrad_plan(d, B, group, planes).partial_bytes;
-  if (d.N % group) pb = std::max(pb, wgrad_plan(d, B, d.N % group, planes).partial_bytes);
-  return pb;
-}
-
 // The kernels read and write the workspace 16 bytes at a time; a caller's may start
 // anywhere, so its first bytes up to the next 16-byte boundary are left unused.
 constexpr size_t kWsAlign = 16;

@@ -90,3 +90,17 @@ def test_batch_norm_shapes(L, hs, B, mode):
                          bn_stats=None if mode == lfs.BN_BATCH else of.unpack_bn_stats(stats.astype(np.float64), fs))
     assert np.linalg.norm(gp - go) <= 1e-4 * np.linalg.norm(go)
     assert np.linalg.norm(gz - zo) <= 1e-4 * np.linalg.norm(zo)
+
+
+@pytest.mark.parametrize("case", [
+    (3, 12, 1, 3, (16, 16), 3),       # default network, slabs of a few slices
+    (3, 6, 1, 3, (32, 32), 2),        # default network, two row tiles and column blocks
+    (3, 4, 1, 7, (5, 18), 2),         # several groups of column tiles
+    (2, 6, 1, 5, (33, 6), 3),         # slabs whose sites are no multiple of four
+    (3, 50, 1, 3, (4,), 1),           # a slab of one slice exceeds the LDS
+])
+def test_weight_gradient_slabs(case):
+    print(f"weight gradients {case}", flush=True)
+    desc, params, z, fs = _case(*case, lfs.LFS_PLAIN_FP32)
+    out, _ = _check_forward(desc, params, z, fs, lfs.LFS_PLAIN_FP32)
+    _check_backward(desc, params, z, fs, out, lfs.LFS_PLAIN_FP32)
