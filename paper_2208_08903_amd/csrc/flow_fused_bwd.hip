@@ -86,6 +86,13 @@ __device__ __forceinline__ void store_cm4(uint16_t* hc, int n, int co0, const u3
   hc[(co0 + 3) * CSTR + n] = (uint16_t)(hv[1] >> 16);
 }
 
+// Weight-gradient output tiles of a wave.
+template <int DIM, int C, bool BF16>
+constexpr int bwd_tiles() {
+  constexpr int T = DIM == 2 ? 9 : 27, MT = (C + 15) / 16;
+  return MT * (!BF16 && DIM == 2 ? 2 : (2 * T + 15) / 16) + MT * T * MT + MT * ((T + 15) / 16);
+}
+
 template <int DIM, int L, int C, bool BF16>
 struct BwdCfg {
   using G = Geo<DIM, L>;
@@ -112,10 +119,14 @@ struct BwdCfg {
   static constexpr bool A1L = HSave<DIM, L, C, BF16>::ok;
   static constexpr size_t A1_BYTES =
       A1L ? (size_t)((C + 15) / 16) * (!BF16 && DIM == 2 ? 2 : kblocks_f32(k_tri(T))) * 64 * 16 : 0;
-  static constexpr size_t lds_main = cmaxz(M::MAIN + (BF16 ? 0 : 16 + (size_t)(T * C / 4) * 2 * 4 * 16) + A1_BYTES,
-                                           (size_t)P_LAYER * 4);
+  // the sums over the waves after the sample loop: weight-gradient tiles, biases, gradient
+  static constexpr size_t RED_BYTES =
+      (size_t)bwd_tiles<DIM, C, BF16>() * 1024 + (8 * ((C + 15) / 16) + 1) * 16 + (size_t)P_LAYER * 4;
+  static constexpr size_t lds_state = cmaxz(M::MAIN + (BF16 ? 0 : 16 + (size_t)(T * C / 4) * 2 * 4 * 16) + A1_BYTES,
+                                            (size_t)P_LAYER * 4);
+  static constexpr size_t lds_main = cmaxz(lds_state, RED_BYTES);
   // 3D shapes need more than the 256 registers a lane gets at 2 waves per SIMD.
-  static constexpr int NT = (lds_main > 80 * 1024 && DIM == 2) ? 512 : 256;
+  static constexpr int NT = (lds_state > 80 * 1024 && DIM == 2) ? 512 : 256;
   // waves per SIMD the register allocation has to allow (SPLIT: two workgroups)
   static constexpr int MINW = SPLIT ? 2 : 1;
   static constexpr int NW = NT / 64;
@@ -153,8 +164,11 @@ struct BwdCfg {
   static constexpr size_t OFF_FRAG = align16(OFF_A1 + A1_BYTES);
   static constexpr int per_cu(size_t bytes) { return bytes > 160 * 1024 ? 0 : cmin(8, (int)(160 * 1024 / bytes)); }
   static constexpr bool FRAG_LDS = OFF_FRAG + FRAG_BYTES + RED_STATIC <= 158 * 1024 &&
-                                   per_cu(OFF_FRAG + FRAG_BYTES + RED_STATIC) == per_cu(lds_main + RED_STATIC);
-  static constexpr size_t lds_bytes = FRAG_LDS ? cmaxz(OFF_FRAG + FRAG_BYTES, (size_t)P_LAYER * 4) : lds_main;
+                                   per_cu(OFF_FRAG + FRAG_BYTES + RED_STATIC) == per_cu(lds_state + RED_STATIC);
+  static constexpr size_t lds_bytes = FRAG_LDS ? cmaxz(OFF_FRAG + FRAG_BYTES, RED_BYTES) : lds_main;
+  // what the number of workgroups follows from: the registers hold fewer of the small
+  // shapes' than either, and the partials' sums keep their order
+  static constexpr size_t lds_grid = FRAG_LDS ? cmaxz(OFF_FRAG + FRAG_BYTES, (size_t)P_LAYER * 4) : lds_state;
   static constexpr int MT = (C + 15) / 16;
   static constexpr int NKC = BF16 ? V / 32 : V / 16;  // K chunks (sites) per sample
   // every wave's share of the K chunks, when it is the same for all waves (a
@@ -179,6 +193,8 @@ struct BwdCfg {
   static constexpr int I3 = MT * NTL3;
   static constexpr int I2 = MT * T * MT;
   static constexpr int I1 = MT * NTL1;
+  static constexpr int TILES = I3 + I2 + I1;
+  static_assert(TILES == bwd_tiles<DIM, C, BF16>(), "LDS of the sums over the waves");
 };
 
 // ---- weight-gradient operands ---------------------------------------------
@@ -1100,80 +1116,102 @@ __global__ void __launch_bounds__(NT, (BwdCfg<DIM, L, C, BF16>::MINW)) kf_backwa
   }
   if constexpr (Cfg::SPLIT) __syncthreads();  // the partial sums below overwrite the sample state
 
-  // ---- sum the waves' weight-gradient tiles in a fixed order, write the partial ----
-  float* red = reinterpret_cast<float*>(smem);
-  for (int i = threadIdx.x; i < Cfg::P_LAYER; i += NT) red[i] = 0.f;
+  // ---- sum the waves' weight-gradient tiles in wave order, write the partial ----
+  // Wave after wave adds its accumulators to the sums as they lie in its registers, 16
+  // bytes a lane, a group of tiles at a time: while one wave adds the second group the
+  // next one adds the first.  The sums are put in the gradient's order at the end, by all
+  // waves.  Added there element by element, wave after wave (each a read, an add and a
+  // write that may alias the next), they took 12800 of the 35700 clocks of a 2D L = 8,
+  // C = 8 launch with one sample per workgroup; now 6800.
+  f32x4* tiles = reinterpret_cast<f32x4*>(smem);  // acc3, acc2, acc1, then db2, db1 (4 j each), db3
+  f32x4* bias4 = tiles + Cfg::TILES * 64;
+  float* red = reinterpret_cast<float*>(bias4 + 8 * LF.nct + 1);
   // bias partials: reduce over the 16 lanes that share j (and, for db3, over all lanes)
 #pragma unroll
   for (int ct = 0; ct < LF.nct; ++ct)
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int o = 1; o < 16; o <<= 1) {
-        db2[ct][i] += __shfl_xor(db2[ct][i], o, 64);
-        db1[ct][i] += __shfl_xor(db1[ct][i], o, 64);
-      }
+    for (int i = 0; i < 4; ++i) {
+      db2[ct][i] = xor_add<8>(xor_add<4>(xor_add<2>(xor_add<1>(db2[ct][i]))));
+      db1[ct][i] = xor_add<8>(xor_add<4>(xor_add<2>(xor_add<1>(db1[ct][i]))));
+    }
   db3s = wave_sum(db3s);
   db3t = wave_sum(db3t);
-  __syncthreads();
-  for (int ww = 0; ww < NW; ++ww) {
-    if (w == ww) {
+  {
+    constexpr int GT = (Cfg::TILES + NW - 1) / NW;
+    auto add = [&](f32x4* at, const f32x4& v) {  // 0 + v for the first wave
+      f32x4 s{0.f, 0.f, 0.f, 0.f};
+      if (w > 0) s = *at;
+      return s + v;
+    };
+    auto acc = [&](auto I) -> f32x4& {
+      constexpr int t = decltype(I)::value;
+      if constexpr (t < Cfg::I3) return acc3[t];
+      else if constexpr (t < Cfg::I3 + Cfg::I2) return acc2[t - Cfg::I3];
+      else return acc1[t - Cfg::I3 - Cfg::I2];
+    };
+    static_for<0, 2 * NW - 1>([&](auto P) {
+      static_for<0, NW>([&](auto Gr) {
+        constexpr int g = decltype(Gr)::value, ww = decltype(P)::value - g, t0 = g * GT,
+                      t1 = cmin(Cfg::TILES, t0 + GT);
+        if constexpr (ww >= 0 && ww < NW && t0 < t1) {
+          if (w == ww) {
+            f32x4 v[t1 - t0];
+            static_for<t0, t1>([&](auto I) {
+              v[decltype(I)::value - t0] = add(tiles + decltype(I)::value * 64 + lane, acc(I));
+            });
+            static_for<t0, t1>([&](auto I) { tiles[decltype(I)::value * 64 + lane] = v[decltype(I)::value - t0]; });
+            if constexpr (g == 0) {
+              if (m == 0) {
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < NTL3; ++nt) {
-          const int col = nt * 16 + m, co = col & 1;
-          const int tap = Cfg::PS3 ? 2 * (m >> 1) + nt : col >> 1;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int ci = mt * 16 + 4 * j + i;
-            if (ci < C && tap < T) red[off_W3 + (co * C + ci) * T + tap] += acc3[mt * NTL3 + nt][i];
-          }
-        }
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int tap = 0; tap < T; ++tap)
-#pragma unroll
-          for (int nt = 0; nt < MT; ++nt) {
-            const int co = nt * 16 + m;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const int ci = mt * 16 + 4 * j + i;
-              if (ci < C && co < C)
-                red[off_W2 + (co * C + ci) * T + tap] += acc2[(mt * T + tap) * MT + nt][i];
+                for (int ct = 0; ct < LF.nct; ++ct) {
+                  bias4[8 * ct + j] = add(bias4 + 8 * ct + j, db2[ct]);
+                  bias4[8 * ct + 4 + j] = add(bias4 + 8 * ct + 4 + j, db1[ct]);
+                }
+              }
+              if (lane == 0) bias4[8 * LF.nct] = add(bias4 + 8 * LF.nct, f32x4{db3s, db3t, 0.f, 0.f});
             }
           }
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < NTL1; ++nt) {
-          const int tap = nt * 16 + m;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int c = mt * 16 + 4 * j + i;
-            if (c < C && tap < T) red[off_W1 + c * T + tap] += acc1[mt * NTL1 + nt][i];
-          }
         }
-      if (m == 0) {
-#pragma unroll
-        for (int ct = 0; ct < LF.nct; ++ct)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int c = ct * 16 + 4 * j + i;
-            if (c < C) {
-              red[off_b2 + c] += db2[ct][i];
-              red[off_b1 + c] += db1[ct][i];
-            }
-          }
-      }
-      if (lane == 0) {
-        red[off_b3] += db3s;
-        red[off_b3 + 1] += db3t;
-      }
-    }
-    __syncthreads();
+      });
+      lds_barrier();
+    });
   }
+  for (int t = w; t < Cfg::TILES; t += NW) {
+    const f32x4 v = tiles[t * 64 + lane];
+    const int t2 = t - Cfg::I3, t1 = t2 - Cfg::I2;
+    int mt, tap, off;  // the tile's rows; the column's tap and, of a row, its offset and stride
+    bool ok;
+    if (t2 < 0) {
+      mt = t / NTL3;
+      const int nt = t - mt * NTL3, col = nt * 16 + m;
+      tap = Cfg::PS3 ? 2 * (m >> 1) + nt : col >> 1;
+      off = off_W3 + (col & 1) * C * T + tap;
+      ok = tap < T;
+    } else if (t1 < 0) {
+      mt = t2 / (T * MT);
+      const int r = t2 - mt * T * MT;
+      tap = r / MT;
+      const int co = (r - tap * MT) * 16 + m;
+      off = off_W2 + co * C * T + tap;
+      ok = co < C;
+    } else {
+      mt = t1 / NTL1;
+      tap = (t1 - mt * NTL1) * 16 + m;
+      off = off_W1 + tap;
+      ok = tap < T;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int c = mt * 16 + 4 * j + i;
+      if (ok && c < C) red[off + c * T] = v[i];
+    }
+  }
+  for (int c = threadIdx.x; c < C; c += NT) {
+    red[off_b2 + c] = bias4[8 * (c >> 4) + ((c >> 2) & 3)][c & 3];
+    red[off_b1 + c] = bias4[8 * (c >> 4) + 4 + ((c >> 2) & 3)][c & 3];
+  }
+  if (threadIdx.x < 2) red[off_b3 + threadIdx.x] = bias4[8 * LF.nct][threadIdx.x];
+  __syncthreads();
   float* out = partial + (size_t)blockIdx.x * Cfg::P_LAYER;
   for (int i = threadIdx.x; i < Cfg::P_LAYER; i += NT) out[i] = red[i];
 }
@@ -1184,7 +1222,7 @@ __global__ void __launch_bounds__(NT, (BwdCfg<DIM, L, C, BF16>::MINW)) kf_backwa
 template <int DIM, int L, int C, bool BF16>
 int bwd_grid(int B) {
   using Cfg = BwdCfg<DIM, L, C, BF16>;
-  const int per_cu = std::max<int>(1, std::min<int>(8, (int)((160 * 1024) / Cfg::lds_bytes)));
+  const int per_cu = std::max<int>(1, std::min<int>(8, (int)((160 * 1024) / Cfg::lds_grid)));
   return std::min(B, num_cus() * per_cu);
 }
 

@@ -15,6 +15,22 @@ namespace {  // each translation unit keeps its own copy of the kernels
 // (loads unrolled, so several are in flight), then the 16 slice sums are
 // combined in index order.  The order depends on G and P only: deterministic.
 constexpr int kRedCols = 64, kRedSlices = 16;
+
+// Partials [g0, g1) of one parameter in index order, eight loads in flight also where there
+// are fewer (one after the other, the four of 64 workgroups' took 3500 clocks of a launch).
+__device__ __forceinline__ float slice_sum(const float* __restrict__ partial, int g0, int g1, int P, int i) {
+  constexpr int U = 8;
+  float acc = 0.f;
+  for (int g = g0; g < g1; g += U) {
+    float v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = partial[(size_t)min(g + u, g1 - 1) * P + i];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (g + u < g1) acc += v[u];
+  }
+  return acc;
+}
 __global__ void __launch_bounds__(kRedCols * kRedSlices) kf_reduce(int G, int P,
                                                                   const float* __restrict__ partial,
                                                                   float* __restrict__ out) {
@@ -24,8 +40,7 @@ __global__ void __launch_bounds__(kRedCols * kRedSlices) kf_reduce(int G, int P,
   float acc = 0.f;
   if (i < P) {
     const int g0 = (int)((long)G * sl / kRedSlices), g1 = (int)((long)G * (sl + 1) / kRedSlices);
-#pragma unroll 8
-    for (int g = g0; g < g1; ++g) acc += partial[(size_t)g * P + i];
+    acc = slice_sum(partial, g0, g1, P, i);
   }
   sh[sl][col] = acc;
   __syncthreads();
@@ -54,8 +69,7 @@ __device__ __forceinline__ void grid_reduce(const float* __restrict__ partial, f
     const int i = base + q;
     float acc = 0.f;
     if (i < P) {
-#pragma unroll 8
-      for (int g = g0; g < g1; ++g) acc += partial[(size_t)g * P + i];
+      acc = slice_sum(partial, g0, g1, P, i);
     }
     sh[sl][q] = acc;
     __syncthreads();
