@@ -51,6 +51,12 @@ __global__ void __launch_bounds__(NT) kf_forward(
   for (int q = threadIdx.x; q < C; q += NT) h1[LY::template off<C>(LY::ZS, q)] = 0, h2[LY::template off<C>(LY::ZS, q)] = 0;
   const int lane = threadIdx.x & 63, w = wave_id(), j = lane >> 4, m = lane & 15;
   const size_t BV = (size_t)B * V;
+  // Small FP32 lattices: a layer's fragments, conv3 table and biases are fetched while the
+  // previous layer's conv3 runs.  Fetched where they are used (as the other shapes do, whose
+  // longer passes hide it or whose registers are full), the passes of an 8 x 8 sample began
+  // with an L2 latency each: 36.9 us for 16 layers of C = 8, now 29.5.
+  constexpr bool NEXT = Cfg::PFA && Cfg::Q3 && !Cfg::C1V;
+  constexpr int NQ = NEXT ? (LF.k3 * 4 + NT - 1) / NT : 1;
 
   for (int b = blockIdx.x; b < B; b += gridDim.x) {
     R zz = 0;
@@ -64,6 +70,37 @@ __global__ void __launch_bounds__(NT) kf_forward(
       }
     }
     R ld = 0;
+    u32x4 A1[LF.nct][LF.k1], A2[LF.nct][LF.k2], qv[NQ];
+    f32x4 hb1[LF.nct], hb2[LF.nct];
+    auto load_a1 = [&](const u32x4* f) {
+#pragma unroll
+      for (int ct = 0; ct < LF.nct; ++ct)
+#pragma unroll
+        for (int c = 0; c < LF.k1; ++c) A1[ct][c] = f[(LF.off1 + ct * LF.k1 + c) * 64];
+    };
+    auto load_a2 = [&](const u32x4* f) {
+#pragma unroll
+      for (int ct = 0; ct < LF.nct; ++ct)
+#pragma unroll
+        for (int c = 0; c < LF.k2; ++c) A2[ct][c] = f[(LF.off2 + ct * LF.k2 + c) * 64];
+    };
+    auto load_next = [&](int l) {
+      const u32x4* f = frags + (size_t)l * LF.total * 64;
+      const float* p = params + (size_t)l * P_layer;
+      load_a1(f + lane);
+      load_a2(f + lane);
+#pragma unroll
+      for (int k = 0; k < NQ; ++k) {
+        const int i = min((int)threadIdx.x + k * NT, LF.k3 * 4 - 1);
+        qv[k] = f[(LF.off3 + (i >> 2)) * 64 + (i & 3)];
+      }
+#pragma unroll
+      for (int ct = 0; ct < LF.nct; ++ct) {
+        hb1[ct] = load_bias4<C>(p + off_b1, ct, j);
+        hb2[ct] = load_bias4<C>(p + off_b2, ct, j);
+      }
+    };
+    if constexpr (NEXT) load_next(0);
     for (int layer = 0; layer < N; ++layer) {
       const int fpar = (layer + parity0) & 1;
       const u32x4* fl = frags + (size_t)layer * LF.total * 64 + lane;
@@ -73,27 +110,22 @@ __global__ void __launch_bounds__(NT) kf_forward(
         // conv3's quad A entries (rows 0..3 of every chunk) into LDS: read by every
         // conv3 chunk of every wave, visible after the next barrier
         const u32x4* f3 = frags + ((size_t)layer * LF.total + LF.off3) * 64;
-        for (int i = threadIdx.x; i < LF.k3 * 4; i += NT) qt[i] = f3[(i >> 2) * 64 + (i & 3)];
+        if constexpr (NEXT) {
+#pragma unroll
+          for (int k = 0; k < NQ; ++k)
+            if (threadIdx.x + k * NT < LF.k3 * 4) qt[threadIdx.x + k * NT] = qv[k];
+        } else {
+          for (int i = threadIdx.x; i < LF.k3 * 4; i += NT) qt[i] = f3[(i >> 2) * 64 + (i & 3)];
+        }
       }
       // Weight fragments.  Where the registers allow (Cfg::PFA) each pass's are
       // fetched one pass ahead, so the L2 latency hides behind the previous
       // pass: conv1's and conv2's here, conv3's when conv2 starts; otherwise
       // each pass fetches its own.
+      // (NEXT: both are there already.)
       constexpr int NA3 = Cfg::X4 ? 4 : 1;
       constexpr int KA3 = Cfg::Q3 ? 1 : LF.k2;  // quad conv3 fetches its fragments per chunk
-      u32x4 A1[LF.nct][LF.k1], A2[LF.nct][LF.k2], A3[NA3][KA3];
-      auto load_a1 = [&]() {
-#pragma unroll
-        for (int ct = 0; ct < LF.nct; ++ct)
-#pragma unroll
-          for (int c = 0; c < LF.k1; ++c) A1[ct][c] = fl[(LF.off1 + ct * LF.k1 + c) * 64];
-      };
-      auto load_a2 = [&]() {
-#pragma unroll
-        for (int ct = 0; ct < LF.nct; ++ct)
-#pragma unroll
-          for (int c = 0; c < LF.k2; ++c) A2[ct][c] = fl[(LF.off2 + ct * LF.k2 + c) * 64];
-      };
+      u32x4 A3[NA3][KA3];
       auto load_a3 = [&]() {
         if constexpr (!Cfg::Q3) {
 #pragma unroll
@@ -104,9 +136,9 @@ __global__ void __launch_bounds__(NT) kf_forward(
           }
         }
       };
-      if constexpr (Cfg::PFA) {
-        if constexpr (!Cfg::C1V) load_a1();
-        load_a2();
+      if constexpr (Cfg::PFA && !NEXT) {
+        if constexpr (!Cfg::C1V) load_a1(fl);
+        load_a2(fl);
       }
       // conv1 operands: row triples of the masked field, built in the (dead) h2
       // buffer, or (Cfg::TRIX) gathered straight from the field by each tile
@@ -118,10 +150,10 @@ __global__ void __launch_bounds__(NT) kf_forward(
       if constexpr (Cfg::C1V) {
         conv1_valu<LY, C, NT>(xs, h1, w1t, fpar);
       } else {
-        if constexpr (!Cfg::PFA) load_a1();
+        if constexpr (!Cfg::PFA) load_a1(fl);
         f32x4 bias[LF.nct];
 #pragma unroll
-        for (int ct = 0; ct < LF.nct; ++ct) bias[ct] = load_bias4<C>(pl + off_b1, ct, j);
+        for (int ct = 0; ct < LF.nct; ++ct) bias[ct] = NEXT ? hb1[ct] : load_bias4<C>(pl + off_b1, ct, j);
         mma_tiles<Cfg::TU1, LF.nct, LF.k1, BF16, k_tri(Cfg::T), true>(
             V / 16, w, NW, A1, bias,
             [&](int tile, int c) {
@@ -147,10 +179,10 @@ __global__ void __launch_bounds__(NT) kf_forward(
         if constexpr (Cfg::PFA)
           load_a3();
         else
-          load_a2();
+          load_a2(fl);
         f32x4 bias[LF.nct];
 #pragma unroll
-        for (int ct = 0; ct < LF.nct; ++ct) bias[ct] = load_bias4<C>(pl + off_b2, ct, j);
+        for (int ct = 0; ct < LF.nct; ++ct) bias[ct] = NEXT ? hb2[ct] : load_bias4<C>(pl + off_b2, ct, j);
         mma_tiles<Cfg::TU2, LF.nct, LF.k2, BF16>(
             V / 16, w, NW, A2, bias,
             [&](int tile, int c) {
@@ -183,6 +215,7 @@ __global__ void __launch_bounds__(NT) kf_forward(
       }
       // conv3 at the active sites, affine update and log-det
       if constexpr (!Cfg::PFA) load_a3();
+      if constexpr (NEXT) load_next(layer + 1 < N ? layer + 1 : 0);
       if constexpr (Cfg::C1V)  // the next layer's (or next sample's first) conv1 weights
         stage_w1t<C, NT>(w1t, params + (size_t)(layer + 1 < N ? layer + 1 : 0) * P_layer, off_W1, off_b1);
       if constexpr (Cfg::Q3) {
