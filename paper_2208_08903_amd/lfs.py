@@ -126,7 +126,8 @@ def version() -> str:
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The current device's current stream (the raw handle: no Stream object is made)."""
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _p(t, dtype=None, name="tensor"):
@@ -138,7 +139,7 @@ def _p(t, dtype=None, name="tensor"):
         raise LfsError(f"{name} must be {dtype}, got {t.dtype}")
     if not t.is_contiguous():
         raise LfsError(f"{name} must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _need(t, n, name, exact=True):
