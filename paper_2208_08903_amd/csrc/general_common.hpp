@@ -151,6 +151,7 @@ __global__ void __launch_bounds__(256) kg_begin(int V, const float* z, float* x,
 
 // ---- weight gradients --------------------------------------------------------------
 
+// (BF16, and lattices of which a slab does not fit the LDS; else general_wgrad.hpp.)
 // dW[co][ci][t] = sum over (sample, site) of g[n][co] u[n + delta_t][ci] as GEMMs over the
 // sites on v_mfma_f64_16x16x4_f64: products of FP32 values are exact and every sum is
 // FP64.  Rows are 16 channels of the operand read in place, columns 16 (tap, channel)
