@@ -322,10 +322,15 @@ __device__ __forceinline__ int nbr_site(const Lat& a, const Site<DIM>& s, int e)
 inline int64_t nbr_bytes(int T, int V) { return 2ll * (T + 2) * V; }
 template <int DIM>
 __device__ __forceinline__ void build_nbr(const NetDev& d, uint16_t* nb) {
+  // a wave per row, a lane per site: the tap is the wave's, a site's coordinates are found once
+  // (entry by entry, with four divisions each, a batch-norm step of 144 launches took 940 us
+  // instead of 934)
   const Lat& lat = d.lat;
-  for (int k = threadIdx.x; k < (d.T + 2) * lat.V; k += blockDim.x) {
-    const int r = fdiv(k, lat.dV), n = k - r * lat.V, t = r - 1;
-    nb[k] = (uint16_t)(t >= 0 && t < d.T ? nbr_site<DIM>(lat, site_of<DIM>(lat, n), tap_entry<DIM>(d, t, 1)) : lat.V);
+  for (int n = threadIdx.x & 63; n < lat.V; n += 64) {
+    const Site<DIM> s = site_of<DIM>(lat, n);
+    for (int r = fused::wave_id(); r < d.T + 2; r += blockDim.x >> 6)
+      nb[r * lat.V + n] =
+          (uint16_t)(r > 0 && r <= d.T ? nbr_site<DIM>(lat, s, tap_entry<DIM>(d, r - 1, 1)) : lat.V);
   }
 }
 
