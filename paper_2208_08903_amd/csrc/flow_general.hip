@@ -29,10 +29,14 @@
 namespace lfs {
 namespace {
 
+// Tiles of 16 active sites, whose sums of s the log-det is made of.
+__host__ __device__ inline int ld_tiles(int V) { return (V / 2 + 15) / 16; }
+
 // LDS of a resident workgroup, byte offsets.
 struct ResLds {
   int ps;  // plane stride
   int xs, xm, gy, go, slot[LFS_MAX_HIDDEN], red, nbr;  // xm: the field at the frozen sites
+  int ts;                     // forward: the tiles' sums of s
   int frags[2];               // a layer's weight fragments (lf), see kg_forward and kg_backward
   bool lf;
   int total;
@@ -62,6 +66,7 @@ ResLds res_lds(const NetDev& d, bool bwd) {
   }
   r.red = take(1024ll * kResWaves);
   r.nbr = take(nbr_bytes(d.T, V));
+  if (!bwd) r.ts = take(8ll * ld_tiles(V));
   // fragments: two layers' in the forward, one layer's forward and transposed ones in the
   // backward
   const int64_t fr = off;
@@ -126,7 +131,8 @@ __device__ __forceinline__ void hidden_convs(const NetDev& d, const ResLds& S, u
   }
 }
 
-// The last convolution at the active sites: f(a, site, o_0, o_1) for the a-th of them.
+// The last convolution at the active sites, 16 to a tile: f(tile, a, o_0, o_1) by every lane,
+// for the a-th of them (-1: none) in one lane each.
 template <int DIM, int MODE, class F>
 __device__ __forceinline__ void last_conv(const NetDev& d, const ResLds& S, unsigned char* smem, const u32x4* frags,
                                           int apar, F&& f) {
@@ -140,8 +146,33 @@ __device__ __forceinline__ void last_conv(const NetDev& d, const ResLds& S, unsi
     return lds_planes<false>(d, nbr, S.ps, in, half_site<DIM>(lat, min(tile * 16 + m, half - 1), apar));
   }, [&](int tile, int, const f32x4& acc) {
     const int a = tile * 16 + m;
-    if (j == 0 && a < half) f(a, half_site<DIM>(lat, a, apar), acc[0], acc[1]);
+    f(tile, j == 0 && a < half ? a : -1, acc[0], acc[1]);
   });
+}
+
+// ---- log q ---------------------------------------------------------------------
+// s is summed in FP64: the 16 active sites of a tile, over the layers, then over the tiles in
+// the order of 256 threads.  Resident and staged kernels add in this order.  (FP32 sums over
+// all layers left the log-det of 12^3 sites and 12 layers off by 6e-5.)
+
+// The sum over the lane's row of 16 lanes, in every lane of the row.
+__device__ __forceinline__ double tile_sum(float s) {
+  return xor_add<8>(xor_add<4>(xor_add<2>(xor_add<1>((double)s))));
+}
+
+// v(0) + .. + v(n - 1) by one wave, in the order of block_sum over 256 threads that take every
+// 256th.
+template <class T, class F>
+__device__ __forceinline__ T sum_of_256(int n, F&& v) {
+  const int lane = threadIdx.x & 63;
+  T r = 0;
+  for (int w = 0; w < 4 && 64 * w < n; ++w) {
+    T acc = 0;
+    for (int t = 64 * w + lane; t < n; t += 256) acc += v(t);
+    acc = wave_sum(acc);
+    r = w == 0 ? acc : r + acc;
+  }
+  return r;
 }
 
 // ---- resident forward ----------------------------------------------------------
@@ -154,25 +185,28 @@ __global__ void __launch_bounds__(64 * kResWaves) kg_forward(NetDev d, ResLds S,
                                                              double* __restrict__ logdet) {
   using R = std::conditional_t<MODE == kBf16, double, float>;
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ R sh[16];
-  const int V = d.lat.V, F = d.frags_fwd;
+  const int V = d.lat.V, F = d.frags_fwd, lane = threadIdx.x & 63;
+  const bool sums = fused::wave_id() == (int)(blockDim.x >> 6) - 1;  // the wave that makes the sample's sums
   float* xs = reinterpret_cast<float*>(smem + S.xs);
   float* xm = reinterpret_cast<float*>(smem + S.xm);
+  double* ts = reinterpret_cast<double*>(smem + S.ts);
   if constexpr (LF) copy_frags(frags, smem + S.frags[0], F);
   build_tables<DIM>(d, S, smem, false);
   const size_t BV = (size_t)B * V;
   int cur = 0;
   for (int b = blockIdx.x; b < B; b += gridDim.x) {
-    R zz = 0, ld = 0;
     for (int n = threadIdx.x; n < V; n += blockDim.x) {
       const float v = z[(size_t)b * V + n];
       xs[n] = v;
       xm[n] = masked(v, (parity_of<DIM>(site_of<DIM>(d.lat, n)) ^ d.parity0) - 1);
       if (saved) saved[(size_t)b * V + n] = v;
-      zz += (R)v * v;
     }
+    if (sums)
+      for (int t = lane; t < ld_tiles(V); t += 64) ts[t] = 0.0;
     if constexpr (LF) wait_copies();
     lds_barrier();
+    double logr = 0.0;
+    if (sums) logr = log_prior(V, sum_of_256<R>(V, [&](int n) { return (R)xs[n] * xs[n]; }));
     for (int l = 0; l < d.N; ++l) {
       const int fpar = (l + d.parity0) & 1;
       const u32x4* fr;
@@ -184,13 +218,18 @@ __global__ void __launch_bounds__(64 * kResWaves) kg_forward(NetDev d, ResLds S,
         fr = frags + (size_t)l * F * 64;
       }
       hidden_convs<MODE>(d, S, smem, fr, [](int, int, int, const f32x4&) {});
-      last_conv<DIM, MODE>(d, S, smem, fr, fpar ^ 1, [&](int a, int n, float o0, float o1) {
-        const float s = d.final_tanh ? tanhf(o0) : o0;
-        const float xn = xs[n] * expf(s) + o1;
-        xs[n] = xn;
-        xm[n] = xn;  // frozen in the next layer, and its partner active
-        xm[half_site<DIM>(d.lat, a, fpar)] = 0.f;
-        ld += (R)s;
+      last_conv<DIM, MODE>(d, S, smem, fr, fpar ^ 1, [&](int tile, int a, float o0, float o1) {
+        float s = 0.f;
+        if (a >= 0) {
+          const int n = half_site<DIM>(d.lat, a, fpar ^ 1);
+          s = d.final_tanh ? tanhf(o0) : o0;
+          const float xn = xs[n] * expf(s) + o1;
+          xs[n] = xn;
+          xm[n] = xn;  // frozen in the next layer, and its partner active
+          xm[half_site<DIM>(d.lat, a, fpar)] = 0.f;
+        }
+        const double t = tile_sum(s);
+        if (lane == 0) ts[tile] += t;  // (a tile is the same wave's in every layer)
       });
       if constexpr (LF) wait_copies();
       lds_barrier();
@@ -200,12 +239,12 @@ __global__ void __launch_bounds__(64 * kResWaves) kg_forward(NetDev d, ResLds S,
       }
     }
     for (int n = threadIdx.x; n < V; n += blockDim.x) phi[(size_t)b * V + n] = xs[n];
-    ld = block_sum(ld, sh);
-    zz = block_sum(zz, sh);
-    if (threadIdx.x == 0) {
-      const double logr = -0.5 * (double)zz - (double)V * kHalfLog2Pi;
-      logq[b] = logr - (double)ld;
-      if (logdet) logdet[b] = (double)ld;
+    if (sums) {
+      const double ld = sum_of_256<double>(ld_tiles(V), [&](int t) { return ts[t]; });
+      if (lane == 0) {
+        logq[b] = logr - ld;
+        if (logdet) logdet[b] = ld;
+      }
     }
   }
 }
@@ -272,8 +311,9 @@ __global__ void __launch_bounds__(64 * kResWaves) kg_backward(NetDev d, ResLds S
         ft = ff + F * 64;
       }
       hidden_convs<MODE>(d, S, smem, ff, [&](int i, int pl, int n, const f32x4& v) { put(d.hplane[i] + pl, n, v); });
-      last_conv<DIM, MODE>(d, S, smem, ff, apar, [&](int a, int n, float o0, float) {
-        const int nf = half_site<DIM>(lat, a, fpar);
+      last_conv<DIM, MODE>(d, S, smem, ff, apar, [&](int, int a, float o0, float) {
+        if (a < 0) return;
+        const int n = half_site<DIM>(lat, a, apar), nf = half_site<DIM>(lat, a, fpar);
         float go0, gx;
         const float g = gy[n];
         affine_bwd(d.final_tanh, o0, xs[n], g, gld, go0, gx);
@@ -335,18 +375,17 @@ __global__ void __launch_bounds__(64 * kResWaves) kg_backward(NetDev d, ResLds S
 
 // ---- staged kernels --------------------------------------------------------------
 
-// log q = log r - sum of the sites' s sums (one block per sample).
-template <typename R>
-__global__ void __launch_bounds__(256) kg_end(int half, const R* __restrict__ ld, const double* __restrict__ logr,
+// log q = log r - the sum of the tiles' sums (one block per sample).
+__global__ void __launch_bounds__(256) kg_end(int tiles, const double* __restrict__ ld, const double* __restrict__ logr,
                                               double* __restrict__ logq, double* __restrict__ logdet) {
-  __shared__ R sh[16];
+  __shared__ double sh[16];
   const int b = blockIdx.x;
-  R acc = 0;
-  for (int a = threadIdx.x; a < half; a += blockDim.x) acc += ld[(size_t)b * half + a];
+  double acc = 0;
+  for (int t = threadIdx.x; t < tiles; t += blockDim.x) acc += ld[(size_t)b * tiles + t];
   acc = block_sum(acc, sh);
   if (threadIdx.x == 0) {
-    logq[b] = logr[b] - (double)acc;
-    if (logdet) logdet[b] = (double)acc;
+    logq[b] = logr[b] - acc;
+    if (logdet) logdet[b] = acc;
   }
 }
 
@@ -364,7 +403,7 @@ struct StagedArgs {
   const float* x;    // Couple: the layer's field; Affine: likewise
   float* xout;       // Couple: the next field (may be x); Affine: g_x
   float* xout2;      // Couple: a second copy of the next field, or null
-  void* ld;          // Couple: per active site sums of s, [B][V / 2]
+  double* ld;        // Couple: the sums of s of every tile of 16 active sites, [B][ld_tiles(V)]
   int first;         // Couple: the sums start here
   const float* gy;   // Affine: the cotangent of the layer's output; GradField: unused
   float gld;
@@ -382,7 +421,6 @@ struct StagedArgs {
 //   GradField  g_x += conv^T(g)                         frozen sites
 template <int DIM, int MODE, Op OP, bool LF>
 __global__ void __launch_bounds__(256) kg_staged(NetDev d, StagedArgs A, const u32x4* frags) {
-  using R = std::conditional_t<MODE == kBf16, double, float>;
   constexpr bool TR = OP == Op::Grad || OP == Op::GradField;
   constexpr bool HALF = OP == Op::Couple || OP == Op::Affine || OP == Op::GradField;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -432,30 +470,35 @@ __global__ void __launch_bounds__(256) kg_staged(NetDev d, StagedArgs A, const u
                         (4 * pl + k - c.rows) >> 31);
         *reinterpret_cast<f32x4*>(A.out + (size_t)b * A.out_ss + ((size_t)pl * V + n) * 4) = v;
       }
+    } else if constexpr (OP == Op::Couple) {
+      float sv = 0.f;
+      if (valid && j == 0) {
+        const size_t o = (size_t)b * V + n, of = (size_t)b * V + half_site<DIM>(lat, a, A.fpar);
+        sv = d.final_tanh ? tanhf(acc[0]) : acc[0];
+        const float xn = A.x[o] * expf(sv) + acc[1], xf = A.x[of];
+        A.xout[o] = xn;
+        if (A.xout != A.x) A.xout[of] = xf;
+        if (A.xout2) A.xout2[o] = xn, A.xout2[of] = xf;
+      }
+      const double t = tile_sum(sv);
+      if (lane == 0 && valid) {
+        double* ld = A.ld + (size_t)b * ld_tiles(V) + (a >> 4);
+        *ld = A.first ? t : *ld + t;
+      }
     } else if (valid && j == 0) {
       const size_t o = (size_t)b * V + n;
       if constexpr (OP == Op::GradField) {
         A.xout[o] += acc[0];
       } else {
         const size_t of = (size_t)b * V + half_site<DIM>(lat, a, A.fpar);
-        if constexpr (OP == Op::Couple) {
-          const float sv = d.final_tanh ? tanhf(acc[0]) : acc[0];
-          const float xn = A.x[o] * expf(sv) + acc[1], xf = A.x[of];
-          A.xout[o] = xn;
-          if (A.xout != A.x) A.xout[of] = xf;
-          if (A.xout2) A.xout2[o] = xn, A.xout2[of] = xf;
-          R* ld = reinterpret_cast<R*>(A.ld) + (size_t)b * half + a;
-          *ld = A.first ? (R)sv : *ld + (R)sv;
-        } else {
-          float go0, gx;
-          const float g = A.gy[o];
-          affine_bwd(d.final_tanh, acc[0], A.x[o], g, A.gld_vec ? (float)(-A.gld_vec[b]) : A.gld, go0, gx);
-          A.xout[o] = gx;
-          A.xout[of] = A.gy[of];
-          float* go = A.out + (size_t)b * A.out_ss;
-          *reinterpret_cast<f32x4*>(go + 4 * n) = f32x4{go0, g, 0.f, 0.f};
-          *reinterpret_cast<f32x4*>(go + 4 * half_site<DIM>(lat, a, A.fpar)) = f32x4{0.f, 0.f, 0.f, 0.f};
-        }
+        float go0, gx;
+        const float g = A.gy[o];
+        affine_bwd(d.final_tanh, acc[0], A.x[o], g, A.gld_vec ? (float)(-A.gld_vec[b]) : A.gld, go0, gx);
+        A.xout[o] = gx;
+        A.xout[of] = A.gy[of];
+        float* go = A.out + (size_t)b * A.out_ss;
+        *reinterpret_cast<f32x4*>(go + 4 * n) = f32x4{go0, g, 0.f, 0.f};
+        *reinterpret_cast<f32x4*>(go + 4 * half_site<DIM>(lat, a, A.fpar)) = f32x4{0.f, 0.f, 0.f, 0.f};
       }
     }
   }
@@ -540,11 +583,10 @@ int32_t staged(const NetDev& d, StagedArgs a, int layer, const FragSrc& src, hip
 }
 
 // Bytes of the staged forward of B samples beside the fragments: log r, the log-det
-// sums of the active sites and the hidden activations (two sets of planes, the
+// sums of the tiles of active sites and the hidden activations (two sets of planes, the
 // convolutions alternating between them).
 struct StagedWs {
-  double* logr;
-  void* ld;
+  double *logr, *ld;
   float* planes[2];
   size_t bytes;
 };
@@ -560,7 +602,7 @@ StagedWs staged_ws(const NetDev& d, int B, char* base) {
   int q[2] = {0, 0};
   for (int i = 0; i + 1 < d.n_conv; ++i) q[i & 1] = std::max(q[i & 1], cdiv(d.cout[i], 4));
   w.logr = (double*)take(sizeof(double) * B);
-  w.ld = take(BV / 2 * (d.mode == kBf16 ? sizeof(double) : sizeof(float)));
+  w.ld = (double*)take(sizeof(double) * B * ld_tiles(d.lat.V));
   for (int k = 0; k < 2; ++k) w.planes[k] = (float*)take(BV * 16 * q[k]);
   w.bytes = off;
   return w;
@@ -599,8 +641,7 @@ int32_t forward_staged(const FlowGeom& g, const NetDev& d, int B, const float* z
     LFS_TRY((staged<DIM, MODE, Op::Couple>(d, a, l, src, st)));
     x = xn;
   }
-  hipLaunchKernelGGL((kg_end<R>), dim3(B), dim3(256), 0, st, V / 2, reinterpret_cast<const R*>(w.ld), w.logr, logq,
-                     logdet);
+  hipLaunchKernelGGL(kg_end, dim3(B), dim3(256), 0, st, ld_tiles(V), w.ld, w.logr, logq, logdet);
   return launch_status();
 }
 

@@ -134,6 +134,9 @@ __device__ __forceinline__ void affine_bwd(int final_tanh, float o0, float x, fl
   gx = g * es;
 }
 
+// log r of a sample of V sites from the sum of its squares.
+__device__ __forceinline__ double log_prior(int V, double zz) { return -0.5 * zz - (double)V * kHalfLog2Pi; }
+
 // log r(z) per sample and the first field: saved[0], or phi (which may be z).
 template <typename R>
 __global__ void __launch_bounds__(256) kg_begin(int V, const float* z, float* x, double* __restrict__ logr) {
@@ -146,7 +149,7 @@ __global__ void __launch_bounds__(256) kg_begin(int V, const float* z, float* x,
     acc += (R)v * v;
   }
   acc = block_sum(acc, sh);
-  if (threadIdx.x == 0) logr[b] = -0.5 * (double)acc - (double)V * kHalfLog2Pi;
+  if (threadIdx.x == 0) logr[b] = log_prior(V, (double)acc);
 }
 
 // ---- weight gradients --------------------------------------------------------------

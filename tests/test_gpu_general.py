@@ -104,3 +104,25 @@ def test_weight_gradient_slabs(case):
     desc, params, z, fs = _case(*case, lfs.LFS_PLAIN_FP32)
     out, _ = _check_forward(desc, params, z, fs, lfs.LFS_PLAIN_FP32)
     _check_backward(desc, params, z, fs, out, lfs.LFS_PLAIN_FP32)
+
+
+@pytest.mark.parametrize("dim,L,N,C,hs,B", [
+    (2, 12, 12, 8, None, 3),          # the default network, a sample in LDS, a ragged last tile
+    (3, 8, 16, 0, (5,), 2),           # many tiles per wave
+    (2, 2, 5, 0, (3, 3), 4),          # one tile, two active sites
+    (2, 68, 16, 16, None, 2),         # a launch per convolution
+    (3, 10, 16, 0, (16, 6), 3),
+])
+@pytest.mark.parametrize("precision", [lfs.LFS_PLAIN_FP32, lfs.LFS_BF16_CONV])
+def test_log_det_keeps_every_bit_of_s(dim, L, N, C, hs, B, precision):
+    """With s = b exactly at every active site the log-det is N (V / 2) b: sums of s in FP64 are
+    within (terms + layers) roundings of it, and sums over layers in FP32 are not."""
+    print(f"log-det dim={dim} L={L} N={N} C={C} hidden={hs} precision={precision}", flush=True)
+    V = L ** dim
+    desc = lfs.make_desc(dim, L, N, C, final_tanh=False, precision=precision, hidden_sizes=hs)
+    params = np.zeros((N, lfs.param_count(desc) // N), np.float32)
+    params[:, -2] = b = np.float32(-0.1)
+    out = run_forward(desc, params.ravel(), si.normal_fields(5, B, V))
+    exact = N * (V // 2) * float(b)
+    bound = (V // 2 + N) * 2.0 ** -53 * abs(exact)
+    assert np.all(np.abs(host(out["logdet"]) - exact) <= bound)
