@@ -35,6 +35,8 @@ __device__ __forceinline__ void put_chunk(uint64_t path, int lane, bool valid, i
 // Chain c reads proposals [offsets[c], offsets[c+1]) (rectangular calls pass
 // offsets == NULL and use [c * n_prop, (c+1) * n_prop)); its state lives at
 // state[state_index[c]] (or state[c]).
+// Positions are unsigned here and below: chunks are looked up past the end, which for the
+// longest chain (2^31 - 1 proposals) is past the largest int.
 __global__ void __launch_bounds__(64) k_mh_chain(int n_prop_rect, const int64_t* __restrict__ offsets,
                                                  const double* __restrict__ logw,
                                                  const double* __restrict__ log_u,
@@ -44,18 +46,19 @@ __global__ void __launch_bounds__(64) k_mh_chain(int n_prop_rect, const int64_t*
                                                  uint8_t* __restrict__ accepted) {
   const int c = blockIdx.x, lane = threadIdx.x;
   const size_t base = offsets ? (size_t)offsets[c] : (size_t)c * n_prop_rect;
-  const int n_prop = offsets ? (int)(offsets[c + 1] - offsets[c]) : n_prop_rect;
+  const int count = offsets ? (int)(offsets[c + 1] - offsets[c]) : n_prop_rect;
+  const unsigned n_prop = (unsigned)max(count, 0);
   lfs_chain_state* state = states + (state_index ? state_index[c] : c);
   lfs_chain_state st = *state;
   const int64_t seen0 = st.n_seen;
   // lanes past the end never accept
-  auto load = [&](int k, double& w, double& u) {
+  auto load = [&](unsigned k, double& w, double& u) {
     w = k < n_prop ? logw[base + k] : 0.0;
     u = k < n_prop ? log_u[base + k] : HUGE_VAL;
   };
   double w, u, wn, un;
   load(lane, w, u);
-  for (int k0 = 0; k0 < n_prop; k0 += kWave) {
+  for (unsigned k0 = 0; k0 < n_prop; k0 += kWave) {
     load(k0 + kWave + lane, wn, un);
     const int64_t g0 = seen0 + k0;
     uint64_t path = 0, open = ~0ull;  // open: positions after the last accepted one
@@ -77,13 +80,13 @@ __global__ void __launch_bounds__(64) k_mh_chain(int n_prop_rect, const int64_t*
     const int64_t before = st.idx_cur;
     if (path) st.idx_cur = g0 + (63 - __builtin_clzll(path));
     st.n_acc += __builtin_popcountll(path & ~seed);
-    const int k = k0 + lane;
+    const unsigned k = k0 + lane;
     put_chunk(path, lane, k < n_prop, g0, before, cur_idx + base + k, accepted ? accepted + base + k : nullptr);
     w = wn;
     u = un;
   }
   if (lane == 0) {
-    st.n_seen = seen0 + n_prop;
+    st.n_seen = seen0 + count;
     *state = st;
   }
 }
@@ -97,11 +100,12 @@ __global__ void __launch_bounds__(64) k_mh_chain(int n_prop_rect, const int64_t*
 // chunks in order: one test against w_cur finds the first accepted position, its mask the
 // rest.  65536 proposals at acceptance 0.43: 5046 -> 198 us, of which the walk 192
 // (2.9 ns per proposal; lane 0 alone took 77).
-__global__ void __launch_bounds__(256) k_mh_paths(int n_prop, const double* __restrict__ logw,
+__global__ void __launch_bounds__(256) k_mh_paths(unsigned n_prop, const double* __restrict__ logw,
                                                   const double* __restrict__ log_u, int64_t* __restrict__ cur_idx) {
-  const int lane = threadIdx.x & 63, k0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * kWave;
+  const int lane = threadIdx.x & 63;
+  const unsigned k0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * kWave;
   if (k0 >= n_prop) return;
-  const size_t at = (size_t)blockIdx.y * n_prop + k0 + lane;
+  const size_t at = (size_t)blockIdx.y * n_prop + (k0 + lane);
   const bool valid = k0 + lane < n_prop;
   const double w = valid ? logw[at] : 0.0, u = valid ? log_u[at] : HUGE_VAL;
   int next = 0;
@@ -126,7 +130,7 @@ __global__ void __launch_bounds__(256) k_mh_paths(int n_prop, const double* __re
 // one, which as per-lane 64-bit arithmetic costs as much as the decisions (one wave doing
 // both: 380 us).
 constexpr int kWalkChunks = 16;  // chunks per group
-__global__ void __launch_bounds__(256) k_mh_walk(int n_prop, const double* __restrict__ logw,
+__global__ void __launch_bounds__(256) k_mh_walk(unsigned n_prop, const double* __restrict__ logw,
                                                  const double* __restrict__ log_u, lfs_chain_state* __restrict__ states,
                                                  int64_t* cur_idx, uint8_t* __restrict__ accepted) {
   constexpr int GP = kWalkChunks * kWave;
@@ -137,14 +141,15 @@ __global__ void __launch_bounds__(256) k_mh_walk(int n_prop, const double* __res
   const size_t base = (size_t)c * n_prop;
   lfs_chain_state st = states[c];
   const int64_t seen0 = st.n_seen;
-  const int groups = (n_prop + GP - 1) / GP;
-  auto fetch = [&](int g, int first, int waves) {
+  const unsigned groups = (n_prop + GP - 1) / GP;
+  auto fetch = [&](unsigned g, int first, int waves) {
     constexpr int MX = (kWalkChunks + 2) / 3;
     double w[MX], u[MX];
     uint64_t p[MX];
 #pragma unroll
     for (int i = 0; i < MX; ++i) {
-      const int ch = first + i * waves, k = g * GP + ch * kWave + lane;
+      const int ch = first + i * waves;
+      const unsigned k = g * GP + ch * kWave + lane;
       const bool ok = ch < kWalkChunks && k < n_prop;
       w[i] = ok ? logw[base + k] : 0.0;
       u[i] = ok ? log_u[base + k] : HUGE_VAL;  // lanes past the end never accept
@@ -158,14 +163,14 @@ __global__ void __launch_bounds__(256) k_mh_walk(int n_prop, const double* __res
   };
   fetch(0, wv, 4);
   __syncthreads();
-  for (int g = 0; g <= groups; ++g) {
+  for (unsigned g = 0; g <= groups; ++g) {
     if (wv == 0) {
       if (g < groups) {
         const double *w = sw[g & 1], *u = su[g & 1];
         const uint64_t* p = sp[g & 1];
         double wl = w[lane], ul = u[lane];
         uint64_t pl = p[lane];
-        const int chunks = min(kWalkChunks, (n_prop - g * GP + kWave - 1) / kWave);
+        const int chunks = (int)min((unsigned)kWalkChunks, (n_prop - g * GP + kWave - 1) / kWave);
         for (int i = 0; i < chunks; ++i) {
           const int nx = min(i + 1, kWalkChunks - 1) * kWave + lane;
           const double wn = w[nx], un = u[nx];
@@ -190,7 +195,7 @@ __global__ void __launch_bounds__(256) k_mh_walk(int n_prop, const double* __res
     } else {
       if (g > 0) {
         for (int i = wv - 1; i < kWalkChunks; i += 3) {
-          const int kc = (g - 1) * GP + i * kWave, k = kc + lane;
+          const unsigned kc = (g - 1) * GP + i * kWave, k = kc + lane;
           if (kc < n_prop)
             put_chunk(spath[(g - 1) & 1][i], lane, k < n_prop, seen0 + kc, sbefore[(g - 1) & 1][i], cur_idx + base + k,
                       accepted ? accepted + base + k : nullptr);
@@ -327,8 +332,8 @@ extern "C" int32_t lfs_mh_chain(int32_t n_chains, int32_t n_prop, const double* 
     return lfs::launch_status();
   }
   const unsigned chunks = ((unsigned)n_prop + lfs::kWave - 1) / lfs::kWave;
-  hipLaunchKernelGGL(lfs::k_mh_paths, dim3((chunks + 3) / 4, n_chains), dim3(256), 0, st, n_prop, logw, log_u, cur_idx);
-  hipLaunchKernelGGL(lfs::k_mh_walk, dim3(n_chains), dim3(256), 0, st, n_prop, logw, log_u, state, cur_idx,
+  hipLaunchKernelGGL(lfs::k_mh_paths, dim3((chunks + 3) / 4, n_chains), dim3(256), 0, st, (unsigned)n_prop, logw, log_u, cur_idx);
+  hipLaunchKernelGGL(lfs::k_mh_walk, dim3(n_chains), dim3(256), 0, st, (unsigned)n_prop, logw, log_u, state, cur_idx,
                      accepted);
   return lfs::launch_status();
 }

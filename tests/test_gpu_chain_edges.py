@@ -84,3 +84,33 @@ def test_ess_edges(n):
     out = torch.empty(1, dtype=torch.float64, device="cuda")
     lfs.ess(dev(w, torch.float64), out)
     assert abs(float(out.item()) - an.ess(w)) <= 1e-12
+
+
+@pytest.mark.parametrize("ragged", [False, True])
+def test_longest_chain(ragged):
+    """2^31 - 1 proposals, the most a call can name: what is looked up past the end lies past
+    the largest int.  Accepted at a few positions only, so the record is known."""
+    n = 2 ** 31 - 1
+    at = [0, 5, 2 ** 30 + 17, n - 66, n - 1]
+    logw = torch.zeros(1, n, dtype=torch.float64, device="cuda")
+    lu = torch.ones(1, n, dtype=torch.float64, device="cuda")
+    lu[0, at[1:]] = -1.0
+    cur = torch.full((1, n), -7, dtype=torch.int64, device="cuda")
+    acc = torch.full((1, n), 9, dtype=torch.uint8, device="cuda")
+    state = lfs.new_chain_state(1)
+    print(f"longest chain, ragged={ragged}", flush=True)
+    if ragged:
+        lfs.mh_chain_ragged(torch.tensor([0, n], device="cuda"), logw.view(-1), lu.view(-1), state,
+                            torch.zeros(1, dtype=torch.int32, device="cuda"), cur.view(-1), acc.view(-1))
+    else:
+        lfs.mh_chain(logw, lu, state, cur, acc)
+    torch.cuda.synchronize()
+    print("done", flush=True)
+    del logw, lu
+    for a, b in zip(at, at[1:] + [n]):
+        assert bool((cur[0, a:b] == a).all()) and int(acc[0, a]) == 1
+    assert int(acc.sum(dtype=torch.int64)) == len(at)
+    st = lfs.decode_chain_state(state)[0]
+    assert st["n_seen"] == n and st["n_acc"] == len(at) - 1 and st["idx_cur"] == n - 1 and st["w_cur"] == 0.0
+    del cur, acc
+    torch.cuda.empty_cache()
