@@ -207,23 +207,22 @@ int32_t lfs_flow_forward(const lfs_flow_desc* desc, const float* params, int32_t
 
 /* lfs_flow_forward for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid allocation):
- * the same kernels and results, bit for bit (but see below), with the
- * workspace taken from a static device array of LFS_NOALLOC_SCRATCH_BYTES that the library holds on
- * every GPU it runs on until the process ends (its address is looked up once
- * per device, on the first call with that device current).  The call allocates
+ * the same results, bit for bit, with the workspace taken from a static device
+ * array (of 12 MiB) that the library holds on every GPU it runs on until the
+ * process ends (its address is looked up once per device, on the first call
+ * with that device current).  The call allocates
  * and frees nothing.  Every call on one GPU shares that GPU's array: calls
  * that overlap on one GPU (different streams, or host threads) race and must
  * be serialised by the caller.  Nothing in the array needs to start at zero.
  * Arguments as lfs_flow_forward, without ws and ws_bytes.
- * Errors: as lfs_flow_forward; LFS_EWORKSPACE when LFS_NOALLOC_SCRATCH_BYTES
- * cannot hold the fused forward's weight fragments (at most 85 KB per layer, at
+ * Errors: as lfs_flow_forward; LFS_EWORKSPACE, and then only, when
+ * LFS_NOALLOC_SCRATCH_BYTES would not hold the fused forward's weight fragments (at most 85 KB per layer, at
  * any batch) or, for the general kernels, two FP64 numbers per sample and the
  * FP32 hidden activations of the whole batch (and the two output channels of a
  * network other than the default one), whether or not they need that much.
- * Where the general kernels' weight fragments of all layers do not fit beside
- * what else they need, they are prepared convolution by convolution and the
- * batch is processed in parts; small lattices then sum their convolutions in
- * another order than lfs_flow_forward (equal to FP32 rounding). */
+ * Where the array does not hold what the general kernels need at once, the
+ * weight fragments are prepared layer by layer or convolution by convolution
+ * and the batch is processed in parts. */
 #define LFS_NOALLOC_SCRATCH_BYTES ((size_t)8 << 20)
 int32_t lfs_flow_forward_noalloc(const lfs_flow_desc* desc, const float* params, int32_t B,
                                  const float* z, float* phi, double* logq, double* logdet,

@@ -104,8 +104,8 @@ size_t ws_bytes_of(const FlowGeom& g, int B, int bwd) {
   }
 }
 
-// What lfs_flow_forward_noalloc holds against its scratch: the fused kernels' weight
-// fragments, or two numbers per sample and the hidden activations (and, in a network
+// What lfs_flow_forward_noalloc holds against LFS_NOALLOC_SCRATCH_BYTES: the fused kernels'
+// weight fragments, or two numbers per sample and the hidden activations (and, in a network
 // other than the default one, the outputs) of the whole batch.
 size_t noalloc_bytes(const FlowGeom& g, int B) {
   if (family(g, 0) == Family::Fused) return fused_ws_bytes(g, B, 0);
@@ -313,14 +313,20 @@ extern "C" int32_t lfs_flow_backward_bn(const lfs_flow_desc* desc, const float* 
 }
 
 // ---- allocation-free forward ------------------------------------------------
-// The forward's workspace (weight fragments, or the generic kernels' hidden
+// The forward's workspace (weight fragments, or the general kernels' hidden
 // activations) lives in one file-scope device array instead of caller memory.
+// Whatever noalloc_bytes lets through fits it, one sample at a time if need be: the
+// general kernels pad channels to four and hold a row tile's fragments beside the two
+// activations, at most 11.7 MB (3D L = 62, hidden [5, 1], kernel 7), or a layer's
+// fragments in BF16, at most 9.0 MB (3D, kernel 7, hidden [64, 64, 64, 64]), and 8 bytes
+// per sample and 32 sites, at most 1.4 MB.
 // Its device address differs per GPU and is looked up once per device with
 // that device current; host code never passes the array's name to a kernel.
 namespace lfs {
 namespace {
 
-__device__ __align__(256) unsigned char scratch[LFS_NOALLOC_SCRATCH_BYTES];
+constexpr size_t kScratchBytes = (size_t)12 << 20;
+__device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -358,6 +364,6 @@ extern "C" int32_t lfs_flow_forward_noalloc(const lfs_flow_desc* desc, const flo
   if (lfs::family(g, 0) == lfs::Family::Fused)
     return lfs_flow_forward(desc, params, B, z, phi, logq, logdet, saved_x, ws, LFS_NOALLOC_SCRATCH_BYTES, stream);
   if (!params || !z || !phi || !logq) return LFS_EINVAL;
-  return lfs::general_forward(g, params, B, z, phi, logq, logdet, saved_x, (char*)ws, LFS_NOALLOC_SCRATCH_BYTES,
+  return lfs::general_forward(g, params, B, z, phi, logq, logdet, saved_x, (char*)ws, lfs::kScratchBytes,
                               (hipStream_t)stream);
 }

@@ -177,12 +177,15 @@ __device__ __forceinline__ T sum_of_256(int n, F&& v) {
 
 // ---- resident forward ----------------------------------------------------------
 
+// Layers [l0, l1), whose fragments frags are: all of them, or, where the workspace does not
+// hold as many, group after group (z of a later one is the earlier one's phi; log r waits in
+// logq, the tiles' sums in carry [B][ld_tiles(V)]).
 // LF: a layer's fragments are read from LDS, the next layer's copied there meanwhile.
 template <int DIM, int MODE, bool LF>
 __global__ void __launch_bounds__(64 * kResWaves) kg_forward(NetDev d, ResLds S, const u32x4* __restrict__ frags,
-                                                             int B, const float* z, float* phi,
-                                                             float* __restrict__ saved, double* __restrict__ logq,
-                                                             double* __restrict__ logdet) {
+                                                             int l0, int l1, int B, const float* z, float* phi,
+                                                             float* __restrict__ saved, double* logq,
+                                                             double* __restrict__ logdet, double* carry) {
   using R = std::conditional_t<MODE == kBf16, double, float>;
   extern __shared__ __align__(16) unsigned char smem[];
   const int V = d.lat.V, F = d.frags_fwd, lane = threadIdx.x & 63;
@@ -198,24 +201,26 @@ __global__ void __launch_bounds__(64 * kResWaves) kg_forward(NetDev d, ResLds S,
     for (int n = threadIdx.x; n < V; n += blockDim.x) {
       const float v = z[(size_t)b * V + n];
       xs[n] = v;
-      xm[n] = masked(v, (parity_of<DIM>(site_of<DIM>(d.lat, n)) ^ d.parity0) - 1);
-      if (saved) saved[(size_t)b * V + n] = v;
+      xm[n] = masked(v, (parity_of<DIM>(site_of<DIM>(d.lat, n)) ^ ((l0 + d.parity0) & 1)) - 1);
+      if (saved && l0 == 0) saved[(size_t)b * V + n] = v;
     }
+    double* cb = carry + (size_t)b * ld_tiles(V);
     if (sums)
-      for (int t = lane; t < ld_tiles(V); t += 64) ts[t] = 0.0;
+      for (int t = lane; t < ld_tiles(V); t += 64) ts[t] = l0 > 0 ? cb[t] : 0.0;
     if constexpr (LF) wait_copies();
     lds_barrier();
     double logr = 0.0;
-    if (sums) logr = log_prior(V, sum_of_256<R>(V, [&](int n) { return (R)xs[n] * xs[n]; }));
-    for (int l = 0; l < d.N; ++l) {
+    if (sums)
+      logr = l0 > 0 ? logq[b] : log_prior(V, sum_of_256<R>(V, [&](int n) { return (R)xs[n] * xs[n]; }));
+    for (int l = l0; l < l1; ++l) {
       const int fpar = (l + d.parity0) & 1;
       const u32x4* fr;
       if constexpr (LF) {
         fr = reinterpret_cast<const u32x4*>(smem + S.frags[cur]);
         cur ^= 1;
-        copy_frags(frags + (size_t)(l + 1 < d.N ? l + 1 : 0) * F * 64, smem + S.frags[cur], F);
+        copy_frags(frags + (size_t)(l + 1 < l1 ? l + 1 - l0 : 0) * F * 64, smem + S.frags[cur], F);
       } else {
-        fr = frags + (size_t)l * F * 64;
+        fr = frags + (size_t)(l - l0) * F * 64;
       }
       hidden_convs<MODE>(d, S, smem, fr, [](int, int, int, const f32x4&) {});
       last_conv<DIM, MODE>(d, S, smem, fr, fpar ^ 1, [&](int tile, int a, float o0, float o1) {
@@ -239,7 +244,10 @@ __global__ void __launch_bounds__(64 * kResWaves) kg_forward(NetDev d, ResLds S,
       }
     }
     for (int n = threadIdx.x; n < V; n += blockDim.x) phi[(size_t)b * V + n] = xs[n];
-    if (sums) {
+    if (sums && l1 < d.N) {
+      for (int t = lane; t < ld_tiles(V); t += 64) cb[t] = ts[t];
+      if (lane == 0) logq[b] = logr;
+    } else if (sums) {
       const double ld = sum_of_256<double>(ld_tiles(V), [&](int t) { return ts[t]; });
       if (lane == 0) {
         logq[b] = logr - ld;
@@ -650,24 +658,35 @@ int32_t forward_impl(const FlowGeom& g, const float* params, int B, const float*
                      double* logdet, float* saved, char* ws, size_t ws_bytes, hipStream_t st) {
   const NetDev d = make_net(g);
   const size_t fb = frag_bytes(d, false), BV = (size_t)B * g.V;
-  const bool res = resident(d, false);
-  if (ws_bytes >= fb + (res ? 0 : staged_ws(d, B, nullptr).bytes)) {
+  // the static scratch may be smaller than general_ws_bytes
+  if (resident(d, false)) {
+    const ResLds S = res_lds(d, false);
+    const size_t layer = (size_t)d.frags_fwd * 1024, cb = align_up(sizeof(double) * B * ld_tiles(d.lat.V));
+    const bool whole = ws_bytes >= fb;
+    const int group = whole ? d.N : ws_bytes < cb ? 0 : (int)std::min<size_t>(d.N, (ws_bytes - cb) / layer);
+    double* carry = whole ? nullptr : reinterpret_cast<double*>(ws);
+    u32x4* frags = reinterpret_cast<u32x4*>(ws + (whole ? 0 : cb));
+    for (int l0 = 0; group > 0 && l0 < d.N; l0 += group) {
+      const int l1 = std::min(l0 + group, d.N);
+      prep<MODE>(d, params + (size_t)l0 * d.P_layer, l1 - l0, 0, d.frags_fwd, frags, st);
+      LFS_TRY(with_lf(S.lf, [&](auto lf) {
+        constexpr auto k = kg_forward<DIM, MODE, decltype(lf)::value>;
+        if (!set_lds_limit<k>(kLdsMax)) return (int32_t)LFS_EDEVICE;
+        hipLaunchKernelGGL(k, dim3((unsigned)std::min(B, num_cus())), dim3(64 * kResWaves), S.total, st, d, S, frags,
+                           l0, l1, B, l0 > 0 ? phi : z, phi, saved, logq, logdet, carry);
+        return launch_status();
+      }));
+    }
+    if (group > 0) return LFS_OK;
+  } else if (ws_bytes >= fb + staged_ws(d, B, nullptr).bytes) {
     u32x4* frags = reinterpret_cast<u32x4*>(ws);
     prep<MODE>(d, params, d.N, 0, d.frags_fwd, frags, st);
-    if (!res)
-      return forward_staged<DIM, MODE>(g, d, B, z, phi, logq, logdet, saved, BV, staged_ws(d, B, ws + fb),
-                                       FragSrc{frags, d.frags_fwd, fb, params}, st);
-    const ResLds S = res_lds(d, false);
-    return with_lf(S.lf, [&](auto lf) {
-      constexpr auto k = kg_forward<DIM, MODE, decltype(lf)::value>;
-      if (!set_lds_limit<k>(kLdsMax)) return (int32_t)LFS_EDEVICE;
-      hipLaunchKernelGGL(k, dim3((unsigned)std::min(B, num_cus())), dim3(64 * kResWaves), S.total, st, d, S, frags, B,
-                         z, phi, saved, logq, logdet);
-      return launch_status();
-    });
+    return forward_staged<DIM, MODE>(g, d, B, z, phi, logq, logdet, saved, BV, staged_ws(d, B, ws + fb),
+                                     FragSrc{frags, d.frags_fwd, fb, params}, st);
   }
-  // a workspace without room for every layer's fragments (the static scratch): the staged
-  // kernels on as many samples at a time as leave room for a row tile's fragments
+  // no room for a layer's fragments (FP32: the sums' order is that of the resident kernels),
+  // or for the whole batch's activations: the staged kernels on as many samples at a time as
+  // leave room for a row tile's fragments
   size_t one = 0;
   for (int i = 0; i < d.n_conv; ++i) one = std::max(one, (size_t)d.f[i].per_ct() * 1024);
   int step = B;

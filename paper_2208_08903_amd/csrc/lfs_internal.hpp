@@ -41,8 +41,8 @@ int32_t make_geom(const lfs_flow_desc* desc, FlowGeom* g);
 inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 
 // General kernels: any network without batch norm on any supported lattice.  A forward
-// workspace smaller than general_ws_bytes is used as far as it goes (LFS_EWORKSPACE
-// where not even one sample fits).
+// workspace smaller than general_ws_bytes is used as far as it goes, with the same bits
+// (LFS_EWORKSPACE where not even one sample fits).
 size_t general_ws_bytes(const FlowGeom& g, int B, int for_backward);
 int32_t general_forward(const FlowGeom& g, const float* params, int B, const float* z, float* phi,
                         double* logq, double* logdet, float* saved, char* ws, size_t ws_bytes, hipStream_t st);
