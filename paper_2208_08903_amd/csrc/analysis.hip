@@ -141,11 +141,22 @@ __global__ void __launch_bounds__(kThreads) k_ac_partial(int64_t n, int T, int c
   // d[q]: element i0 + q for q < chunk, then element i0 + lag0 + q - chunk onwards, where
   // lag0 is the workgroup's first lag
   const int lag0 = blockIdx.z * kThreads * 4, span = chunk + 4 * kThreads + 4;
+  bool wild = false;
   for (int q = threadIdx.x; q < chunk + span; q += kThreads) {
     const int64_t k = i0 + (q < chunk ? q : lag0 + q - chunk);
-    d[q] = k < n ? x[(size_t)s * ldx + series_at(index, n, s, k)] - mu : 0.0;
+    const double v = k < n ? x[(size_t)s * ldx + series_at(index, n, s, k)] - mu : 0.0;
+    wild |= !__builtin_isfinite(v);
+    d[q] = v;
   }
-  __syncthreads();
+  if (__syncthreads_or(wild)) {  // the zeros past the end would turn an infinity into a NaN
+    for (int t = t0; t < t0 + 4 && t <= T; ++t) {
+      const double* b = d + chunk + (t - lag0);
+      double acc = 0.0;
+      for (int i = 0; i < chunk && i < n - i0 - t; ++i) acc += d[i] * b[i];
+      out[t] = acc;
+    }
+    return;
+  }
   if (t0 > T) return;
   const f64x2* a = reinterpret_cast<const f64x2*>(d);
   const f64x2* b = reinterpret_cast<const f64x2*>(d + chunk + 4 * threadIdx.x);

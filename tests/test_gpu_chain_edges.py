@@ -114,3 +114,20 @@ def test_longest_chain(ragged):
     assert st["n_seen"] == n and st["n_acc"] == len(at) - 1 and st["idx_cur"] == n - 1 and st["w_cur"] == 0.0
     del cur, acc
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+@pytest.mark.parametrize("n,at", [(600, 300), (600, 0), (1500, 800)])
+def test_autocorr_of_infinities(n, at, value):
+    """A lag's average is over its own pairs only: it is infinite where no pair holds the
+    element whose deviation is NaN, and NaN where one does."""
+    x = si.correlated_series(71, 1, n, 0.7)
+    x[0, at] = value
+    gamma = torch.empty(1, n, dtype=torch.float64, device="cuda")
+    tau = torch.empty(1, dtype=torch.float64, device="cuda")
+    lfs.autocorr(dev(x, torch.float64), n - 1, 6.0, tau, gamma=gamma)
+    with np.errstate(invalid="ignore"):
+        d = x[0] - x[0].mean()
+        ref = np.array([np.sum(d[:n - t] * d[t:]) / (n - t) for t in range(n)])
+    np.testing.assert_array_equal(host(gamma)[0], ref)
+    assert np.isnan(float(tau.item()))
