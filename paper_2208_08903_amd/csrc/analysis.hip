@@ -114,6 +114,9 @@ __device__ __forceinline__ double series_mean(int64_t n, int nsum, const double*
   return wave_sum(lane < nsum ? sums[lane] : 0.0) / (double)n;
 }
 
+// Lags 0 .. T, at most those of a workgroup, in fours.
+__host__ __device__ inline int ac_lags(int T) { return T + 4 < 4 * kThreads ? (T + 4) / 4 * 4 : 4 * kThreads; }
+
 // Partial autocovariance sums of one chunk of elements against i + t, for kThreads groups
 // of four consecutive lags: deviations from the mean in LDS, zeros past the series' end.
 // A thread slides over the chunk four elements at a time, so its 16 products take four
@@ -126,7 +129,7 @@ __global__ void __launch_bounds__(kThreads) k_ac_partial(int64_t n, int T, int c
                                                         const double* __restrict__ sums,
                                                         const int32_t* __restrict__ bad,
                                                         double* __restrict__ partial) {
-  extern __shared__ __align__(16) double d[];  // [chunk + 4 kThreads + 4]
+  extern __shared__ __align__(16) double d[];  // [2 chunk + lags of the workgroup]
   typedef double f64x2 __attribute__((ext_vector_type(2)));
   const int c = blockIdx.x, s = blockIdx.y, nchunk = gridDim.x, t0 = (blockIdx.z * kThreads + threadIdx.x) * 4;
   const int64_t i0 = (int64_t)c * chunk;
@@ -140,7 +143,7 @@ __global__ void __launch_bounds__(kThreads) k_ac_partial(int64_t n, int T, int c
   }
   // d[q]: element i0 + q for q < chunk, then element i0 + lag0 + q - chunk onwards, where
   // lag0 is the workgroup's first lag
-  const int lag0 = blockIdx.z * kThreads * 4, span = chunk + 4 * kThreads + 4;
+  const int lag0 = blockIdx.z * kThreads * 4, span = chunk + ac_lags(T - lag0);
   bool wild = false;
   for (int q = threadIdx.x; q < chunk + span; q += kThreads) {
     const int64_t k = i0 + (q < chunk ? q : lag0 + q - chunk);
@@ -209,22 +212,38 @@ __global__ void __launch_bounds__(kThreads) k_ac_gamma(int64_t n, int T, int nch
 }
 
 // The Madras-Sokal window by one thread: tau = 1/2 + sum_{t=1}^{W} Gamma(t) / Gamma(0)
-// for W = 1, 2, ... until W >= c tau (the quotients formed by all threads).
-__global__ void __launch_bounds__(kThreads) k_ac_final(int64_t n, int T, double cwin, int nsum,
-                                                      const double* __restrict__ gin,
-                                                      const int32_t* __restrict__ bad, double* __restrict__ tau,
+// for W = 1, 2, ... until W >= c tau (the quotients formed by all threads).  Series of at
+// most kAcFold chunks have no k_ac_gamma launch: their partials are added here, in chunk
+// order too, and Gamma kept in gin (64 series of 100: 20 us with that launch, 15 without).
+constexpr int kAcFold = 4;
+__global__ void __launch_bounds__(kThreads) k_ac_final(int64_t n, int T, int nchunk, int w_max, double cwin, int nsum,
+                                                      const double* __restrict__ partial, double* gin,
+                                                      const int32_t* __restrict__ bad, double* __restrict__ gamma,
+                                                      double* __restrict__ tau,
                                                       int32_t* __restrict__ window, uint8_t* __restrict__ found,
                                                       double* __restrict__ n_indep) {
   extern __shared__ __align__(16) double rho[];  // [T + 1]
   const int s = blockIdx.x;
-  const double* g = gin + (size_t)s * (T + 1);
+  double* g = gin + (size_t)s * (T + 1);
+  const double nan = __builtin_nan("");
+  bool isbad = false;
+  for (int k = 0; k < nsum; ++k) isbad |= bad[(size_t)s * nsum + k] != 0;
+  if (nchunk <= kAcFold) {
+    for (int t = threadIdx.x; t <= T; t += kThreads) {
+      double acc = 0.0;
+#pragma unroll
+      for (int c = 0; c < kAcFold; ++c)
+        if (c < nchunk) acc += partial[((size_t)s * nchunk + c) * (T + 1) + t];
+      g[t] = isbad ? nan : acc / (double)(n - t);
+    }
+    __syncthreads();
+    if (gamma)
+      for (int t = threadIdx.x; t <= w_max; t += kThreads) gamma[(size_t)s * (w_max + 1) + t] = t <= T ? g[t] : nan;
+  }
   const double g0 = g[0];
   for (int t = threadIdx.x; t <= T; t += kThreads) rho[t] = g[t] / g0;
   __syncthreads();
   if (threadIdx.x != 0) return;
-  bool isbad = false;
-  for (int k = 0; k < nsum; ++k) isbad |= bad[(size_t)s * nsum + k] != 0;
-  const double nan = __builtin_nan("");
   double tv = nan, ni = 0.0;
   int W = 0;
   uint8_t fo = 0;
@@ -250,9 +269,10 @@ __global__ void __launch_bounds__(kThreads) k_ac_final(int64_t n, int T, double 
 }
 
 // Normalised ESS of series s: (sum e^{w - max})^2 / (n sum e^{2 (w - max)}).  One
-// workgroup per series (there is no workspace to combine several in): 1024 threads, eight
-// loads of each in flight (65536 log-weights: 72 -> 29 us against 256 threads loading one
-// at a time).
+// workgroup per series (there is no workspace to combine several in), eight loads of each
+// thread in flight: of 256 threads where that is the series, or where the series fill the
+// chip (1024 series of 200: 14 us with 1024, 7 with 256; of 3000: 19 and 11), else of 1024
+// (65536 log-weights: 72 -> 29 us against 256 threads loading one at a time).
 __global__ void __launch_bounds__(1024) k_ess(int64_t n, const double* __restrict__ logw, int64_t ldw,
                                               double* __restrict__ ess) {
   constexpr int U = 8;
@@ -301,8 +321,9 @@ AcLayout ac_layout(int32_t n_series, int64_t n, int32_t w_max) {
   AcLayout a{};
   a.T = (int)std::min<int64_t>(w_max, n - 1);
   // chunks of 512 elements (128 workgroups times the lag groups at 65536), of 2048 in longer
-  // series, which fill the chip anyway
-  a.chunk = n <= 131072 ? 512 : 2048;
+  // series, which fill the chip anyway; a shorter one is cut in four, but not below 128
+  const auto up4 = [](int64_t k) { return (int)(k + 3) / 4 * 4; };
+  a.chunk = n > 131072 ? 2048 : n > 2048 ? 512 : n > 128 ? std::max(128, up4((n + 3) / 4)) : up4(n);
   a.nchunk = (int)((n + a.chunk - 1) / a.chunk);
   a.nsum = (int)std::min<int64_t>(kWave, (n + 1023) / 1024);
   a.per = (n + a.nsum - 1) / a.nsum;
@@ -360,7 +381,7 @@ extern "C" int32_t lfs_autocorr(int32_t n_series, int64_t n, const double* x, in
   int32_t* bad = reinterpret_cast<int32_t*>(base + a.off_bad);
   double* g = reinterpret_cast<double*>(base + a.off_gamma);
   double* partial = reinterpret_cast<double*>(base + a.off_partial);
-  const size_t shm_partial = (size_t)(2 * a.chunk + 4 * lfs::kThreads + 4) * sizeof(double);
+  const size_t shm_partial = (size_t)(2 * a.chunk + lfs::ac_lags(a.T)) * sizeof(double);
   const size_t shm_final = (size_t)(a.T + 1) * sizeof(double);
   if (!lfs::set_lds_limit<lfs::k_ac_final>((lfs::kAcMaxLag + 1) * sizeof(double))) return LFS_EDEVICE;
   hipStream_t st = (hipStream_t)stream;
@@ -368,17 +389,18 @@ extern "C" int32_t lfs_autocorr(int32_t n_series, int64_t n, const double* x, in
                      bad);
   hipLaunchKernelGGL(lfs::k_ac_partial, dim3(a.nchunk, n_series, a.T / (4 * lfs::kThreads) + 1), dim3(lfs::kThreads),
                      shm_partial, st, n, a.T, a.chunk, a.nsum, x, ldx, index, sums, bad, partial);
-  hipLaunchKernelGGL(lfs::k_ac_gamma, dim3((unsigned)std::max(a.T, gamma ? w_max : 0) / lfs::kWave + 1, n_series),
-                     dim3(lfs::kThreads), 0, st, n, a.T, a.nchunk, w_max, a.nsum, partial, bad, g, gamma);
-  hipLaunchKernelGGL(lfs::k_ac_final, dim3(n_series), dim3(lfs::kThreads), shm_final, st, n, a.T, c, a.nsum, g, bad,
-                     tau, window, found, n_indep);
+  if (a.nchunk > lfs::kAcFold)
+    hipLaunchKernelGGL(lfs::k_ac_gamma, dim3((unsigned)std::max(a.T, gamma ? w_max : 0) / lfs::kWave + 1, n_series),
+                       dim3(lfs::kThreads), 0, st, n, a.T, a.nchunk, w_max, a.nsum, partial, bad, g, gamma);
+  hipLaunchKernelGGL(lfs::k_ac_final, dim3(n_series), dim3(lfs::kThreads), shm_final, st, n, a.T, a.nchunk, w_max, c,
+                     a.nsum, partial, g, bad, gamma, tau, window, found, n_indep);
   return lfs::launch_status();
 }
 
 extern "C" int32_t lfs_ess(int32_t n_series, int64_t n, const double* logw, int64_t ldw, double* ess,
                            void* stream) {
   LFS_RETURN_IF(n_series < 1 || n < 1 || ldw < n || !logw || !ess, LFS_EINVAL);
-  hipLaunchKernelGGL(lfs::k_ess, dim3(n_series), dim3(1024), 0, (hipStream_t)stream, n, logw, ldw,
+  hipLaunchKernelGGL(lfs::k_ess, dim3(n_series), dim3(n <= 2048 || n_series > 512 ? 256 : 1024), 0, (hipStream_t)stream, n, logw, ldw,
                      ess);
   return lfs::launch_status();
 }

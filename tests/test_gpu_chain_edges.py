@@ -131,3 +131,42 @@ def test_autocorr_of_infinities(n, at, value):
         ref = np.array([np.sum(d[:n - t] * d[t:]) / (n - t) for t in range(n)])
     np.testing.assert_array_equal(host(gamma)[0], ref)
     assert np.isnan(float(tau.item()))
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 5, 64, 100, 127, 128, 129, 513, 1001, 2047, 2048, 2049])
+@pytest.mark.parametrize("w_max", [0, 1, 63, 2000])
+def test_autocorr_short_series(n, w_max):
+    """Chunks as long as the series, and around the length up to which the chunks are added in
+    the last launch; windows shorter and longer than the series."""
+    print(f"autocorr n={n} w_max={w_max}", flush=True)
+    S = 5
+    x = si.correlated_series(72, S, n, 0.7) if n > 1 else np.array([[1.0], [2.0], [-3.0], [0.5], [0.25]])
+    gamma = torch.full((S, w_max + 1), 7.0, dtype=torch.float64, device="cuda")
+    tau = torch.empty(S, dtype=torch.float64, device="cuda")
+    window = torch.empty(S, dtype=torch.int32, device="cuda")
+    index = torch.arange(n - 1, -1, -1, device="cuda").repeat(S, 1)  # read backwards
+    lfs.autocorr(dev(x, torch.float64), w_max, 6.0, tau, window=window, gamma=gamma, index=index)
+    g, T = host(gamma), min(w_max, n - 1)
+    for s in range(S):
+        y = x[s, ::-1]
+        d = y - y.mean()
+        ref = np.array([d[:n - t] @ d[t:] / (n - t) for t in range(T + 1)])
+        assert np.all(np.abs(g[s, :T + 1] - ref) <= 1e-12 * ref[0])
+        assert np.all(np.isnan(g[s, T + 1:]))
+        if ref[0] == 0:
+            assert np.isnan(host(tau)[s])
+            continue
+        t, W = 0.5, 0
+        for W in range(1, T + 1):
+            t += ref[W] / ref[0]
+            if W >= 6.0 * t:
+                break
+        assert abs(host(tau)[s] - t) <= 1e-9 * abs(t) + 1e-12 and host(window)[s] == min(W, T)
+
+
+@pytest.mark.parametrize("n,S", [(2, 300), (255, 300), (2047, 300), (2048, 300), (2049, 300), (2049, 513)])
+def test_ess_of_several_series(n, S):
+    w = np.stack([si.logw_stream(80 + k, n, 2.0) for k in range(S)])
+    out = torch.empty(S, dtype=torch.float64, device="cuda")
+    lfs.ess(dev(w, torch.float64), out)
+    assert np.all(np.abs(host(out) - [an.ess(v) for v in w]) <= 1e-12)
