@@ -299,20 +299,36 @@ __global__ void __launch_bounds__(256) kg_wgrad(NetDev d, WgArgs A, const float*
   }
 }
 
-// g_params of the group's layers: the chunks' partials summed in order (batch-norm
-// gammas and betas, written elsewhere, are left alone).
-__global__ void __launch_bounds__(256) kg_reduce(NetDev d, int n, int chunks, const double* __restrict__ partial,
-                                                 float* __restrict__ out) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
+// g_params of the group's layers: the chunks' partials summed in order, or, of SLICES waves
+// each a share of the chunks in order, then the shares (batch-norm gammas and betas, written
+// elsewhere, are left alone).  256 chunks of a few parameters: 10 us by one thread, 5 so.
+constexpr int kRedChunks = 64;
+template <int SLICES>
+__global__ void __launch_bounds__(SLICES > 1 ? 64 * SLICES : 256) kg_reduce(NetDev d, int n, int chunks,
+                                                                            const double* __restrict__ partial,
+                                                                            float* __restrict__ out) {
+  __shared__ double sh[SLICES][64];
+  const int col = threadIdx.x & 63, sl = SLICES > 1 ? threadIdx.x >> 6 : 0;
+  const int p = SLICES > 1 ? blockIdx.x * 64 + col : blockIdx.x * blockDim.x + threadIdx.x;
+  const int c0 = chunks * sl / SLICES, c1 = chunks * (sl + 1) / SLICES;
+  double acc = 0.0;
+  if (p < n) {
+#pragma unroll 8
+    for (int c = c0; c < c1; ++c) acc += partial[(size_t)c * n + p];
+  }
+  if constexpr (SLICES > 1) {
+    sh[sl][col] = acc;
+    __syncthreads();
+    if (sl > 0) return;
+#pragma unroll
+    for (int k = 1; k < SLICES; ++k) acc += sh[k][col];
+  }
   if (p >= n) return;
   if (d.bn) {
     const int r = p % d.P_layer;
     for (int i = 0; i + 1 < d.n_conv; ++i)
       if (r >= d.offg[i] && r < d.offg[i] + 2 * d.cout[i]) return;
   }
-  double acc = 0.0;
-#pragma unroll 8
-  for (int c = 0; c < chunks; ++c) acc += partial[(size_t)c * n + p];
   out[p] = (float)acc;
 }
 

@@ -41,6 +41,7 @@ struct WsArgs {
   int jobs, waves;        // workgroups per (layer, chunk); waves with columns, CHAIN: one more for db
   int planes;             // planes of a sample's block of the store
   int l0, layers, B, chunks, per;  // per: samples of a chunk
+  int parts;              // or, above 1, chunks of one part of a sample's leading axis each
   Magic dLp;              // L + 2 (K / 2)
   int lds;
 };
@@ -107,7 +108,8 @@ __global__ void __launch_bounds__(1024) kg_wgrad_slab(NetDev d, WsArgs A, const 
 #pragma unroll
       for (int k = 0; k < 16; ++k) err[q][k] = 0.f;
   }
-  const int b0 = blockIdx.y * A.per, b1 = min(b0 + A.per, A.B);
+  const int b0 = blockIdx.y / A.parts * A.per, b1 = min(b0 + A.per, A.B), part = blockIdx.y % A.parts;
+  const int zlo = L * part / A.parts, zhi = L * (part + 1) / A.parts;
   for (int b = b0; b < b1; ++b) {
     const float* st = store + ((size_t)ll * A.B + b) * A.planes * V * 4;
     const float* sx = saved + ((size_t)layer * A.B + b) * V;
@@ -116,8 +118,8 @@ __global__ void __launch_bounds__(1024) kg_wgrad_slab(NetDev d, WsArgs A, const 
       for (int q = 0; q < CT; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
       b32 = 0.f;
     }
-    for (int z0 = 0; z0 < L; z0 += C.slices) {
-      const int ns = min(C.slices, L - z0) * area, n4 = (ns + 3) & ~3;
+    for (int z0 = zlo; z0 < zhi; z0 += C.slices) {
+      const int ns = min(C.slices, zhi - z0) * area, n4 = (ns + 3) & ~3;
       __syncthreads();  // the last slab's readers
       for (int n = threadIdx.x; n < n4; n += blockDim.x)
         for (int p = 0; p < gp; ++p) {
@@ -126,7 +128,7 @@ __global__ void __launch_bounds__(1024) kg_wgrad_slab(NetDev d, WsArgs A, const 
             v = *reinterpret_cast<const f32x4*>(st + ((size_t)(C.gplane + 4 * rt + p) * V + z0 * area + n) * 4);
           *reinterpret_cast<f32x4*>(gl + p * C.gs + 4 * n) = v;
         }
-      const int np = (min(C.slices, L - z0) + 2 * h) * parea;
+      const int np = (min(C.slices, zhi - z0) + 2 * h) * parea;
       for (int e = threadIdx.x; e < np; e += blockDim.x) {
         // padded coordinates to a site, fastest axis last
         int c[DIM], q = e;
@@ -263,6 +265,10 @@ WsPlan wgrad_slab_plan(const NetDev& d, int B, int layers, int planes) {
   const int n = d.n_conv, L = d.lat.L, h = d.K / 2, Lp = L + 2 * h;
   const int64_t area = d.dim == 2 ? L : (int64_t)L * L, parea = d.dim == 2 ? Lp : (int64_t)Lp * Lp;
   auto stride = [](int64_t floats) { return (floats + 47) / 64 * 64 + 16; };  // 16 mod 64: planes in other banks
+  auto bytes = [&](const WsConv& c, int i, int64_t s) {
+    const int64_t up = i == 0 ? 1 : c.cw / 4, us = i == 0 ? stride((s + 2 * h) * parea) : stride(4 * (s + 2 * h) * parea);
+    return 4 * ((s * area + 3) / 4 * 4 + std::min(4, c.gplanes) * stride(4 * (s * area + 3)) + up * us);
+  };
   int most = 0;
   for (int i = 0; i < n; ++i) {
     WsConv& c = a.c[i];
@@ -273,27 +279,28 @@ WsPlan wgrad_slab_plan(const NetDev& d, int B, int layers, int planes) {
     c.uplane = i > 0 ? d.hplane[i - 1] : 0;
     c.uplanes = cdiv(d.cin[i], 4);
     c.cw = i == 0 ? 1 : 4 * std::min(4, c.uplanes);
-    // the thickest slab that leaves room for two workgroups per CU, else the thinnest, of
-    // fewer channels where that does not fit
-    auto bytes = [&](int64_t s) {
-      const int64_t up = i == 0 ? 1 : c.cw / 4, us = i == 0 ? stride((s + 2 * h) * parea) : stride(4 * (s + 2 * h) * parea);
-      return 4 * ((s * area + 3) / 4 * 4 + std::min(4, c.gplanes) * stride(4 * (s * area + 3)) + up * us);
-    };
-    while (i > 0 && c.cw > 4 && bytes(1) > kLdsMax) c.cw -= 4;
-    if (bytes(1) > kLdsMax) return WsPlan{};
-    int s = 1;
-    while (s < L && bytes(s + 1) <= 78 * 1024) ++s;
-    s = cdiv(L, cdiv(L, s));
-    c.slices = s;
-    c.gs = (int)stride(4 * (s * area + 3));
-    c.us = (int)(i == 0 ? stride((s + 2 * h) * parea) : stride(4 * (s + 2 * h) * parea));
-    a.lds = std::max(a.lds, (int)bytes(s));
+    // fewer channels where even a slab of one slice does not fit
+    while (i > 0 && c.cw > 4 && bytes(c, i, 1) > kLdsMax) c.cw -= 4;
+    if (bytes(c, i, 1) > kLdsMax) return WsPlan{};
     c.dcw = magic(c.cw);
     c.ncb = i == 0 ? 1 : cdiv(c.uplanes * 4, c.cw);
     c.tiles = cdiv(d.T * c.cw, 16);
     most = std::max(most, c.tiles);
   }
   a.waves = std::min(15, cdiv(most, kWsCols));
+  // the thickest slab, or one slice, that leaves room for two workgroups per CU, for more where
+  // they have few waves: 16 waves a CU, or eight workgroups
+  const int64_t room = d.mode == kSeq ? 78 * 1024 : std::clamp(156 * 1024 * a.waves / 16, 19 * 1024, 78 * 1024);
+  for (int i = 0; i < n; ++i) {
+    WsConv& c = a.c[i];
+    int s = 1;
+    while (s < L && bytes(c, i, s + 1) <= room) ++s;
+    s = cdiv(L, cdiv(L, s));
+    c.slices = s;
+    c.gs = (int)stride(4 * (s * area + 3));
+    c.us = (int)(i == 0 ? stride((s + 2 * h) * parea) : stride(4 * (s + 2 * h) * parea));
+    a.lds = std::max(a.lds, (int)bytes(c, i, s));
+  }
   int job = 0;
   for (int i = 0; i < n; ++i) {
     WsConv& c = a.c[i];
@@ -306,9 +313,14 @@ WsPlan wgrad_slab_plan(const NetDev& d, int B, int layers, int planes) {
   a.layers = layers;
   a.planes = planes;
   a.B = B;
-  const int64_t want = std::max<int64_t>(1, std::min<int64_t>(B, 2048 / ((int64_t)job * layers)));
-  a.per = cdiv(B, (int)want);
-  a.chunks = cdiv(B, a.per);
+  // about 2048 workgroups; where the samples are fewer, each is cut along its leading axis (not
+  // in Seq, whose sums over a sample are FP32).  Four samples of 256 x 256, hidden [1], kernel
+  // 1, 2 layers: 5537 us with whole samples, 87 with parts of them; three of 32^3, hidden
+  // [2, 4]: 2790 and 207.
+  const int64_t want = std::max<int64_t>(1, 2048 / ((int64_t)job * layers));
+  a.per = cdiv(B, (int)std::min<int64_t>(B, want));
+  a.parts = d.mode == kSeq || want <= B ? 1 : std::min(L, cdiv((int)want, B));
+  a.chunks = cdiv(B, a.per) * a.parts;
   p.partial_bytes = sizeof(double) * (size_t)a.chunks * layers * d.P_layer;
   return p;
 }
@@ -335,8 +347,12 @@ int32_t run_wgrad(const NetDev& d, int B, int l0, int layers, int planes, const 
     hipLaunchKernelGGL((kg_wgrad<DIM, MODE == kBf16>), dim3((unsigned)(p.a.jobs * layers), (unsigned)chunks),
                        dim3(256), 0, st, d, p.a, store, saved, partial);
   }
-  hipLaunchKernelGGL(kg_reduce, dim3(blocks(n)), dim3(256), 0, st, d, n, chunks, partial,
-                     g_params + (size_t)l0 * d.P_layer);
+  if (chunks > kRedChunks)
+    hipLaunchKernelGGL(kg_reduce<16>, dim3(blocks(n, 64)), dim3(1024), 0, st, d, n, chunks, partial,
+                       g_params + (size_t)l0 * d.P_layer);
+  else
+    hipLaunchKernelGGL(kg_reduce<1>, dim3(blocks(n)), dim3(256), 0, st, d, n, chunks, partial,
+                       g_params + (size_t)l0 * d.P_layer);
   return LFS_OK;
 }
 

@@ -126,3 +126,17 @@ def test_log_det_keeps_every_bit_of_s(dim, L, N, C, hs, B, precision):
     exact = N * (V // 2) * float(b)
     bound = (V // 2 + N) * 2.0 ** -53 * abs(exact)
     assert np.all(np.abs(host(out["logdet"]) - exact) <= bound)
+
+
+@pytest.mark.parametrize("case", [
+    (2, 10, 2, 3, (6, 5), 100),       # samples cut in uneven parts
+    (2, 6, 1, 3, (3,), 1),            # a slice a part
+    (2, 34, 1, 5, (9,), 1),           # parts thinner than a slab, more than 64 chunks
+    (3, 8, 1, 1, (2,), 70),
+    (2, 4, 2, 3, (4, 4), 1100),       # more samples than chunks
+])
+def test_weight_gradient_parts(case):
+    print(f"weight gradients of parts of samples {case}", flush=True)
+    desc, params, z, fs = _case(*case, lfs.LFS_PLAIN_FP32)
+    out, _ = _check_forward(desc, params, z, fs, lfs.LFS_PLAIN_FP32)
+    _check_backward(desc, params, z, fs, out, lfs.LFS_PLAIN_FP32)
