@@ -35,8 +35,8 @@ __device__ __forceinline__ void put_chunk(uint64_t path, int lane, bool valid, i
 // Chain c reads proposals [offsets[c], offsets[c+1]) (rectangular calls pass
 // offsets == NULL and use [c * n_prop, (c+1) * n_prop)); its state lives at
 // state[state_index[c]] (or state[c]).
-// Positions are unsigned here and below: chunks are looked up past the end, which for the
-// longest chain (2^31 - 1 proposals) is past the largest int.
+// Positions are unsigned: the chunk after the last one is looked up, which for the longest
+// chain (2^31 - 1 proposals) is past the largest int.
 __global__ void __launch_bounds__(64) k_mh_chain(int n_prop_rect, const int64_t* __restrict__ offsets,
                                                  const double* __restrict__ logw,
                                                  const double* __restrict__ log_u,
@@ -130,7 +130,7 @@ __global__ void __launch_bounds__(256) k_mh_paths(unsigned n_prop, const double*
 // one, which as per-lane 64-bit arithmetic costs as much as the decisions (one wave doing
 // both: 380 us).
 constexpr int kWalkChunks = 16;  // chunks per group
-__global__ void __launch_bounds__(256) k_mh_walk(unsigned n_prop, const double* __restrict__ logw,
+__global__ void __launch_bounds__(256) k_mh_walk(int n_prop, const double* __restrict__ logw,
                                                  const double* __restrict__ log_u, lfs_chain_state* __restrict__ states,
                                                  int64_t* cur_idx, uint8_t* __restrict__ accepted) {
   constexpr int GP = kWalkChunks * kWave;
@@ -141,15 +141,14 @@ __global__ void __launch_bounds__(256) k_mh_walk(unsigned n_prop, const double* 
   const size_t base = (size_t)c * n_prop;
   lfs_chain_state st = states[c];
   const int64_t seen0 = st.n_seen;
-  const unsigned groups = (n_prop + GP - 1) / GP;
-  auto fetch = [&](unsigned g, int first, int waves) {
+  const int groups = (n_prop - 1) / GP + 1;
+  auto fetch = [&](int g, int first, int waves) {
     constexpr int MX = (kWalkChunks + 2) / 3;
     double w[MX], u[MX];
     uint64_t p[MX];
 #pragma unroll
     for (int i = 0; i < MX; ++i) {
-      const int ch = first + i * waves;
-      const unsigned k = g * GP + ch * kWave + lane;
+      const int ch = first + i * waves, k = g * GP + min(ch, kWalkChunks - 1) * kWave + lane;
       const bool ok = ch < kWalkChunks && k < n_prop;
       w[i] = ok ? logw[base + k] : 0.0;
       u[i] = ok ? log_u[base + k] : HUGE_VAL;  // lanes past the end never accept
@@ -163,14 +162,14 @@ __global__ void __launch_bounds__(256) k_mh_walk(unsigned n_prop, const double* 
   };
   fetch(0, wv, 4);
   __syncthreads();
-  for (unsigned g = 0; g <= groups; ++g) {
+  for (int g = 0; g <= groups; ++g) {
     if (wv == 0) {
       if (g < groups) {
         const double *w = sw[g & 1], *u = su[g & 1];
         const uint64_t* p = sp[g & 1];
         double wl = w[lane], ul = u[lane];
         uint64_t pl = p[lane];
-        const int chunks = (int)min((unsigned)kWalkChunks, (n_prop - g * GP + kWave - 1) / kWave);
+        const int chunks = min(kWalkChunks, (int)(((unsigned)(n_prop - g * GP) + kWave - 1) / kWave));
         for (int i = 0; i < chunks; ++i) {
           const int nx = min(i + 1, kWalkChunks - 1) * kWave + lane;
           const double wn = w[nx], un = u[nx];
@@ -195,7 +194,7 @@ __global__ void __launch_bounds__(256) k_mh_walk(unsigned n_prop, const double* 
     } else {
       if (g > 0) {
         for (int i = wv - 1; i < kWalkChunks; i += 3) {
-          const unsigned kc = (g - 1) * GP + i * kWave, k = kc + lane;
+          const int kc = (g - 1) * GP + i * kWave, k = kc + lane;
           if (kc < n_prop)
             put_chunk(spath[(g - 1) & 1][i], lane, k < n_prop, seen0 + kc, sbefore[(g - 1) & 1][i], cur_idx + base + k,
                       accepted ? accepted + base + k : nullptr);
@@ -333,7 +332,7 @@ extern "C" int32_t lfs_mh_chain(int32_t n_chains, int32_t n_prop, const double* 
   }
   const unsigned chunks = ((unsigned)n_prop + lfs::kWave - 1) / lfs::kWave;
   hipLaunchKernelGGL(lfs::k_mh_paths, dim3((chunks + 3) / 4, n_chains), dim3(256), 0, st, (unsigned)n_prop, logw, log_u, cur_idx);
-  hipLaunchKernelGGL(lfs::k_mh_walk, dim3(n_chains), dim3(256), 0, st, (unsigned)n_prop, logw, log_u, state, cur_idx,
+  hipLaunchKernelGGL(lfs::k_mh_walk, dim3(n_chains), dim3(256), 0, st, n_prop, logw, log_u, state, cur_idx,
                      accepted);
   return lfs::launch_status();
 }
