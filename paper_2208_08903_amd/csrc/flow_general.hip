@@ -9,20 +9,20 @@
 //   staged    larger samples: one launch per convolution over the whole batch,
 //             activations in HBM (kg_staged)
 //
-// Which of the two runs depends on the shape alone, never on the batch, so a
-// sample's result does not depend on the batch it is in.  Either backward leaves
-// the hidden activations and the gradients of every convolution's output in HBM
-// for a group of layers, and one launch forms all their weight gradients
-// (kg_wgrad).
+// Which of the two runs depends, in BF16, on the shape alone, and in FP32 both add in
+// the same order, so a sample's result does not depend on the batch it is in.  Either
+// backward leaves the hidden activations and the gradients of every convolution's output
+// in HBM for a group of layers, and one launch forms all their weight gradients
+// (kg_wgrad_slab, kg_wgrad).
 //
 // Small samples are bound by latency: 64 samples of 64 sites keep 64 of the 256 CUs
 // busy with a chain of N n_conv dependent convolutions.  What counts is the time from
 // one barrier to the next, hence one launch for all layers instead of one per
 // convolution, fragments fetched a layer ahead, neighbours from a table and gathers
 // without branches.  Training step of the 2D L = 8 flow with hidden [16, 16, 16], 16
-// layers, batch 64, FP32: 3400 us with a launch per convolution and direct sums, 440 so
-// (forward 121, backward 246, weight gradients 55).  3D L = 12, hidden 16, 12 layers,
-// batch 50, FP32, where a sample does not fit: 47.1 -> 3.2 ms (a hidden convolution of
+// layers, batch 64, FP32: 3400 us with a launch per convolution and direct sums, 470 so
+// (forward 121, backward 246, weight gradients 85).  3D L = 12, hidden 16, 12 layers,
+// batch 50, FP32, where a sample does not fit: 47.1 -> 2.57 ms (a hidden convolution of
 // 86400 sites 25 us, its data gradient 24 us; direct sums: 294 and 257).
 #include "general_wgrad.hpp"
 
@@ -42,7 +42,8 @@ struct ResLds {
   int total;
 };
 
-ResLds res_lds(const NetDev& d, bool bwd) {
+// of `waves` waves, with the fragments in LDS where they fit and lf asks for it.
+ResLds res_lds(const NetDev& d, bool bwd, int waves = kResWaves, bool lf = true) {
   ResLds r{};
   const int V = d.lat.V;
   r.ps = lds_plane_stride(V);
@@ -64,14 +65,14 @@ ResLds res_lds(const NetDev& d, bool bwd) {
     const int a = take(4ll * r.ps * q), b = d.n_conv > 2 ? take(4ll * r.ps * q) : a;
     for (int i = 0; i + 1 < d.n_conv; ++i) r.slot[i] = i & 1 ? b : a;
   }
-  r.red = take(1024ll * kResWaves);
+  r.red = take(waves == kResWaves ? 1024ll * kResWaves : 0);
   r.nbr = take(nbr_bytes(d.T, V));
   if (!bwd) r.ts = take(8ll * ld_tiles(V));
   // fragments: two layers' in the forward, one layer's forward and transposed ones in the
   // backward
   const int64_t fr = off;
   const int64_t f0 = d.frags_fwd * 1024ll, f1 = (bwd ? d.frags_all - d.frags_fwd : d.frags_fwd) * 1024ll;
-  r.lf = fr + f0 + f1 <= (int64_t)kLdsMax;
+  r.lf = lf && fr + f0 + f1 <= (int64_t)kLdsMax;
   if (r.lf) {
     r.frags[0] = take(f0);
     r.frags[1] = take(f1);
@@ -514,12 +515,49 @@ __global__ void __launch_bounds__(256) kg_staged(NetDev d, StagedArgs A, const u
 
 // ---- host ------------------------------------------------------------------------
 
-// Whether a sample's forward (backward) state fits the LDS.
-// (the neighbour table holds 16-bit sites)
-bool resident(const NetDev& d, bool bwd) { return d.lat.V < 65536 && (size_t)res_lds(d, bwd).total <= kLdsMax; }
+// Whether B samples are run by the resident kernels: a sample's forward (backward) state has
+// to fit the LDS (the neighbour table holds 16-bit sites).  In FP32, where the staged kernels
+// give the same bits, they take over where most CUs would be idle and a wave would have four
+// tiles or more of every convolution: one sample of 24 x 24, hidden [16, 16, 16], 2 layers, 81
+// us forward and 179 backward resident, 56 and 116 staged; 64 of them 79 and 261 or 78 and
+// 242; of 20 x 20 the two are as fast.
+bool resident(const NetDev& d, int B, bool bwd) {
+  if (d.mode != kBf16 && d.lat.V >= 512 && B <= 64) return false;
+  return d.lat.V < 65536 && (size_t)res_lds(d, bwd).total <= kLdsMax;
+}
 
 size_t frag_bytes(const NetDev& d, bool bwd) {
   return (size_t)d.N * (bwd ? d.frags_all : d.frags_fwd) * 1024;
+}
+
+// Workgroups of a resident launch.  A sample per CU or less: eight waves each, whose latency is
+// what counts.  More: up to 16 waves of a CU, in workgroups of the fewer waves the more
+// samples there are, but one for 16 sites, two for 64 and four above at least; and
+// fragments read from the L2 where so many workgroups have no room for them in LDS.  Forward of
+// 8 layers, hidden 8, FP32, 4096 samples of 4 x 4: 422 us with eight waves and one workgroup a
+// CU, 64 with one wave and 16; of 6 x 6: 438, 138 (two and eight; 125 with one and 16);
+// hidden 16, of 12 x 12: 895, 551 (four and four).  The sums' orders do not depend on it.
+struct ResGrid {
+  ResLds S;
+  int waves, blocks;
+};
+ResGrid res_grid(const NetDev& d, int B, bool bwd) {
+  const int cus = num_cus(), per = cdiv(B, cus), V = d.lat.V;
+  if (per == 1) return ResGrid{res_lds(d, bwd), kResWaves, B};
+  int units = 1;
+  for (int i = 0; i < d.n_conv; ++i)
+    units = std::max(units, cdiv(V, 16) * std::max(d.f[i].nct, bwd ? d.t[i].nct : 0));
+  const int lo = V <= 16 ? 1 : V <= 64 ? 2 : 4, hi = units > 4 ? kResWaves : 4;
+  int waves = hi;
+  while (waves > lo && waves * per > 16) waves /= 2;
+  const int want = std::min(per, 16 / waves);
+  auto fit = [](const ResLds& S) { return std::max(1, (int)(160 * 1024 / S.total)); };
+  ResLds S = res_lds(d, bwd, waves);
+  if (S.lf && fit(S) < want) {
+    const ResLds L2 = res_lds(d, bwd, waves, false);
+    if (fit(L2) > fit(S)) S = L2;
+  }
+  return ResGrid{S, waves, std::min(B, cus * std::min(want, fit(S)))};
 }
 
 struct BwdWs {
@@ -659,8 +697,8 @@ int32_t forward_impl(const FlowGeom& g, const float* params, int B, const float*
   const NetDev d = make_net(g);
   const size_t fb = frag_bytes(d, false), BV = (size_t)B * g.V;
   // the static scratch may be smaller than general_ws_bytes
-  if (resident(d, false)) {
-    const ResLds S = res_lds(d, false);
+  if (resident(d, B, false)) {
+    const ResGrid R = res_grid(d, B, false);
     const size_t layer = (size_t)d.frags_fwd * 1024, cb = align_up(sizeof(double) * B * ld_tiles(d.lat.V));
     const bool whole = ws_bytes >= fb;
     const int group = whole ? d.N : ws_bytes < cb ? 0 : (int)std::min<size_t>(d.N, (ws_bytes - cb) / layer);
@@ -669,10 +707,10 @@ int32_t forward_impl(const FlowGeom& g, const float* params, int B, const float*
     for (int l0 = 0; group > 0 && l0 < d.N; l0 += group) {
       const int l1 = std::min(l0 + group, d.N);
       prep<MODE>(d, params + (size_t)l0 * d.P_layer, l1 - l0, 0, d.frags_fwd, frags, st);
-      LFS_TRY(with_lf(S.lf, [&](auto lf) {
+      LFS_TRY(with_lf(R.S.lf, [&](auto lf) {
         constexpr auto k = kg_forward<DIM, MODE, decltype(lf)::value>;
         if (!set_lds_limit<k>(kLdsMax)) return (int32_t)LFS_EDEVICE;
-        hipLaunchKernelGGL(k, dim3((unsigned)std::min(B, num_cus())), dim3(64 * kResWaves), S.total, st, d, S, frags,
+        hipLaunchKernelGGL(k, dim3((unsigned)R.blocks), dim3(64 * R.waves), R.S.total, st, d, R.S, frags,
                            l0, l1, B, l0 > 0 ? phi : z, phi, saved, logq, logdet, carry);
         return launch_status();
       }));
@@ -713,19 +751,19 @@ int32_t backward_impl(const FlowGeom& g, const float* params, int B, const float
   const BwdWs w = carve_bwd(d, B, ws, &total);
   prep<MODE>(d, params, d.N, 0, d.frags_all, w.frags, st);
   const FragSrc src{w.frags, d.frags_all, frag_bytes(d, true), params};
-  const bool res = resident(d, true);
+  const bool res = resident(d, B, true);
   const float* gy = g_phi;
   float* bufs[2] = {w.gA, w.gB};
   int which = 0;
   for (int l1 = d.N; l1 > 0;) {
     const int l0 = l1 > group ? l1 - group : 0;
     if (res) {
-      const ResLds S = res_lds(d, true);
+      const ResGrid R = res_grid(d, B, true);
       float* gx = bufs[which];
-      LFS_TRY(with_lf(S.lf, [&](auto lf) {
+      LFS_TRY(with_lf(R.S.lf, [&](auto lf) {
         constexpr auto k = kg_backward<DIM, MODE, decltype(lf)::value>;
         if (!set_lds_limit<k>(kLdsMax)) return (int32_t)LFS_EDEVICE;
-        hipLaunchKernelGGL(k, dim3((unsigned)std::min(B, num_cus())), dim3(64 * kResWaves), S.total, st, d, S, w.frags,
+        hipLaunchKernelGGL(k, dim3((unsigned)R.blocks), dim3(64 * R.waves), R.S.total, st, d, R.S, w.frags,
                            B, l0, l1, saved, gy, (float)(-g_logq), g_logq_vec, gx, w.store);
         return (int32_t)LFS_OK;
       }));
@@ -795,7 +833,7 @@ int32_t dispatch(const FlowGeom& g, F&& f) {
 size_t general_ws_bytes(const FlowGeom& g, int B, int for_backward) {
   const NetDev d = make_net(g);
   if (!for_backward)
-    return kWsAlign + frag_bytes(d, false) + (resident(d, false) ? 0 : staged_ws(d, B, nullptr).bytes);
+    return kWsAlign + frag_bytes(d, false) + (resident(d, B, false) ? 0 : staged_ws(d, B, nullptr).bytes);
   size_t total;
   carve_bwd(d, B, nullptr, &total);
   return kWsAlign + total;

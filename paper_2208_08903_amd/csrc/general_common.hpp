@@ -36,7 +36,8 @@ __global__ void __launch_bounds__(256) kg_prep(NetDev d, const float* __restrict
   frags[gid] = frag_entry<MODE>(d, params + (size_t)layer * d.P_layer, i, tr, ct, r - ct * c.per_ct() - 1, lane);
 }
 
-// Waves of a resident workgroup (small lattices split the K blocks of a unit over them).
+// Waves of a resident workgroup at most (of so many, small lattices split the K blocks of a
+// unit over them).
 constexpr int kResWaves = 8;
 
 // Copies n fragments to LDS without passing through registers: 1 KB per instruction, lane
@@ -67,18 +68,23 @@ __device__ __forceinline__ void conv_pass(int tiles, const ConvDir& cd, const u3
   constexpr bool TREE = MODE == kTree;
   int ks = 1;
   if constexpr (TREE)
-    ks = units < 4 && 4 * units <= nw ? 4 : 1;
+    ks = units <= 2 && nw == kResWaves ? 4 : 1;
   else if constexpr (MODE == kBf16)
-    while (ks < 4 && 2 * ks * units <= 8 && 2 * ks <= c.nb) ks *= 2;
+    while (ks < 4 && 2 * ks * units <= kResWaves && 2 * ks <= c.nb) ks *= 2;
   auto bias = [&](int ct) { return __builtin_bit_cast(f32x4, W.at(ct, -1)); };
-  if (ks == 1) {
+  if (ks == 1 || nw < kResWaves) {  // (of fewer waves one makes all shares, in the same order)
     for (int u = w; u < units; u += nw) {
       const int tile = fdiv(u, c.dnct), ct = u - tile * nct;
       const auto rd = reader(tile);
-      if constexpr (TREE)
+      if constexpr (TREE) {
         epi(tile, ct, TR ? tree<false>(rd, c, W, ct, j, 0) : tree<false>(rd, c, W, ct, j, 0) + bias(ct));
-      else
-        epi(tile, ct, chain<MODE, TR>(rd, c, W, ct, j, 0, c.nb, bias(ct)));
+      } else {
+        f32x4 acc = chain<MODE, TR>(rd, c, W, ct, j, 0, c.nb / ks, bias(ct));
+        if constexpr (MODE == kBf16)
+          for (int p = 1; p < ks; ++p)
+            acc += chain<MODE, TR>(rd, c, W, ct, j, c.nb * p / ks, c.nb * (p + 1) / ks, f32x4{0.f, 0.f, 0.f, 0.f});
+        epi(tile, ct, acc);
+      }
     }
     return;
   }
