@@ -171,9 +171,7 @@ struct BnConvArgs {
 
 template <int DIM, int MODE, bool LF, Kind KIND>
 __global__ void __launch_bounds__(64 * kResWaves) kb_conv(NetDev d, BnLds S, BnConvArgs A, const u32x4* frags) {
-  using R = std::conditional_t<MODE == kBf16, double, float>;
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ R sh[16];
   const Lat& lat = d.lat;
   const ConvDir& c = d.f[A.i];
   const int V = lat.V, half = V / 2, lane = threadIdx.x & 63, j = lane >> 4, m = lane & 15, w = fused::wave_id(),
@@ -284,7 +282,6 @@ __global__ void __launch_bounds__(64 * kResWaves) kb_conv(NetDev d, BnLds S, BnC
         }
       }
     } else {
-      R ssum = 0;
       const size_t o = (size_t)b * V;
       const int apar = A.fpar ^ 1;
       const float gld = KIND == Kind::Affine && A.gld_vec ? (float)(-A.gld_vec[b]) : A.gld;
@@ -297,7 +294,7 @@ __global__ void __launch_bounds__(64 * kResWaves) kb_conv(NetDev d, BnLds S, BnC
         if constexpr (KIND == Kind::Couple) {
           const float s = d.final_tanh ? tanhf(v[0]) : v[0];
           const float xn = xb[n] * expf(s) + v[1], xf = xb[nf];
-          ssum += (R)s;
+          out[a] = s;
           A.xout[o + n] = xn;
           if (A.xout != A.x) A.xout[o + nf] = xf;
           if (A.xout2) A.xout2[o + n] = xn, A.xout2[o + nf] = xf;
@@ -313,8 +310,11 @@ __global__ void __launch_bounds__(64 * kResWaves) kb_conv(NetDev d, BnLds S, BnC
         }
       });
       if constexpr (KIND == Kind::Couple) {
-        ssum = block_sum(ssum, sh);
-        if (threadIdx.x == 0) A.ld[b] = (double)ssum;
+        lds_barrier();
+        if (w == 0) {
+          const double ld = sum_of_256<double>(half, [&](int a) { return (double)out[a]; });
+          if (lane == 0) A.ld[b] = ld;
+        }
       }
     }
     lds_barrier();
@@ -510,6 +510,23 @@ struct BnWs {
   float *store, *gA, *gB;
   double* partial;
 };
+// Workgroups of a launch.  Up to one sample per CU: eight waves each.  More samples: two such
+// workgroups per CU; 16 and more samples per CU of a narrow network: four of four waves (4096
+// samples of 8 x 8, hidden [8, 8], 4 layers: 533 us forward with one workgroup per CU, 390
+// with two, 381 with four; hidden [32, 32], whose merges are longer, 2048 samples: 601, 536
+// and 1122).
+struct BnGrid {
+  int blocks, waves;
+};
+BnGrid bn_grid(const NetDev& d, int B) {
+  const int cus = num_cus();
+  int widest = 0;
+  for (int i = 0; i + 1 < d.n_conv; ++i) widest = std::max(widest, d.cout[i]);
+  if (B <= cus) return BnGrid{B, kResWaves};
+  if (B < 16 * cus || widest > 8) return BnGrid{std::min(B, 2 * cus), kResWaves};
+  return BnGrid{4 * cus, kResWaves / 2};
+}
+
 constexpr int kBnPlanes(int hp, bool bwd) { return bwd ? 3 * hp + 1 : hp; }
 
 BnWs bn_carve(const NetDev& d, int B, bool bwd, char* base, size_t* total) {
@@ -525,7 +542,7 @@ BnWs bn_carve(const NetDev& d, int B, bool bwd, char* base, size_t* total) {
   w.frags = (u32x4*)take((size_t)d.N * (bwd ? d.frags_all : d.frags_fwd) * 1024);
   w.logr = (double*)take(sizeof(double) * B);
   w.ld = (double*)take(bwd ? 0 : sizeof(double) * B * d.N);
-  for (auto& p : w.part) p = (double*)take(sizeof(double) * 2 * kMaxC * (size_t)std::min(B, num_cus()));
+  for (auto& p : w.part) p = (double*)take(sizeof(double) * 2 * kMaxC * (size_t)bn_grid(d, B).blocks);
   w.mr = (double*)take(sizeof(double) * 2 * kMaxC * LFS_MAX_HIDDEN);
   w.store = (float*)take((size_t)group * BV * planes * 16);
   if (bwd) {
@@ -537,8 +554,7 @@ BnWs bn_carve(const NetDev& d, int B, bool bwd, char* base, size_t* total) {
   return w;
 }
 
-void set_counts(BnIn& in, int B, int V) {
-  const int G = std::min(B, num_cus());
+void set_counts(BnIn& in, int B, int V, int G) {
   in.inv_n = 1.0 / ((double)B * V);
   in.inv_cnt[0] = 1.0 / ((double)((B + G - 1) / G) * V);
   in.inv_cnt[1] = 1.0 / ((double)((B - (G - 1) + G - 1) / G) * V);
@@ -549,7 +565,8 @@ int32_t launch_conv(const NetDev& d, const BnLds& S, const BnConvArgs& a, const 
   return with_lf(S.lf, [&](auto lf) {
     constexpr auto k = kb_conv<DIM, MODE, decltype(lf)::value, KIND>;
     if (!set_lds_limit<k>(kLdsMax)) return (int32_t)LFS_EDEVICE;
-    hipLaunchKernelGGL(k, dim3((unsigned)std::min(a.B, num_cus())), dim3(64 * kResWaves), S.total, st, d, S, a,
+    const BnGrid G = bn_grid(d, a.B);
+    hipLaunchKernelGGL(k, dim3((unsigned)G.blocks), dim3(64 * G.waves), S.total, st, d, S, a,
                        layer_frags + (size_t)d.f[a.i].off * 64);
     return (int32_t)LFS_OK;
   });
@@ -598,7 +615,7 @@ int32_t forward_impl(const FlowGeom& g, const float* params, int B, const float*
     a.B = B;
     a.fpar = g.frozen_parity(l);
     a.in.batch = bn_mode == LFS_BN_BATCH;
-    set_counts(a.in, B, V);
+    set_counts(a.in, B, V, bn_grid(d, B).blocks);
     a.in.momentum = momentum;
     a.x = x;
     a.store = w.store;
@@ -642,7 +659,7 @@ int32_t backward_impl(const FlowGeom& g, const float* params, int B, const float
       a.B = B;
       a.fpar = fpar;
       a.in.batch = batch;
-      set_counts(a.in, B, V);
+      set_counts(a.in, B, V, bn_grid(d, B).blocks);
       a.x = saved + (size_t)l * BV;
       a.store = sl;
       a.ss = ss;
@@ -684,8 +701,8 @@ int32_t backward_impl(const FlowGeom& g, const float* params, int B, const float
           return with_lf(S.lf, [&](auto in_lds) {
             constexpr auto k = kb_grad<DIM, MODE, decltype(in_lds)::value, decltype(field)::value>;
             if (!set_lds_limit<k>(kLdsMax)) return (int32_t)LFS_EDEVICE;
-            hipLaunchKernelGGL(k, dim3((unsigned)std::min(B, num_cus())), dim3(64 * kResWaves), S.total, st, d, S, q,
-                               fr);
+            const BnGrid G = bn_grid(d, B);
+            hipLaunchKernelGGL(k, dim3((unsigned)G.blocks), dim3(64 * G.waves), S.total, st, d, S, q, fr);
             return (int32_t)LFS_OK;
           });
         };

@@ -161,21 +161,6 @@ __device__ __forceinline__ double tile_sum(float s) {
   return xor_add<8>(xor_add<4>(xor_add<2>(xor_add<1>((double)s))));
 }
 
-// v(0) + .. + v(n - 1) by one wave, in the order of block_sum over 256 threads that take every
-// 256th.
-template <class T, class F>
-__device__ __forceinline__ T sum_of_256(int n, F&& v) {
-  const int lane = threadIdx.x & 63;
-  T r = 0;
-  for (int w = 0; w < 4 && 64 * w < n; ++w) {
-    T acc = 0;
-    for (int t = 64 * w + lane; t < n; t += 256) acc += v(t);
-    acc = wave_sum(acc);
-    r = w == 0 ? acc : r + acc;
-  }
-  return r;
-}
-
 // ---- resident forward ----------------------------------------------------------
 
 // Layers [l0, l1), whose fragments frags are: all of them, or, where the workspace does not

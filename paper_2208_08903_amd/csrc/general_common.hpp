@@ -140,6 +140,21 @@ __device__ __forceinline__ void affine_bwd(int final_tanh, float o0, float x, fl
   gx = g * es;
 }
 
+// v(0) + .. + v(n - 1) by one wave, in the order of block_sum over 256 threads that take every
+// 256th.
+template <class T, class F>
+__device__ __forceinline__ T sum_of_256(int n, F&& v) {
+  const int lane = threadIdx.x & 63;
+  T r = 0;
+  for (int w = 0; w < 4 && 64 * w < n; ++w) {
+    T acc = 0;
+    for (int t = 64 * w + lane; t < n; t += 256) acc += v(t);
+    acc = wave_sum(acc);
+    r = w == 0 ? acc : r + acc;
+  }
+  return r;
+}
+
 // log r of a sample of V sites from the sum of its squares.
 __device__ __forceinline__ double log_prior(int V, double zz) { return -0.5 * zz - (double)V * kHalfLog2Pi; }
 

@@ -140,3 +140,22 @@ def test_weight_gradient_parts(case):
     desc, params, z, fs = _case(*case, lfs.LFS_PLAIN_FP32)
     out, _ = _check_forward(desc, params, z, fs, lfs.LFS_PLAIN_FP32)
     _check_backward(desc, params, z, fs, out, lfs.LFS_PLAIN_FP32)
+
+
+@pytest.mark.parametrize("L,hs,B", [(4, (5, 4), 700), (4, (8, 3), 4097), (2, (20,), 4100)])
+def test_batch_norm_workgroups(L, hs, B):
+    """More samples than workgroups, at two eight-wave workgroups a CU and at four of four
+    waves, against the oracle; log q too."""
+    from . import test_gpu_bn as bn
+    print(f"batch norm L={L} hidden={hs} B={B}", flush=True)
+    desc, params, z, stats, fs = bn._case(2, L, 2, 3, hs, B, lfs.LFS_PLAIN_FP32)
+    out = bn._forward(desc, params, z, lfs.BN_BATCH, stats)
+    f = of.flow_forward(params.astype(np.float64), z.astype(np.float64), fs)
+    ref = f["phi"].reshape(B, -1)
+    assert np.all(np.abs(host(out["phi"]) - ref) <= 1e-5 * (1 + np.abs(ref)))
+    assert np.all(np.abs(host(out["logq"]) - f["logq"]) <= 1e-4 * L * L)
+    g_phi = np.random.default_rng(4).standard_normal(z.shape).astype(np.float32)
+    gp, gz = bn._backward(desc, out, g_phi, 0.37, lfs.BN_BATCH)
+    go, zo = of.flow_vjp(params.astype(np.float64), z.astype(np.float64), fs, g_phi.astype(np.float64), 0.37)
+    assert np.linalg.norm(gp - go) <= 1e-4 * np.linalg.norm(go)
+    assert np.linalg.norm(gz - zo) <= 1e-4 * np.linalg.norm(zo)
