@@ -16,10 +16,11 @@ namespace {  // each translation unit keeps its own copy of the kernels
 // combined in index order.  The order depends on G and P only: deterministic.
 constexpr int kRedCols = 64, kRedSlices = 16;
 
-// Partials [g0, g1) of one parameter in index order, eight loads in flight also where there
-// are fewer (one after the other, the four of 64 workgroups' took 3500 clocks of a launch).
+// Partials [g0, g1) of one parameter in index order, U loads in flight also where there are
+// fewer (one after the other, the four of 64 workgroups' took 3500 clocks of a launch; eight
+// for the one of a single workgroup made a 2D L = 8, C = 16 backward launch 57 -> 65 us).
+template <int U>
 __device__ __forceinline__ float slice_sum(const float* __restrict__ partial, int g0, int g1, int P, int i) {
-  constexpr int U = 8;
   float acc = 0.f;
   for (int g = g0; g < g1; g += U) {
     float v[U];
@@ -31,6 +32,11 @@ __device__ __forceinline__ float slice_sum(const float* __restrict__ partial, in
   }
   return acc;
 }
+__device__ __forceinline__ float slice_sum(const float* __restrict__ partial, int G, int sl, int P, int i) {
+  const int g0 = (int)((long)G * sl / kRedSlices), g1 = (int)((long)G * (sl + 1) / kRedSlices);
+  if (G <= kRedSlices) return slice_sum<1>(partial, g0, g1, P, i);
+  return slice_sum<8>(partial, g0, g1, P, i);
+}
 __global__ void __launch_bounds__(kRedCols * kRedSlices) kf_reduce(int G, int P,
                                                                   const float* __restrict__ partial,
                                                                   float* __restrict__ out) {
@@ -38,10 +44,7 @@ __global__ void __launch_bounds__(kRedCols * kRedSlices) kf_reduce(int G, int P,
   const int col = threadIdx.x % kRedCols, sl = threadIdx.x / kRedCols;
   const int i = blockIdx.x * kRedCols + col;
   float acc = 0.f;
-  if (i < P) {
-    const int g0 = (int)((long)G * sl / kRedSlices), g1 = (int)((long)G * (sl + 1) / kRedSlices);
-    acc = slice_sum(partial, g0, g1, P, i);
-  }
+  if (i < P) acc = slice_sum(partial, G, sl, P, i);
   sh[sl][col] = acc;
   __syncthreads();
   if (sl == 0 && i < P) {
@@ -64,13 +67,10 @@ __device__ __forceinline__ void grid_reduce(const float* __restrict__ partial, f
   constexpr int PW = NT / kRedSlices;  // parameters per pass
   __shared__ float sh[kRedSlices][PW + 1];
   const int q = threadIdx.x % PW, sl = threadIdx.x / PW;
-  const int g0 = (int)((long)G * sl / kRedSlices), g1 = (int)((long)G * (sl + 1) / kRedSlices);
   for (int base = blockIdx.x * PW; base < P; base += gridDim.x * PW) {
     const int i = base + q;
     float acc = 0.f;
-    if (i < P) {
-      acc = slice_sum(partial, g0, g1, P, i);
-    }
+    if (i < P) acc = slice_sum(partial, G, sl, P, i);
     sh[sl][q] = acc;
     __syncthreads();
     if (sl == 0 && i < P) {
