@@ -23,7 +23,7 @@ namespace {
 
 constexpr double kHalfLog2Pi = 0.91893853320467274178;
 
-template <int DIM, int L, int C, bool BF16, int NT>
+template <int DIM, int L, int C, bool BF16, int NT, bool NEXT>
 __global__ void __launch_bounds__(NT) kf_forward(
     const u32x4* __restrict__ frags, const float* __restrict__ params, int P_layer, int off_b1,
     int off_b2, int off_b3, int N, int parity0, int final_tanh, int B, const float* __restrict__ z,
@@ -51,11 +51,10 @@ __global__ void __launch_bounds__(NT) kf_forward(
   for (int q = threadIdx.x; q < C; q += NT) h1[LY::template off<C>(LY::ZS, q)] = 0, h2[LY::template off<C>(LY::ZS, q)] = 0;
   const int lane = threadIdx.x & 63, w = wave_id(), j = lane >> 4, m = lane & 15;
   const size_t BV = (size_t)B * V;
-  // Small FP32 lattices: a layer's fragments, conv3 table and biases are fetched while the
+  // NEXT (small FP32 lattices): a layer's fragments, conv3 table and biases are fetched while the
   // previous layer's conv3 runs.  Fetched where they are used (as the other shapes do, whose
   // longer passes hide it or whose registers are full), the passes of an 8 x 8 sample began
   // with an L2 latency each: 36.9 us for 16 layers of C = 8, now 29.5.
-  constexpr bool NEXT = Cfg::PFA && Cfg::Q3 && !Cfg::C1V;
   constexpr int NQ = NEXT ? (LF.k3 * 4 + NT - 1) / NT : 1;
 
   for (int b = blockIdx.x; b < B; b += gridDim.x) {
@@ -336,13 +335,22 @@ int32_t launch_forward(const FlowGeom& g, const float* params, int B, const floa
   const long nthreads = (long)LF.total * 64 * g.N;
   hipLaunchKernelGGL((kf_prep<BF16>), dim3((unsigned)((nthreads + 255) / 256)), dim3(256), 0, st,
                      params, g.N, g.T, (int)g.P_layer, tab, frags);
-  constexpr auto kern = kf_forward<DIM, L, C, BF16, Cfg::NT>;
-  if (!set_lds_limit<kern>(Cfg::lds_bytes)) return LFS_EDEVICE;
-  hipLaunchKernelGGL(kern, dim3(B), dim3(Cfg::NT), Cfg::lds_bytes, st, frags, params,
-                     (int)g.P_layer, (int)g.off_b1, (int)g.off_b2, (int)g.off_b3, g.N, g.parity0,
-                     g.final_tanh, B, z, phi, saved, logq, logdet,
-                     HSave<DIM, L, C, BF16>::ok ? hsave : nullptr, (int)g.off_W1);
-  return launch_status();
+  constexpr bool CAN = Cfg::PFA && Cfg::Q3 && !Cfg::C1V;
+  auto launch = [&](auto next) -> int32_t {
+    constexpr auto kern = kf_forward<DIM, L, C, BF16, Cfg::NT, CAN && decltype(next)::value>;
+    if (!set_lds_limit<kern>(Cfg::lds_bytes)) return LFS_EDEVICE;
+    hipLaunchKernelGGL(kern, dim3(B), dim3(Cfg::NT), Cfg::lds_bytes, st, frags, params,
+                       (int)g.P_layer, (int)g.off_b1, (int)g.off_b2, (int)g.off_b3, g.N, g.parity0,
+                       g.final_tanh, B, z, phi, saved, logq, logdet,
+                       HSave<DIM, L, C, BF16>::ok ? hsave : nullptr, (int)g.off_W1);
+    return launch_status();
+  };
+  // Fetched ahead, the weights take registers that leave a CU three workgroups instead of four
+  // or five: worth it where the LDS holds no more than three (2D L = 16, C = 16), or where the
+  // samples are at most two per CU (4 layers of 2D L = 8, C = 16: 512 samples 23.3 us with, 22.6
+  // without; 256 19.8 and 21.8; 4096 105.0 and 95.2).
+  constexpr bool FREE = 4 * (Cfg::lds_bytes + 128) > 160 * 1024;
+  return CAN && (FREE || B <= 2 * num_cus()) ? launch(std::true_type{}) : launch(std::false_type{});
 }
 
 using FwdFn = int32_t (*)(const FlowGeom&, const float*, int, const float*, float*, double*,
