@@ -159,3 +159,40 @@ def test_batch_norm_workgroups(L, hs, B):
     go, zo = of.flow_vjp(params.astype(np.float64), z.astype(np.float64), fs, g_phi.astype(np.float64), 0.37)
     assert np.linalg.norm(gp - go) <= 1e-4 * np.linalg.norm(go)
     assert np.linalg.norm(gz - zo) <= 1e-4 * np.linalg.norm(zo)
+
+
+@pytest.mark.parametrize("case", [
+    (2, 8, 3, 1, (64, 64, 64, 64), 1000),    # 132 MB of planes a layer: two layers, then one
+    (2, 64, 3, 1, (64, 64, 64, 64), 16),     # as much, by a launch per convolution
+    (2, 8, 2, 1, (64, 64, 64, 64), 1300),    # one layer a group
+])
+def test_layer_groups(case):
+    """More planes than are kept at once for the weight gradients."""
+    print(f"layer groups {case}", flush=True)
+    desc, params, z, fs = _case(*case, lfs.LFS_PLAIN_FP32)
+    assert lfs.workspace_bytes(desc, case[5], True) < 400 << 20
+    out, _ = _check_forward(desc, params, z, fs, lfs.LFS_PLAIN_FP32)
+    _check_backward(desc, params, z, fs, out, lfs.LFS_PLAIN_FP32)
+
+
+def test_layer_groups_batch_norm():
+    """The same with batch norm, whose store has three planes a hidden one: two layers, then one."""
+    from . import test_gpu_bn as bn
+    hs, B = (64, 64, 64, 64), 700
+    desc, params, z, stats, fs = bn._case(2, 8, 3, 1, hs, B, lfs.LFS_PLAIN_FP32)
+    params *= np.float32(0.5)
+    out = bn._forward(desc, params, z, lfs.BN_BATCH, stats)
+    g_phi = np.random.default_rng(4).standard_normal(z.shape).astype(np.float32)
+    gp, gz = bn._backward(desc, out, g_phi, 0.37, lfs.BN_BATCH)
+    go, zo = of.flow_vjp(params.astype(np.float64), z.astype(np.float64), fs, g_phi.astype(np.float64), 0.37)
+    assert np.linalg.norm(gp - go) <= 1e-4 * np.linalg.norm(go)
+    assert np.linalg.norm(gz - zo) <= 1e-4 * np.linalg.norm(zo)
+
+
+def test_default_network_beyond_slabs():
+    """The default network in FP32 on a lattice of which a slab of one slice exceeds the LDS."""
+    case = (3, 38, 1, 3, (16, 16), 1)
+    print(f"large default network {case}", flush=True)
+    desc, params, z, fs = _case(*case, lfs.LFS_PLAIN_FP32)
+    out, _ = _check_forward(desc, params, z, fs, lfs.LFS_PLAIN_FP32)
+    _check_backward(desc, params, z, fs, out, lfs.LFS_PLAIN_FP32)
