@@ -1,5 +1,5 @@
 // C ABI of the flow: descriptor validation, parameter layout, workspace
-// sizing and dispatch between the fused and the generic kernel families.
+// sizing and dispatch between the fused, the general and the batch-norm kernels.
 #include <hip/hip_runtime.h>
 
 #include <mutex>

@@ -101,12 +101,12 @@ __device__ __forceinline__ void for_taps(const SiteMath<DIM>& sm, const int (&c)
   }
 }
 
-// out[b][n][co] = act(bias[co] + sum_t sum_ci W[co][ci][t] in[b][n + delta_t][ci]),
+// out[b][n][co] = bias[co] + sum_t sum_ci W[co][ci][t] in[b][n + delta_t][ci],
 // kSplit lanes per output.  first: the input is the layer's field with the
 // active sites zeroed (cin = 1).
 template <int DIM, int K, bool BF16>
 __global__ void __launch_bounds__(256) kn_conv(int L, int lg, int V, int B, int cin, int cout,
-                                               int first, int fpar, int act,
+                                               int first, int fpar,
                                                const float* __restrict__ in,
                                                const float* __restrict__ W,
                                                const float* __restrict__ bias,
@@ -139,7 +139,7 @@ __global__ void __launch_bounds__(256) kn_conv(int L, int lg, int V, int B, int 
     }
   });
   acc = split_sum(acc) + bias[co];
-  if (s == 0) out[idx] = act ? leaky(acc) : acc;
+  if (s == 0) out[idx] = acc;
 }
 
 // Affine update of the active sites from o = (o_0, o_1) and per-sample log-det
@@ -490,13 +490,13 @@ struct NetWs {
   double *logdet, *logr, *partial;
   float* h[LFS_MAX_HIDDEN];
   float *o, *go, *gA, *gB, *gxA, *gxB;
-  // batch norm: pre-normalisation outputs, per-channel mean and r of every
+  // pre-normalisation outputs, per-channel mean and r of every
   // hidden convolution, and per-channel sums
   float* a[LFS_MAX_HIDDEN];
   double *bn_mean, *bn_rstd, *bn_sum;
 };
 
-// How a layer's network normalises (batch norm only).
+// How a layer's network normalises.
 struct BnRun {
   int mode;              // LFS_BN_BATCH or LFS_BN_RUNNING
   const float* stats;    // running mode: the layer's statistics block
@@ -535,13 +535,11 @@ NetWs carve(const FlowGeom& g, int B, char* base, size_t* total) {
   for (int i = 0; i + 1 < g.n_conv; ++i) w.h[i] = (float*)take(sizeof(float) * BV * g.cout[i]);
   w.o = (float*)take(sizeof(float) * BV * 2);
   const size_t partial_bytes = sizeof(double) * (size_t)wg_chunks(B, g.V) * max_conv_params(g);
-  if (g.bn) {
-    for (int i = 0; i + 1 < g.n_conv; ++i) w.a[i] = (float*)take(sizeof(float) * BV * g.cout[i]);
-    w.bn_mean = (double*)take(sizeof(double) * LFS_MAX_HIDDEN * kMaxWidth);
-    w.bn_rstd = (double*)take(sizeof(double) * LFS_MAX_HIDDEN * kMaxWidth);
-    w.bn_sum = (double*)take(sizeof(double) * 2 * kMaxWidth);
-    w.partial = (double*)take(partial_bytes);
-  }
+  for (int i = 0; i + 1 < g.n_conv; ++i) w.a[i] = (float*)take(sizeof(float) * BV * g.cout[i]);
+  w.bn_mean = (double*)take(sizeof(double) * LFS_MAX_HIDDEN * kMaxWidth);
+  w.bn_rstd = (double*)take(sizeof(double) * LFS_MAX_HIDDEN * kMaxWidth);
+  w.bn_sum = (double*)take(sizeof(double) * 2 * kMaxWidth);
+  w.partial = (double*)take(partial_bytes);
   const size_t fwd = off;
   const int mw = max_width(g);
   w.go = (float*)take(sizeof(float) * BV * 2);
@@ -549,7 +547,6 @@ NetWs carve(const FlowGeom& g, int B, char* base, size_t* total) {
   w.gB = (float*)take(sizeof(float) * BV * mw);
   w.gxA = (float*)take(sizeof(float) * BV);
   w.gxB = (float*)take(sizeof(float) * BV);
-  if (!g.bn) w.partial = (double*)take(partial_bytes);
   total[0] = fwd;
   total[1] = off;
   return w;
@@ -586,15 +583,14 @@ void run_net(const FlowGeom& g, const float* p, int B, const float* x, int fpar,
   const int64_t BV = (int64_t)B * g.V;
   for (int i = 0; i < g.n_conv; ++i) {
     const bool last = i + 1 == g.n_conv;
-    const bool norm = g.bn && !last;
-    float* out = last ? w.o : norm ? w.a[i] : w.h[i];
+    float* out = last ? w.o : w.a[i];
     const float* in = i == 0 ? x : w.h[i - 1];
     with_kernel_size(g.K, [&](auto kc) {
       hipLaunchKernelGGL((kn_conv<DIM, decltype(kc)::value, BF16>), grid_for(BV * g.cout[i] * kSplit),
                          dim3(256), 0, st, g.L, log2_or_neg(g.L), g.V, B, g.cin[i], g.cout[i], i == 0, fpar,
-                         !last && !norm, in, p + g.offW[i], p + g.offb[i], out);
+                         in, p + g.offW[i], p + g.offb[i], out);
     });
-    if (norm) run_bn(g, p, B, i, bn, w, st);
+    if (!last) run_bn(g, p, B, i, bn, w, st);
   }
 }
 
@@ -619,7 +615,7 @@ int32_t forward_impl(const FlowGeom& g, const float* params, int B, const float*
     float* xout = saved ? saved + (size_t)(l + 1) * BV : phi;
     const int fpar = g.frozen_parity(l);
     BnRun bn{bn_mode, nullptr, nullptr, momentum};
-    if (g.bn && stats) {
+    if (stats) {
       if (bn_mode == LFS_BN_RUNNING)
         bn.stats = stats + (size_t)l * g.S_layer;
       else
@@ -661,7 +657,7 @@ int32_t backward_impl(const FlowGeom& g, const float* params, int B, const float
     const int fpar = g.frozen_parity(l);
     float* gx = gxs[which];
     // batch statistics are recomputed (no running update); running ones are read
-    const BnRun bn{bn_mode, g.bn && bn_mode == LFS_BN_RUNNING ? stats + (size_t)l * g.S_layer : nullptr,
+    const BnRun bn{bn_mode, bn_mode == LFS_BN_RUNNING ? stats + (size_t)l * g.S_layer : nullptr,
                    nullptr, 0.f};
     run_net<DIM, BF16>(g, p, B, x, fpar, w, bn, st);
     hipLaunchKernelGGL((kn_affine_bwd<DIM>), grid_for(BV), dim3(256), 0, st, g.L, g.V, B, fpar,
@@ -683,7 +679,7 @@ int32_t backward_impl(const FlowGeom& g, const float* params, int B, const float
                            dim3(256), 0, st, g.L, log2_or_neg(g.L), g.V, B, g.cin[i], g.cout[i], i == 0,
                            fpar, gcur, p + g.offW[i], i == 0 ? nullptr : w.h[i - 1], gin);
       });
-      if (g.bn && i > 0) {
+      if (i > 0) {
         // gin holds g_y of hidden convolution j = i - 1: back through its normalisation
         const int j = i - 1, c = g.cout[j];
         const double* mean = w.bn_mean + j * kMaxWidth;
