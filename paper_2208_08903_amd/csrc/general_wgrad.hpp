@@ -313,13 +313,17 @@ WsPlan wgrad_slab_plan(const NetDev& d, int B, int layers, int planes) {
   a.layers = layers;
   a.planes = planes;
   a.B = B;
-  // about 2048 workgroups; where the samples are fewer, each is cut along its leading axis (not
-  // in Seq, whose sums over a sample are FP32).  Four samples of 256 x 256, hidden [1], kernel
-  // 1, 2 layers: 5537 us with whole samples, 87 with parts of them; three of 32^3, hidden
-  // [2, 4]: 2790 and 207.
-  const int64_t want = std::max<int64_t>(1, 2048 / ((int64_t)job * layers));
+  // about 2048 workgroups of whole samples.  Where these make fewer than 2048 waves, each sample
+  // is cut along its leading axis, in parts of 64 sites or more and no thinner than half their
+  // halo (not in Seq, whose sums over a sample are FP32).  Four samples of 256 x 256, hidden [1], kernel 1, 2
+  // layers: 5537 us with whole samples, 87 with parts of them; three of 32^3, hidden [2, 4]: 2790
+  // and 207.  (98 of 8 x 8, hidden [16, 12, 4], kernel 7, which fill the chip, cut in two: a
+  // training step of 4 layers 454 -> 544 us.)
+  const int64_t each = (int64_t)job * layers, want = std::max<int64_t>(1, 2048 / each);
   a.per = cdiv(B, (int)std::min<int64_t>(B, want));
-  a.parts = d.mode == kSeq || want <= B ? 1 : std::min(L, cdiv((int)want, B));
+  a.parts = 1;
+  if (d.mode != kSeq && each * B * a.waves < 2048)
+    a.parts = std::max(1, std::min({L / std::max(1, h), d.lat.V / 64, cdiv((int)(4096 / (each * a.waves)), B)}));
   a.chunks = cdiv(B, a.per) * a.parts;
   p.partial_bytes = sizeof(double) * (size_t)a.chunks * layers * d.P_layer;
   return p;
