@@ -100,12 +100,11 @@ __global__ void __launch_bounds__(64) k_mh_chain(int n_prop_rect, const int64_t*
 // chunks in order: one test against w_cur finds the first accepted position, its mask the
 // rest.  65536 proposals at acceptance 0.43: 5046 -> 198 us, of which the walk 192
 // (2.9 ns per proposal; lane 0 alone took 77).
-__global__ void __launch_bounds__(256) k_mh_paths(unsigned n_prop, const double* __restrict__ logw,
+__global__ void __launch_bounds__(256) k_mh_paths(int n_prop, const double* __restrict__ logw,
                                                   const double* __restrict__ log_u, int64_t* __restrict__ cur_idx) {
-  const int lane = threadIdx.x & 63;
-  const unsigned k0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * kWave;
+  const int lane = threadIdx.x & 63, k0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * kWave;
   if (k0 >= n_prop) return;
-  const size_t at = (size_t)blockIdx.y * n_prop + (k0 + lane);
+  const size_t at = (size_t)blockIdx.y * n_prop + k0 + lane;
   const bool valid = k0 + lane < n_prop;
   const double w = valid ? logw[at] : 0.0, u = valid ? log_u[at] : HUGE_VAL;
   int next = 0;
@@ -130,6 +129,8 @@ __global__ void __launch_bounds__(256) k_mh_paths(unsigned n_prop, const double*
 // one, which as per-lane 64-bit arithmetic costs as much as the decisions (one wave doing
 // both: 380 us).
 constexpr int kWalkChunks = 16;  // chunks per group
+// Longer chains take the other kernel: a group more than they have would be counted in int.
+constexpr int kWalkMost = INT32_MAX - kWalkChunks * kWave;
 __global__ void __launch_bounds__(256) k_mh_walk(int n_prop, const double* __restrict__ logw,
                                                  const double* __restrict__ log_u, lfs_chain_state* __restrict__ states,
                                                  int64_t* cur_idx, uint8_t* __restrict__ accepted) {
@@ -141,14 +142,14 @@ __global__ void __launch_bounds__(256) k_mh_walk(int n_prop, const double* __res
   const size_t base = (size_t)c * n_prop;
   lfs_chain_state st = states[c];
   const int64_t seen0 = st.n_seen;
-  const int groups = (n_prop - 1) / GP + 1;
+  const int groups = (n_prop + GP - 1) / GP;
   auto fetch = [&](int g, int first, int waves) {
     constexpr int MX = (kWalkChunks + 2) / 3;
     double w[MX], u[MX];
     uint64_t p[MX];
 #pragma unroll
     for (int i = 0; i < MX; ++i) {
-      const int ch = first + i * waves, k = g * GP + min(ch, kWalkChunks - 1) * kWave + lane;
+      const int ch = first + i * waves, k = g * GP + ch * kWave + lane;
       const bool ok = ch < kWalkChunks && k < n_prop;
       w[i] = ok ? logw[base + k] : 0.0;
       u[i] = ok ? log_u[base + k] : HUGE_VAL;  // lanes past the end never accept
@@ -169,7 +170,7 @@ __global__ void __launch_bounds__(256) k_mh_walk(int n_prop, const double* __res
         const uint64_t* p = sp[g & 1];
         double wl = w[lane], ul = u[lane];
         uint64_t pl = p[lane];
-        const int chunks = min(kWalkChunks, (int)(((unsigned)(n_prop - g * GP) + kWave - 1) / kWave));
+        const int chunks = min(kWalkChunks, (n_prop - g * GP + kWave - 1) / kWave);
         for (int i = 0; i < chunks; ++i) {
           const int nx = min(i + 1, kWalkChunks - 1) * kWave + lane;
           const double wn = w[nx], un = u[nx];
@@ -325,13 +326,13 @@ extern "C" int32_t lfs_mh_chain(int32_t n_chains, int32_t n_prop, const double* 
   hipStream_t st = (hipStream_t)stream;
   // two launches take 12.5 us at 512 proposals whatever is accepted; one takes 9 to 16 us at
   // 256 (acceptance 0 to 0.85) and 13 to 30 at 512
-  if (n_prop < 512 || n_chains > 65535) {
+  if (n_prop < 512 || n_chains > 65535 || n_prop > lfs::kWalkMost) {
     hipLaunchKernelGGL(lfs::k_mh_chain, dim3(n_chains), dim3(lfs::kWave), 0, st, n_prop, nullptr, logw, log_u, state,
                        nullptr, cur_idx, accepted);
     return lfs::launch_status();
   }
   const unsigned chunks = ((unsigned)n_prop + lfs::kWave - 1) / lfs::kWave;
-  hipLaunchKernelGGL(lfs::k_mh_paths, dim3((chunks + 3) / 4, n_chains), dim3(256), 0, st, (unsigned)n_prop, logw, log_u, cur_idx);
+  hipLaunchKernelGGL(lfs::k_mh_paths, dim3((chunks + 3) / 4, n_chains), dim3(256), 0, st, n_prop, logw, log_u, cur_idx);
   hipLaunchKernelGGL(lfs::k_mh_walk, dim3(n_chains), dim3(256), 0, st, n_prop, logw, log_u, state, cur_idx,
                      accepted);
   return lfs::launch_status();
