@@ -80,37 +80,45 @@ __device__ __forceinline__ int64_t series_at(const int64_t* index, int64_t n, in
 }
 
 // Sum of one of the nsum segments of series s, and whether any of its indices falls
-// outside [0, ldx).  Segments rather than one workgroup per series: its gathers are bound
+// outside [0, ldx) (kBad) or any of its values is not finite, or so large that a deviation
+// might not be (kWild).  Segments rather than one workgroup per series: its gathers are bound
 // by latency (65536 elements in one workgroup took 48 us).
+constexpr int32_t kBad = 1, kWild = 2;
 __global__ void __launch_bounds__(kThreads) k_ac_sums(int64_t n, int64_t per, const double* __restrict__ x,
                                                      int64_t ldx, const int64_t* __restrict__ index,
                                                      double* __restrict__ sums, int32_t* __restrict__ bad) {
   __shared__ double red[kWaves];
   const int s = blockIdx.y, o = blockIdx.y * gridDim.x + blockIdx.x;
   const int64_t k1 = std::min<int64_t>(n, (blockIdx.x + 1) * per);
-  double acc = 0.0, nbad = 0.0;
+  double acc = 0.0;
+  int32_t f = 0;
 #pragma unroll 4
   for (int64_t k = blockIdx.x * per + threadIdx.x; k < k1; k += kThreads) {
     const int64_t j = series_at(index, n, s, k);
     if (j < 0 || j >= ldx) {
-      nbad += 1.0;
+      f |= kBad;
     } else {
-      acc += x[(size_t)s * ldx + j];
+      const double v = x[(size_t)s * ldx + j];
+      f |= fabs(v) <= 1e290 ? 0 : kWild;
+      acc += v;
     }
   }
   acc = block_sum(acc, red);
-  nbad = block_sum(nbad, red);
+  const bool isbad = __syncthreads_or(f & kBad), wild = __syncthreads_or(f & kWild);
   if (threadIdx.x == 0) {
     sums[o] = acc;
-    bad[o] = nbad > 0.0;
+    bad[o] = (isbad ? kBad : 0) | (wild ? kWild : 0);
   }
 }
 
 // Mean of a series from its segment sums (at most 64, one per lane, fixed butterfly);
-// bad: any segment has an index out of range.
-__device__ __forceinline__ double series_mean(int64_t n, int nsum, const double* sums, const int32_t* bad, bool& isbad) {
+// isbad, wild: any segment is.
+__device__ __forceinline__ double series_mean(int64_t n, int nsum, const double* sums, const int32_t* bad, bool& isbad,
+                                              bool& wild) {
   const int lane = threadIdx.x & (kWave - 1);
-  isbad = __ballot(lane < nsum && bad[lane] != 0) != 0;
+  const int32_t f = lane < nsum ? bad[lane] : 0;
+  isbad = __ballot(f & kBad) != 0;
+  wild = __ballot(f & kWild) != 0;
   return wave_sum(lane < nsum ? sums[lane] : 0.0) / (double)n;
 }
 
@@ -134,8 +142,8 @@ __global__ void __launch_bounds__(kThreads) k_ac_partial(int64_t n, int T, int c
   const int c = blockIdx.x, s = blockIdx.y, nchunk = gridDim.x, t0 = (blockIdx.z * kThreads + threadIdx.x) * 4;
   const int64_t i0 = (int64_t)c * chunk;
   double* out = partial + ((size_t)s * nchunk + c) * (T + 1);
-  bool isbad;
-  const double mu = series_mean(n, nsum, sums + (size_t)s * nsum, bad + (size_t)s * nsum, isbad);
+  bool isbad, wild;
+  const double mu = series_mean(n, nsum, sums + (size_t)s * nsum, bad + (size_t)s * nsum, isbad, wild);
   if (isbad) {
     for (int r = 0; r < 4; ++r)
       if (t0 + r <= T) out[t0 + r] = 0.0;
@@ -144,14 +152,12 @@ __global__ void __launch_bounds__(kThreads) k_ac_partial(int64_t n, int T, int c
   // d[q]: element i0 + q for q < chunk, then element i0 + lag0 + q - chunk onwards, where
   // lag0 is the workgroup's first lag
   const int lag0 = blockIdx.z * kThreads * 4, span = chunk + ac_lags(T - lag0);
-  bool wild = false;
   for (int q = threadIdx.x; q < chunk + span; q += kThreads) {
     const int64_t k = i0 + (q < chunk ? q : lag0 + q - chunk);
-    const double v = k < n ? x[(size_t)s * ldx + series_at(index, n, s, k)] - mu : 0.0;
-    wild |= !__builtin_isfinite(v);
-    d[q] = v;
+    d[q] = k < n ? x[(size_t)s * ldx + series_at(index, n, s, k)] - mu : 0.0;
   }
-  if (__syncthreads_or(wild)) {  // the zeros past the end would turn an infinity into a NaN
+  __syncthreads();
+  if (wild) {  // the zeros past the end would turn an infinity into a NaN
     for (int t = t0; t < t0 + 4 && t <= T; ++t) {
       const double* b = d + chunk + (t - lag0);
       double acc = 0.0;
@@ -192,7 +198,7 @@ __global__ void __launch_bounds__(kThreads) k_ac_gamma(int64_t n, int T, int nch
   const int s = blockIdx.y, lane = threadIdx.x & (kWave - 1), sl = threadIdx.x / kWave;
   const int t = blockIdx.x * kWave + lane;
   bool isbad = false;
-  for (int k = 0; k < nsum; ++k) isbad |= bad[(size_t)s * nsum + k] != 0;
+  for (int k = 0; k < nsum; ++k) isbad |= (bad[(size_t)s * nsum + k] & kBad) != 0;
   double acc = 0.0;
   if (t <= T) {
     const int c1 = (int)((int64_t)nchunk * (sl + 1) / kWaves);
@@ -227,7 +233,7 @@ __global__ void __launch_bounds__(kThreads) k_ac_final(int64_t n, int T, int nch
   double* g = gin + (size_t)s * (T + 1);
   const double nan = __builtin_nan("");
   bool isbad = false;
-  for (int k = 0; k < nsum; ++k) isbad |= bad[(size_t)s * nsum + k] != 0;
+  for (int k = 0; k < nsum; ++k) isbad |= (bad[(size_t)s * nsum + k] & kBad) != 0;
   if (nchunk <= kAcFold) {
     for (int t = threadIdx.x; t <= T; t += kThreads) {
       double acc = 0.0;
