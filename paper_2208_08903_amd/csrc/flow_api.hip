@@ -317,9 +317,9 @@ extern "C" int32_t lfs_flow_backward_bn(const lfs_flow_desc* desc, const float* 
 // activations) lives in one file-scope device array instead of caller memory.
 // Whatever noalloc_bytes lets through fits it, one sample at a time if need be: the
 // general kernels pad channels to four and hold a row tile's fragments beside the two
-// activations, at most 11.7 MB (3D L = 62, hidden [5, 1], kernel 7), or a layer's
-// fragments in BF16, at most 9.0 MB (3D, kernel 7, hidden [64, 64, 64, 64]), and 8 bytes
-// per sample and 32 sites, at most 1.4 MB.
+// activations, at most 12.5 MB (3D L = 62, hidden [5, 1], kernel 7), or a layer's
+// fragments in BF16, at most 9.0 MB (3D, kernel 7, hidden [64, 64, 64, 64]), and 4 bytes
+// per sample and site, at most 2.8 MB.
 // Its device address differs per GPU and is looked up once per device with
 // that device current; host code never passes the array's name to a kernel.
 namespace lfs {

@@ -169,7 +169,7 @@ struct BnConvArgs {
   int go;               // Affine: plane of g_o
 };
 
-template <int DIM, int MODE, bool LF, Kind KIND>
+template <int DIM, int MODE, bool LF, bool FEW, Kind KIND>
 __global__ void __launch_bounds__(64 * kResWaves) kb_conv(NetDev d, BnLds S, BnConvArgs A, const u32x4* frags) {
   extern __shared__ __align__(16) unsigned char smem[];
   const Lat& lat = d.lat;
@@ -251,11 +251,11 @@ __global__ void __launch_bounds__(64 * kResWaves) kb_conv(NetDev d, BnLds S, BnC
         }
       };
       if (A.i == 0) {
-        conv_pass<MODE, false>((V + 15) >> 4, c, frags, red, [&](int tile) {
+        conv_pass<MODE, false, FEW>((V + 15) >> 4, c, frags, red, [&](int tile) {
           return lds_field(d, nbr, xs, min(tile * 16 + m, V - 1));
         }, epi);
       } else {
-        conv_pass<MODE, false>((V + 15) >> 4, c, frags, red, [&](int tile) {
+        conv_pass<MODE, false, FEW>((V + 15) >> 4, c, frags, red, [&](int tile) {
           return lds_planes<false>(d, nbr, S.ps, in, min(tile * 16 + m, V - 1));
         }, epi);
       }
@@ -285,7 +285,7 @@ __global__ void __launch_bounds__(64 * kResWaves) kb_conv(NetDev d, BnLds S, BnC
       const size_t o = (size_t)b * V;
       const int apar = A.fpar ^ 1;
       const float gld = KIND == Kind::Affine && A.gld_vec ? (float)(-A.gld_vec[b]) : A.gld;
-      conv_pass<MODE, false>((half + 15) >> 4, c, frags, red, [&](int tile) {
+      conv_pass<MODE, false, FEW>((half + 15) >> 4, c, frags, red, [&](int tile) {
         return lds_planes<false>(d, nbr, S.ps, in, half_site<DIM>(lat, min(tile * 16 + m, half - 1), apar));
       }, [&](int tile, int, const f32x4& v) {
         const int a = tile * 16 + m;
@@ -342,7 +342,7 @@ struct BnGradArgs {
   float* gx;                  // i = 0: the field's gradient
 };
 
-template <int DIM, int MODE, bool LF, bool FIELD>
+template <int DIM, int MODE, bool LF, bool FEW, bool FIELD>
 __global__ void __launch_bounds__(64 * kResWaves) kb_grad(NetDev d, BnLds S, BnGradArgs A, const u32x4* frags) {
   extern __shared__ __align__(16) unsigned char smem[];
   const Lat& lat = d.lat;
@@ -440,14 +440,14 @@ __global__ void __launch_bounds__(64 * kResWaves) kb_grad(NetDev d, BnLds S, BnG
     lds_barrier();
     if constexpr (FIELD) {
       float* gx = A.gx + (size_t)b * V;
-      conv_pass<MODE, true>((half + 15) >> 4, c, frags, red, [&](int tile) {
+      conv_pass<MODE, true, FEW>((half + 15) >> 4, c, frags, red, [&](int tile) {
         return lds_planes<true>(d, nbr, S.ps, in, half_site<DIM>(lat, min(tile * 16 + m, half - 1), A.fpar));
       }, [&](int tile, int, const f32x4& v) {
         const int a = tile * 16 + m;
         if (j == 0 && a < half) gx[half_site<DIM>(lat, a, A.fpar)] += v[0];
       });
     } else {
-      conv_pass<MODE, true>((V + 15) >> 4, c, frags, red, [&](int tile) {
+      conv_pass<MODE, true, FEW>((V + 15) >> 4, c, frags, red, [&](int tile) {
         return lds_planes<true>(d, nbr, S.ps, in, min(tile * 16 + m, V - 1));
       }, [&](int tile, int ct, const f32x4& v) {
         const int n = tile * 16 + m, pl = ct * 4 + j;
@@ -562,10 +562,10 @@ void set_counts(BnIn& in, int B, int V, int G) {
 
 template <int DIM, int MODE, Kind KIND>
 int32_t launch_conv(const NetDev& d, const BnLds& S, const BnConvArgs& a, const u32x4* layer_frags, hipStream_t st) {
-  return with_lf(S.lf, [&](auto lf) {
-    constexpr auto k = kb_conv<DIM, MODE, decltype(lf)::value, KIND>;
+  const BnGrid G = bn_grid(d, a.B);
+  return with_lf(S.lf, G.waves < kResWaves, [&](auto lf, auto few) {
+    constexpr auto k = kb_conv<DIM, MODE, decltype(lf)::value, decltype(few)::value, KIND>;
     if (!set_lds_limit<k>(kLdsMax)) return (int32_t)LFS_EDEVICE;
-    const BnGrid G = bn_grid(d, a.B);
     hipLaunchKernelGGL(k, dim3((unsigned)G.blocks), dim3(64 * G.waves), S.total, st, d, S, a,
                        layer_frags + (size_t)d.f[a.i].off * 64);
     return (int32_t)LFS_OK;
@@ -698,10 +698,10 @@ int32_t backward_impl(const FlowGeom& g, const float* params, int B, const float
         q.gx = gx;
         const u32x4* fr = lf + (size_t)d.t[i].off * 64;
         auto launch = [&](auto field) {
-          return with_lf(S.lf, [&](auto in_lds) {
-            constexpr auto k = kb_grad<DIM, MODE, decltype(in_lds)::value, decltype(field)::value>;
+          const BnGrid G = bn_grid(d, B);
+          return with_lf(S.lf, G.waves < kResWaves, [&](auto in_lds, auto few) {
+            constexpr auto k = kb_grad<DIM, MODE, decltype(in_lds)::value, decltype(few)::value, decltype(field)::value>;
             if (!set_lds_limit<k>(kLdsMax)) return (int32_t)LFS_EDEVICE;
-            const BnGrid G = bn_grid(d, B);
             hipLaunchKernelGGL(k, dim3((unsigned)G.blocks), dim3(64 * G.waves), S.total, st, d, S, q, fr);
             return (int32_t)LFS_OK;
           });

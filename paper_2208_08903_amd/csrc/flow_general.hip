@@ -29,14 +29,11 @@
 namespace lfs {
 namespace {
 
-// Tiles of 16 active sites, whose sums of s the log-det is made of.
-__host__ __device__ inline int ld_tiles(int V) { return (V / 2 + 15) / 16; }
-
 // LDS of a resident workgroup, byte offsets.
 struct ResLds {
   int ps;  // plane stride
   int xs, xm, gy, go, slot[LFS_MAX_HIDDEN], red, nbr;  // xm: the field at the frozen sites
-  int ts;                     // forward: the tiles' sums of s
+  int ls;                     // forward: every active site's sum of s over the layers
   int frags[2];               // a layer's weight fragments (lf), see kg_forward and kg_backward
   bool lf;
   int total;
@@ -67,7 +64,7 @@ ResLds res_lds(const NetDev& d, bool bwd, int waves = kResWaves, bool lf = true)
   }
   r.red = take(waves == kResWaves ? 1024ll * kResWaves : 0);
   r.nbr = take(nbr_bytes(d.T, V));
-  if (!bwd) r.ts = take(8ll * ld_tiles(V));
+  if (!bwd) r.ls = take(4ll * V);
   // fragments: two layers' in the forward, one layer's forward and transposed ones in the
   // backward
   const int64_t fr = off;
@@ -96,7 +93,7 @@ __device__ __forceinline__ void build_tables(const NetDev& d, const ResLds& S, u
 // The hidden convolutions of one layer from the masked field into the slots.  store(i, plane,
 // site, values) also receives every quad of activation i.  frags: the layer's forward
 // fragments.
-template <int MODE, class Store>
+template <int MODE, bool FEW, class Store>
 __device__ __forceinline__ void hidden_convs(const NetDev& d, const ResLds& S, unsigned char* smem,
                                              const u32x4* frags, Store&& store) {
   const Lat& lat = d.lat;
@@ -119,12 +116,12 @@ __device__ __forceinline__ void hidden_convs(const NetDev& d, const ResLds& S, u
       }
     };
     if (i == 0) {
-      conv_pass<MODE, false>(tiles, c, frags + c.off * 64, red, [&](int tile) {
+      conv_pass<MODE, false, FEW>(tiles, c, frags + c.off * 64, red, [&](int tile) {
         return lds_field(d, nbr, reinterpret_cast<const float*>(smem + S.xm), min(tile * 16 + m, lat.V - 1));
       }, epi);
     } else {
       const float* in = reinterpret_cast<const float*>(smem + S.slot[i - 1]);
-      conv_pass<MODE, false>(tiles, c, frags + c.off * 64, red, [&](int tile) {
+      conv_pass<MODE, false, FEW>(tiles, c, frags + c.off * 64, red, [&](int tile) {
         return lds_planes<false>(d, nbr, S.ps, in, min(tile * 16 + m, lat.V - 1));
       }, epi);
     }
@@ -132,9 +129,8 @@ __device__ __forceinline__ void hidden_convs(const NetDev& d, const ResLds& S, u
   }
 }
 
-// The last convolution at the active sites, 16 to a tile: f(tile, a, o_0, o_1) by every lane,
-// for the a-th of them (-1: none) in one lane each.
-template <int DIM, int MODE, class F>
+// The last convolution at the active sites: f(a, site, o_0, o_1) for the a-th of them.
+template <int DIM, int MODE, bool FEW, class F>
 __device__ __forceinline__ void last_conv(const NetDev& d, const ResLds& S, unsigned char* smem, const u32x4* frags,
                                           int apar, F&& f) {
   const Lat& lat = d.lat;
@@ -142,43 +138,39 @@ __device__ __forceinline__ void last_conv(const NetDev& d, const ResLds& S, unsi
   const ConvDir& c = d.f[i];
   const uint16_t* nbr = reinterpret_cast<const uint16_t*>(smem + S.nbr);
   const float* in = reinterpret_cast<const float*>(smem + S.slot[i - 1]);
-  conv_pass<MODE, false>((half + 15) >> 4, c, frags + c.off * 64, reinterpret_cast<f32x4*>(smem + S.red),
+  conv_pass<MODE, false, FEW>((half + 15) >> 4, c, frags + c.off * 64, reinterpret_cast<f32x4*>(smem + S.red),
                                     [&](int tile) {
     return lds_planes<false>(d, nbr, S.ps, in, half_site<DIM>(lat, min(tile * 16 + m, half - 1), apar));
   }, [&](int tile, int, const f32x4& acc) {
     const int a = tile * 16 + m;
-    f(tile, j == 0 && a < half ? a : -1, acc[0], acc[1]);
+    if (j == 0 && a < half) f(a, half_site<DIM>(lat, a, apar), acc[0], acc[1]);
   });
 }
 
 // ---- log q ---------------------------------------------------------------------
-// s is summed in FP64: the 16 active sites of a tile, over the layers, then over the tiles in
-// the order of 256 threads.  Resident and staged kernels add in this order.  (FP32 sums over
-// all layers left the log-det of 12^3 sites and 12 layers off by 6e-5.)
-
-// The sum over the lane's row of 16 lanes, in every lane of the row.
-__device__ __forceinline__ double tile_sum(float s) {
-  return xor_add<8>(xor_add<4>(xor_add<2>(xor_add<1>((double)s))));
-}
+// s is summed in FP64: the a-th active site's over the layers, then over the sites in the
+// order of 256 threads.  Resident and staged kernels add in this order.  (FP32 sums over all
+// layers left the log-det of 12^3 sites and 12 layers off by 6e-5.  The 16 sites of a tile
+// added in every layer, by lane exchanges, took 0.25 us a layer more.)
 
 // ---- resident forward ----------------------------------------------------------
 
 // Layers [l0, l1), whose fragments frags are: all of them, or, where the workspace does not
 // hold as many, group after group (z of a later one is the earlier one's phi; log r waits in
-// logq, the tiles' sums in carry [B][ld_tiles(V)]).
+// logq, the sites' sums in carry [B][V / 2]).
 // LF: a layer's fragments are read from LDS, the next layer's copied there meanwhile.
-template <int DIM, int MODE, bool LF>
+template <int DIM, int MODE, bool LF, bool FEW>
 __global__ void __launch_bounds__(64 * kResWaves) kg_forward(NetDev d, ResLds S, const u32x4* __restrict__ frags,
                                                              int l0, int l1, int B, const float* z, float* phi,
                                                              float* __restrict__ saved, double* logq,
                                                              double* __restrict__ logdet, double* carry) {
   using R = std::conditional_t<MODE == kBf16, double, float>;
   extern __shared__ __align__(16) unsigned char smem[];
-  const int V = d.lat.V, F = d.frags_fwd, lane = threadIdx.x & 63;
+  const int V = d.lat.V, half = V / 2, F = d.frags_fwd, lane = threadIdx.x & 63;
   const bool sums = fused::wave_id() == (int)(blockDim.x >> 6) - 1;  // the wave that makes the sample's sums
   float* xs = reinterpret_cast<float*>(smem + S.xs);
   float* xm = reinterpret_cast<float*>(smem + S.xm);
-  double* ts = reinterpret_cast<double*>(smem + S.ts);
+  double* ls = reinterpret_cast<double*>(smem + S.ls);
   if constexpr (LF) copy_frags(frags, smem + S.frags[0], F);
   build_tables<DIM>(d, S, smem, false);
   const size_t BV = (size_t)B * V;
@@ -190,9 +182,8 @@ __global__ void __launch_bounds__(64 * kResWaves) kg_forward(NetDev d, ResLds S,
       xm[n] = masked(v, (parity_of<DIM>(site_of<DIM>(d.lat, n)) ^ ((l0 + d.parity0) & 1)) - 1);
       if (saved && l0 == 0) saved[(size_t)b * V + n] = v;
     }
-    double* cb = carry + (size_t)b * ld_tiles(V);
-    if (sums)
-      for (int t = lane; t < ld_tiles(V); t += 64) ts[t] = l0 > 0 ? cb[t] : 0.0;
+    double* cb = carry + (size_t)b * half;
+    for (int a = threadIdx.x; a < half; a += blockDim.x) ls[a] = l0 > 0 ? cb[a] : 0.0;
     if constexpr (LF) wait_copies();
     lds_barrier();
     double logr = 0.0;
@@ -208,19 +199,15 @@ __global__ void __launch_bounds__(64 * kResWaves) kg_forward(NetDev d, ResLds S,
       } else {
         fr = frags + (size_t)(l - l0) * F * 64;
       }
-      hidden_convs<MODE>(d, S, smem, fr, [](int, int, int, const f32x4&) {});
-      last_conv<DIM, MODE>(d, S, smem, fr, fpar ^ 1, [&](int tile, int a, float o0, float o1) {
-        float s = 0.f;
-        if (a >= 0) {
-          const int n = half_site<DIM>(d.lat, a, fpar ^ 1);
-          s = d.final_tanh ? tanhf(o0) : o0;
-          const float xn = xs[n] * expf(s) + o1;
-          xs[n] = xn;
-          xm[n] = xn;  // frozen in the next layer, and its partner active
-          xm[half_site<DIM>(d.lat, a, fpar)] = 0.f;
-        }
-        const double t = tile_sum(s);
-        if (lane == 0) ts[tile] += t;  // (a tile is the same wave's in every layer)
+      hidden_convs<MODE, FEW>(d, S, smem, fr, [](int, int, int, const f32x4&) {});
+      last_conv<DIM, MODE, FEW>(d, S, smem, fr, fpar ^ 1, [&](int a, int n, float o0, float o1) {
+        const double ld = ls[a];  // (the a-th site is the same lane's in every layer)
+        const float s = d.final_tanh ? tanhf(o0) : o0;
+        const float xn = xs[n] * expf(s) + o1;
+        xs[n] = xn;
+        xm[n] = xn;  // frozen in the next layer, and its partner active
+        xm[half_site<DIM>(d.lat, a, fpar)] = 0.f;
+        ls[a] = ld + (double)s;
       });
       if constexpr (LF) wait_copies();
       lds_barrier();
@@ -230,16 +217,18 @@ __global__ void __launch_bounds__(64 * kResWaves) kg_forward(NetDev d, ResLds S,
       }
     }
     for (int n = threadIdx.x; n < V; n += blockDim.x) phi[(size_t)b * V + n] = xs[n];
-    if (sums && l1 < d.N) {
-      for (int t = lane; t < ld_tiles(V); t += 64) cb[t] = ts[t];
-      if (lane == 0) logq[b] = logr;
+    if (l1 < d.N) {
+      for (int a = threadIdx.x; a < half; a += blockDim.x) cb[a] = ls[a];
+      if (sums && lane == 0) logq[b] = logr;
     } else if (sums) {
-      const double ld = sum_of_256<double>(ld_tiles(V), [&](int t) { return ts[t]; });
+      const double ld = sum_of_256<double>(half, [&](int a) { return ls[a]; });
       if (lane == 0) {
         logq[b] = logr - ld;
         if (logdet) logdet[b] = ld;
       }
+      // (the sums are cleared for the next sample by other waves, behind this one's reads)
     }
+    lds_barrier();
   }
 }
 
@@ -254,7 +243,7 @@ __host__ __device__ inline int store_planes(const NetDev& d) { return 2 * d.hpla
 // Layers [l0, l1) of every sample, last to first: g_in is the cotangent of layer l1 - 1's
 // output, g_out receives that of layer l0's input.  LF: the layer's forward fragments
 // and its transposed ones each have a place in LDS; one is filled while the other is used.
-template <int DIM, int MODE, bool LF>
+template <int DIM, int MODE, bool LF, bool FEW>
 __global__ void __launch_bounds__(64 * kResWaves) kg_backward(NetDev d, ResLds S, const u32x4* __restrict__ frags,
                                                               int B, int l0, int l1, const float* __restrict__ saved,
                                                               const float* g_in, float g_ld,
@@ -304,10 +293,9 @@ __global__ void __launch_bounds__(64 * kResWaves) kg_backward(NetDev d, ResLds S
         ff = frags + (size_t)l * d.frags_all * 64;
         ft = ff + F * 64;
       }
-      hidden_convs<MODE>(d, S, smem, ff, [&](int i, int pl, int n, const f32x4& v) { put(d.hplane[i] + pl, n, v); });
-      last_conv<DIM, MODE>(d, S, smem, ff, apar, [&](int, int a, float o0, float) {
-        if (a < 0) return;
-        const int n = half_site<DIM>(lat, a, apar), nf = half_site<DIM>(lat, a, fpar);
+      hidden_convs<MODE, FEW>(d, S, smem, ff, [&](int i, int pl, int n, const f32x4& v) { put(d.hplane[i] + pl, n, v); });
+      last_conv<DIM, MODE, FEW>(d, S, smem, ff, apar, [&](int a, int n, float o0, float) {
+        const int nf = half_site<DIM>(lat, a, fpar);
         float go0, gx;
         const float g = gy[n];
         affine_bwd(d.final_tanh, o0, xs[n], g, gld, go0, gx);
@@ -330,7 +318,7 @@ __global__ void __launch_bounds__(64 * kResWaves) kg_backward(NetDev d, ResLds S
         const float* in = i + 1 == d.n_conv ? go : reinterpret_cast<const float*>(smem + S.slot[i]);
         float* h = reinterpret_cast<float*>(smem + S.slot[i - 1]);
         const int rows = c.rows;
-        conv_pass<MODE, true>((V + 15) >> 4, c, ft + (c.off - F) * 64, red, [&](int tile) {
+        conv_pass<MODE, true, FEW>((V + 15) >> 4, c, ft + (c.off - F) * 64, red, [&](int tile) {
           return lds_planes<true>(d, nbr, S.ps, in, min(tile * 16 + m, V - 1));
         }, [&](int tile, int ct, const f32x4& acc) {
           const int n = tile * 16 + m, pl = ct * 4 + j;
@@ -351,7 +339,7 @@ __global__ void __launch_bounds__(64 * kResWaves) kg_backward(NetDev d, ResLds S
         const int half = V / 2;
         const float* in = reinterpret_cast<const float*>(smem + S.slot[0]);
         const ConvDir& c = d.t[0];
-        conv_pass<MODE, true>((half + 15) >> 4, c, ft + (c.off - F) * 64, red, [&](int tile) {
+        conv_pass<MODE, true, FEW>((half + 15) >> 4, c, ft + (c.off - F) * 64, red, [&](int tile) {
           return lds_planes<true>(d, nbr, S.ps, in, half_site<DIM>(lat, min(tile * 16 + m, half - 1), fpar));
         }, [&](int tile, int, const f32x4& acc) {
           const int a = tile * 16 + m;
@@ -369,13 +357,13 @@ __global__ void __launch_bounds__(64 * kResWaves) kg_backward(NetDev d, ResLds S
 
 // ---- staged kernels --------------------------------------------------------------
 
-// log q = log r - the sum of the tiles' sums (one block per sample).
-__global__ void __launch_bounds__(256) kg_end(int tiles, const double* __restrict__ ld, const double* __restrict__ logr,
+// log q = log r - the sum of the active sites' sums (one block per sample).
+__global__ void __launch_bounds__(256) kg_end(int half, const double* __restrict__ ld, const double* __restrict__ logr,
                                               double* __restrict__ logq, double* __restrict__ logdet) {
   __shared__ double sh[16];
   const int b = blockIdx.x;
   double acc = 0;
-  for (int t = threadIdx.x; t < tiles; t += blockDim.x) acc += ld[(size_t)b * tiles + t];
+  for (int a = threadIdx.x; a < half; a += blockDim.x) acc += ld[(size_t)b * half + a];
   acc = block_sum(acc, sh);
   if (threadIdx.x == 0) {
     logq[b] = logr[b] - acc;
@@ -397,7 +385,7 @@ struct StagedArgs {
   const float* x;    // Couple: the layer's field; Affine: likewise
   float* xout;       // Couple: the next field (may be x); Affine: g_x
   float* xout2;      // Couple: a second copy of the next field, or null
-  double* ld;        // Couple: the sums of s of every tile of 16 active sites, [B][ld_tiles(V)]
+  double* ld;        // Couple: per active site sums of s, [B][V / 2]
   int first;         // Couple: the sums start here
   const float* gy;   // Affine: the cotangent of the layer's output; GradField: unused
   float gld;
@@ -464,35 +452,31 @@ __global__ void __launch_bounds__(256) kg_staged(NetDev d, StagedArgs A, const u
                         (4 * pl + k - c.rows) >> 31);
         *reinterpret_cast<f32x4*>(A.out + (size_t)b * A.out_ss + ((size_t)pl * V + n) * 4) = v;
       }
-    } else if constexpr (OP == Op::Couple) {
-      float sv = 0.f;
-      if (valid && j == 0) {
-        const size_t o = (size_t)b * V + n, of = (size_t)b * V + half_site<DIM>(lat, a, A.fpar);
-        sv = d.final_tanh ? tanhf(acc[0]) : acc[0];
-        const float xn = A.x[o] * expf(sv) + acc[1], xf = A.x[of];
-        A.xout[o] = xn;
-        if (A.xout != A.x) A.xout[of] = xf;
-        if (A.xout2) A.xout2[o] = xn, A.xout2[of] = xf;
-      }
-      const double t = tile_sum(sv);
-      if (lane == 0 && valid) {
-        double* ld = A.ld + (size_t)b * ld_tiles(V) + (a >> 4);
-        *ld = A.first ? t : *ld + t;
-      }
     } else if (valid && j == 0) {
       const size_t o = (size_t)b * V + n;
       if constexpr (OP == Op::GradField) {
         A.xout[o] += acc[0];
       } else {
         const size_t of = (size_t)b * V + half_site<DIM>(lat, a, A.fpar);
-        float go0, gx;
-        const float g = A.gy[o];
-        affine_bwd(d.final_tanh, acc[0], A.x[o], g, A.gld_vec ? (float)(-A.gld_vec[b]) : A.gld, go0, gx);
-        A.xout[o] = gx;
-        A.xout[of] = A.gy[of];
-        float* go = A.out + (size_t)b * A.out_ss;
-        *reinterpret_cast<f32x4*>(go + 4 * n) = f32x4{go0, g, 0.f, 0.f};
-        *reinterpret_cast<f32x4*>(go + 4 * half_site<DIM>(lat, a, A.fpar)) = f32x4{0.f, 0.f, 0.f, 0.f};
+        if constexpr (OP == Op::Couple) {
+          double* ld = A.ld + (size_t)b * half + a;
+          const double l = A.first ? 0.0 : *ld;
+          const float sv = d.final_tanh ? tanhf(acc[0]) : acc[0];
+          const float xn = A.x[o] * expf(sv) + acc[1], xf = A.x[of];
+          A.xout[o] = xn;
+          if (A.xout != A.x) A.xout[of] = xf;
+          if (A.xout2) A.xout2[o] = xn, A.xout2[of] = xf;
+          *ld = l + (double)sv;
+        } else {
+          float go0, gx;
+          const float g = A.gy[o];
+          affine_bwd(d.final_tanh, acc[0], A.x[o], g, A.gld_vec ? (float)(-A.gld_vec[b]) : A.gld, go0, gx);
+          A.xout[o] = gx;
+          A.xout[of] = A.gy[of];
+          float* go = A.out + (size_t)b * A.out_ss;
+          *reinterpret_cast<f32x4*>(go + 4 * n) = f32x4{go0, g, 0.f, 0.f};
+          *reinterpret_cast<f32x4*>(go + 4 * half_site<DIM>(lat, a, A.fpar)) = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
       }
     }
   }
@@ -502,13 +486,19 @@ __global__ void __launch_bounds__(256) kg_staged(NetDev d, StagedArgs A, const u
 
 // Whether B samples are run by the resident kernels: a sample's forward (backward) state has
 // to fit the LDS (the neighbour table holds 16-bit sites).  In FP32, where the staged kernels
-// give the same bits, they take over where most CUs would be idle and a wave would have four
-// tiles or more of every convolution: one sample of 24 x 24, hidden [16, 16, 16], 2 layers, 81
-// us forward and 179 backward resident, 56 and 116 staged; 64 of them 79 and 261 or 78 and
-// 242; of 20 x 20 the two are as fast.
+// give the same bits, they take over where most CUs would be idle and a sample is many tiles
+// to eight waves.  8 layers, resident and staged, us forward (backward):
+//   34 x 34, hidden [4], 1 sample 149 and 82 (385 and 173), 64 150 and 136 (460 and 385), 128
+//     150 and 187 (518 and 607)
+//   24 x 24, hidden [16, 16, 16], 16 samples 276 and 185 (691 and 491), 64 274 and 272 (877
+//     and 839); [8, 8], kernel 3, 16 samples 109 and 126 (316 and 298)
+//   20 x 20, hidden [16, 16], kernel 3, 16 samples 117 and 137 (311 and 312)
 bool resident(const NetDev& d, int B, bool bwd) {
-  if (d.mode != kBf16 && d.lat.V >= 512 && B <= 64) return false;
-  return d.lat.V < 65536 && (size_t)res_lds(d, bwd).total <= kLdsMax;
+  int widest = 0;
+  for (int i = 0; i + 1 < d.n_conv; ++i) widest = std::max(widest, d.cout[i]);
+  const int V = d.lat.V, few = V >= 900 || (bwd && widest >= 12) ? 64 : bwd || widest >= 12 ? 16 : 0;
+  if (d.mode != kBf16 && V >= 512 && B <= few) return false;
+  return V < 65536 && (size_t)res_lds(d, bwd).total <= kLdsMax;
 }
 
 size_t frag_bytes(const NetDev& d, bool bwd) {
@@ -516,33 +506,39 @@ size_t frag_bytes(const NetDev& d, bool bwd) {
 }
 
 // Workgroups of a resident launch.  A sample per CU or less: eight waves each, whose latency is
-// what counts.  More: up to 16 waves of a CU, in workgroups of the fewer waves the more
-// samples there are, but one for 16 sites, two for 64 and four above at least; and
-// fragments read from the L2 where so many workgroups have no room for them in LDS.  Forward of
-// 8 layers, hidden 8, FP32, 4096 samples of 4 x 4: 422 us with eight waves and one workgroup a
-// CU, 64 with one wave and 16; of 6 x 6: 438, 138 (two and eight; 125 with one and 16);
-// hidden 16, of 12 x 12: 895, 551 (four and four).  The sums' orders do not depend on it.
+// what counts.  More: the number of waves per workgroup, and fragments in LDS or read from the
+// L2, that give a CU the most waves with a unit of their own, within its LDS, the registers
+// (12 to 24 waves) and its share of the samples; of as many, fragments in LDS first, then
+// the smaller workgroups.  Forward of 8 layers, hidden 8, FP32, 4096 samples of 4 x 4: 422 us
+// with eight waves and one workgroup a CU, 64 with one wave and 16; of 6 x 6: 438 and 138; 523
+// of 24 x 24: 301, 237 with two workgroups whose fragments stay in the L2.  The sums' orders do
+// not depend on it.
 struct ResGrid {
   ResLds S;
   int waves, blocks;
 };
 ResGrid res_grid(const NetDev& d, int B, bool bwd) {
-  const int cus = num_cus(), per = cdiv(B, cus), V = d.lat.V;
-  if (per == 1) return ResGrid{res_lds(d, bwd), kResWaves, B};
+  const int cus = num_cus(), per = cdiv(B, cus);
+  ResGrid best{res_lds(d, bwd), kResWaves, std::min(B, cus)};
+  if (per == 1) return best;
   int units = 1;
   for (int i = 0; i < d.n_conv; ++i)
-    units = std::max(units, cdiv(V, 16) * std::max(d.f[i].nct, bwd ? d.t[i].nct : 0));
-  const int lo = V <= 16 ? 1 : V <= 64 ? 2 : 4, hi = units > 4 ? kResWaves : 4;
-  int waves = hi;
-  while (waves > lo && waves * per > 16) waves /= 2;
-  const int want = std::min(per, 16 / waves);
-  auto fit = [](const ResLds& S) { return std::max(1, (int)(160 * 1024 / S.total)); };
-  ResLds S = res_lds(d, bwd, waves);
-  if (S.lf && fit(S) < want) {
-    const ResLds L2 = res_lds(d, bwd, waves, false);
-    if (fit(L2) > fit(S)) S = L2;
-  }
-  return ResGrid{S, waves, std::min(B, cus * std::min(want, fit(S)))};
+    units = std::max(units, cdiv(d.lat.V, 16) * std::max(d.f[i].nct, bwd ? d.t[i].nct : 0));
+  // (in BF16 eight waves share a CU's few units; with many samples they are better apart)
+  const bool apart = d.mode != kBf16 || per >= 8;
+  const int cap = d.mode == kTree ? (bwd ? 16 : 12) : d.mode == kBf16 && !bwd ? 20 : 24;
+  int most = 0;
+  for (const bool lf : {true, false})
+    for (int waves = 1; waves <= kResWaves; waves *= 2) {
+      const ResLds S = res_lds(d, bwd, waves, lf);
+      if ((size_t)S.total > kLdsMax || (lf && !S.lf)) continue;
+      const int wgs = std::min({per, std::max(1, cap / waves), 160 * 1024 / (S.total + 1024)});
+      const int busy = wgs * (apart ? std::min(waves, units) : waves);
+      if (busy <= most) continue;
+      most = busy;
+      best = ResGrid{S, waves, std::min(B, cus * wgs)};
+    }
+  return best;
 }
 
 struct BwdWs {
@@ -614,7 +610,7 @@ int32_t staged(const NetDev& d, StagedArgs a, int layer, const FragSrc& src, hip
 }
 
 // Bytes of the staged forward of B samples beside the fragments: log r, the log-det
-// sums of the tiles of active sites and the hidden activations (two sets of planes, the
+// sums of the active sites and the hidden activations (two sets of planes, the
 // convolutions alternating between them).
 struct StagedWs {
   double *logr, *ld;
@@ -633,7 +629,7 @@ StagedWs staged_ws(const NetDev& d, int B, char* base) {
   int q[2] = {0, 0};
   for (int i = 0; i + 1 < d.n_conv; ++i) q[i & 1] = std::max(q[i & 1], cdiv(d.cout[i], 4));
   w.logr = (double*)take(sizeof(double) * B);
-  w.ld = (double*)take(sizeof(double) * B * ld_tiles(d.lat.V));
+  w.ld = (double*)take(sizeof(double) * (BV / 2));
   for (int k = 0; k < 2; ++k) w.planes[k] = (float*)take(BV * 16 * q[k]);
   w.bytes = off;
   return w;
@@ -672,7 +668,7 @@ int32_t forward_staged(const FlowGeom& g, const NetDev& d, int B, const float* z
     LFS_TRY((staged<DIM, MODE, Op::Couple>(d, a, l, src, st)));
     x = xn;
   }
-  hipLaunchKernelGGL(kg_end, dim3(B), dim3(256), 0, st, ld_tiles(V), w.ld, w.logr, logq, logdet);
+  hipLaunchKernelGGL(kg_end, dim3(B), dim3(256), 0, st, V / 2, w.ld, w.logr, logq, logdet);
   return launch_status();
 }
 
@@ -684,7 +680,7 @@ int32_t forward_impl(const FlowGeom& g, const float* params, int B, const float*
   // the static scratch may be smaller than general_ws_bytes
   if (resident(d, B, false)) {
     const ResGrid R = res_grid(d, B, false);
-    const size_t layer = (size_t)d.frags_fwd * 1024, cb = align_up(sizeof(double) * B * ld_tiles(d.lat.V));
+    const size_t layer = (size_t)d.frags_fwd * 1024, cb = align_up(sizeof(double) * (BV / 2));
     const bool whole = ws_bytes >= fb;
     const int group = whole ? d.N : ws_bytes < cb ? 0 : (int)std::min<size_t>(d.N, (ws_bytes - cb) / layer);
     double* carry = whole ? nullptr : reinterpret_cast<double*>(ws);
@@ -692,8 +688,8 @@ int32_t forward_impl(const FlowGeom& g, const float* params, int B, const float*
     for (int l0 = 0; group > 0 && l0 < d.N; l0 += group) {
       const int l1 = std::min(l0 + group, d.N);
       prep<MODE>(d, params + (size_t)l0 * d.P_layer, l1 - l0, 0, d.frags_fwd, frags, st);
-      LFS_TRY(with_lf(R.S.lf, [&](auto lf) {
-        constexpr auto k = kg_forward<DIM, MODE, decltype(lf)::value>;
+      LFS_TRY(with_lf(R.S.lf, R.waves < kResWaves, [&](auto lf, auto few) {
+        constexpr auto k = kg_forward<DIM, MODE, decltype(lf)::value, decltype(few)::value>;
         if (!set_lds_limit<k>(kLdsMax)) return (int32_t)LFS_EDEVICE;
         hipLaunchKernelGGL(k, dim3((unsigned)R.blocks), dim3(64 * R.waves), R.S.total, st, d, R.S, frags,
                            l0, l1, B, l0 > 0 ? phi : z, phi, saved, logq, logdet, carry);
@@ -745,8 +741,8 @@ int32_t backward_impl(const FlowGeom& g, const float* params, int B, const float
     if (res) {
       const ResGrid R = res_grid(d, B, true);
       float* gx = bufs[which];
-      LFS_TRY(with_lf(R.S.lf, [&](auto lf) {
-        constexpr auto k = kg_backward<DIM, MODE, decltype(lf)::value>;
+      LFS_TRY(with_lf(R.S.lf, R.waves < kResWaves, [&](auto lf, auto few) {
+        constexpr auto k = kg_backward<DIM, MODE, decltype(lf)::value, decltype(few)::value>;
         if (!set_lds_limit<k>(kLdsMax)) return (int32_t)LFS_EDEVICE;
         hipLaunchKernelGGL(k, dim3((unsigned)R.blocks), dim3(64 * R.waves), R.S.total, st, d, R.S, w.frags,
                            B, l0, l1, saved, gy, (float)(-g_logq), g_logq_vec, gx, w.store);

@@ -56,9 +56,11 @@ __device__ __forceinline__ void wait_copies() { __builtin_amdgcn_s_waitcnt(0x0F7
 // of the K blocks (Tree: of the eight sums; Seq keeps its order and is not split), joined
 // through red.  A Tree unit per SIMD is faster whole: split, the four waves of a SIMD took
 // as long over its MFMAs and four times the LDS reads (two floats of each 32 bytes).  reader(tile) gives the operand reader of the lane's
-// site, epi(tile, ct, acc) takes a unit's result.  Ends before any barrier that publishes
+// site, epi(tile, ct, acc) takes a unit's result.  FEW: the workgroup may have fewer waves than
+// kResWaves; in Bf16 a wave then makes all shares of its unit, in the same order (compiled
+// apart: beside the other path it cost that 4 %).  Ends before any barrier that publishes
 // epi's stores.
-template <int MODE, bool TR, class Reader, class Epi>
+template <int MODE, bool TR, bool FEW, class Reader, class Epi>
 __device__ __forceinline__ void conv_pass(int tiles, const ConvDir& cd, const u32x4* frags, f32x4* red,
                                           Reader&& reader, Epi&& epi) {
   const int w = fused::wave_id(), nw = blockDim.x >> 6, lane = threadIdx.x & 63, j = lane >> 4;
@@ -66,23 +68,24 @@ __device__ __forceinline__ void conv_pass(int tiles, const ConvDir& cd, const u3
   const ConvDir c = cd;
   const Weights W{frags, c.per_ct(), lane};
   constexpr bool TREE = MODE == kTree;
-  int ks = 1;
+  int sh = 0;  // a unit in 2^sh shares
   if constexpr (TREE)
-    ks = units <= 2 && nw == kResWaves ? 4 : 1;
+    sh = !FEW && units <= 2 ? 2 : 0;
   else if constexpr (MODE == kBf16)
-    while (ks < 4 && 2 * ks * units <= kResWaves && 2 * ks <= c.nb) ks *= 2;
+    while (sh < 2 && (2 * units << sh) <= kResWaves && (2 << sh) <= c.nb) ++sh;
+  const int ks = 1 << sh;
   auto bias = [&](int ct) { return __builtin_bit_cast(f32x4, W.at(ct, -1)); };
-  if (ks == 1 || nw < kResWaves) {  // (of fewer waves one makes all shares, in the same order)
+  if (sh == 0 || FEW) {
     for (int u = w; u < units; u += nw) {
       const int tile = fdiv(u, c.dnct), ct = u - tile * nct;
       const auto rd = reader(tile);
       if constexpr (TREE) {
         epi(tile, ct, TR ? tree<false>(rd, c, W, ct, j, 0) : tree<false>(rd, c, W, ct, j, 0) + bias(ct));
       } else {
-        f32x4 acc = chain<MODE, TR>(rd, c, W, ct, j, 0, c.nb / ks, bias(ct));
-        if constexpr (MODE == kBf16)
+        f32x4 acc = chain<MODE, TR>(rd, c, W, ct, j, 0, c.nb >> sh, bias(ct));
+        if constexpr (FEW)
           for (int p = 1; p < ks; ++p)
-            acc += chain<MODE, TR>(rd, c, W, ct, j, c.nb * p / ks, c.nb * (p + 1) / ks, f32x4{0.f, 0.f, 0.f, 0.f});
+            acc += chain<MODE, TR>(rd, c, W, ct, j, c.nb * p >> sh, c.nb * (p + 1) >> sh, f32x4{0.f, 0.f, 0.f, 0.f});
         epi(tile, ct, acc);
       }
     }
@@ -97,7 +100,7 @@ __device__ __forceinline__ void conv_pass(int tiles, const ConvDir& cd, const u3
       acc = tree<true>(rd, c, W, ct, j, kp);
     } else {
       if (kp == 0) acc = bias(ct);
-      acc = chain<MODE, TR>(rd, c, W, ct, j, c.nb * kp / ks, c.nb * (kp + 1) / ks, acc);
+      acc = chain<MODE, TR>(rd, c, W, ct, j, c.nb * kp >> sh, c.nb * (kp + 1) >> sh, acc);
     }
     if (kp > 0) red[((kp - 1) * units + u) * 64 + lane] = acc;
   }
@@ -409,10 +412,14 @@ WgPlan wgrad_plan(const NetDev& d, int B, int layers, int planes) {
   return p;
 }
 
-// f(std::true_type) or f(std::false_type).
+// f(std::true_type) or f(std::false_type), and of two conditions.
 template <class F>
 int32_t with_lf(bool lf, F&& f) {
   return lf ? f(std::true_type{}) : f(std::false_type{});
+}
+template <class F>
+int32_t with_lf(bool lf, bool few, F&& f) {
+  return with_lf(lf, [&](auto l) { return with_lf(few, [&](auto w) { return f(l, w); }); });
 }
 
 template <int MODE>
