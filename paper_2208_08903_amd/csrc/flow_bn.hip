@@ -10,7 +10,7 @@
 // the affine update or its backward.  A backward launch likewise turns g_y into g_a on its
 // way in and leaves the sums the next one needs.  Per layer of n convolutions that is n
 // launches forward and 2 n backward where one operation per launch took 5 n - 2 and
-// 11 n - 8.  2D L = 8, hidden [8, 8], 16 layers, batch 64, FP32 training step: 2877 -> 934 us.
+// 11 n - 8.  2D L = 8, hidden [8, 8], 16 layers, batch 64, FP32 training step: 2877 -> 930 us.
 //
 // Statistics are FP64: per sample the sum and the squared deviations from the sample's
 // own mean, merged by count (Chan, Golub and LeVeque's update) in a fixed order.

@@ -20,7 +20,7 @@
 // one barrier to the next, hence one launch for all layers instead of one per
 // convolution, fragments fetched a layer ahead, neighbours from a table and gathers
 // without branches.  Training step of the 2D L = 8 flow with hidden [16, 16, 16], 16
-// layers, batch 64, FP32: 3400 us with a launch per convolution and direct sums, 470 so
+// layers, batch 64, FP32: 3400 us with a launch per convolution and direct sums, 465 so
 // (forward 121, backward 246, weight gradients 85).  3D L = 12, hidden 16, 12 layers,
 // batch 50, FP32, where a sample does not fit: 47.1 -> 2.57 ms (a hidden convolution of
 // 86400 sites 25 us, its data gradient 24 us; direct sums: 294 and 257).
@@ -510,7 +510,7 @@ size_t frag_bytes(const NetDev& d, bool bwd) {
 // L2, that give a CU the most waves with a unit of their own, within its LDS, the registers
 // (12 to 24 waves) and its share of the samples; of as many, fragments in LDS first, then
 // the smaller workgroups.  Forward of 8 layers, hidden 8, FP32, 4096 samples of 4 x 4: 422 us
-// with eight waves and one workgroup a CU, 64 with one wave and 16; of 6 x 6: 438 and 138; 523
+// with eight waves and one workgroup a CU, 65 with one wave and 16; of 6 x 6: 427 and 121; 523
 // of 24 x 24: 301, 237 with two workgroups whose fragments stay in the L2.  The sums' orders do
 // not depend on it.
 struct ResGrid {

@@ -435,7 +435,7 @@ void prep(const NetDev& d, const float* params, int layers, int f0, int count, u
   } while (0)
 
 // Layers whose activations and gradients are kept at once for the weight gradients: as
-// many as fit 320 MB.  (50 samples of 12^3, 12 layers in one weight-gradient launch or in two
+// many as fit 320 MB; compared at one shape only.  (50 samples of 12^3, 12 layers in one weight-gradient launch or in two
 // of 192 MB each, which the last-level cache holds: 591 us or 626.)
 int layer_group(const NetDev& d, int B, int planes) {
   const size_t per = (size_t)B * planes * d.lat.V * 16;
