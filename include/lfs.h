@@ -216,8 +216,8 @@ int32_t lfs_flow_forward(const lfs_flow_desc* desc, const float* params, int32_t
  * be serialised by the caller.  Nothing in the array needs to start at zero.
  * Arguments as lfs_flow_forward, without ws and ws_bytes.
  * Errors: as lfs_flow_forward; LFS_EWORKSPACE, and then only, when
- * LFS_NOALLOC_SCRATCH_BYTES would not hold the fused forward's weight fragments (at most 85 KB per layer, at
- * any batch) or, for the general kernels, two FP64 numbers per sample and the
+ * LFS_NOALLOC_SCRATCH_BYTES would not hold the fused forward's weight
+ * fragments (at most 85 KB per layer, at any batch) or, for the general kernels, two FP64 numbers per sample and the
  * FP32 hidden activations of the whole batch (and the two output channels of a
  * network other than the default one), whether or not they need that much.
  * Where the array does not hold what the general kernels need at once, the

@@ -406,7 +406,7 @@ extern "C" int32_t lfs_autocorr(int32_t n_series, int64_t n, const double* x, in
 extern "C" int32_t lfs_ess(int32_t n_series, int64_t n, const double* logw, int64_t ldw, double* ess,
                            void* stream) {
   LFS_RETURN_IF(n_series < 1 || n < 1 || ldw < n || !logw || !ess, LFS_EINVAL);
-  hipLaunchKernelGGL(lfs::k_ess, dim3(n_series), dim3(n <= 2048 || n_series > 512 ? 256 : 1024), 0, (hipStream_t)stream, n, logw, ldw,
-                     ess);
+  hipLaunchKernelGGL(lfs::k_ess, dim3(n_series), dim3(n <= 2048 || n_series > 512 ? 256 : 1024), 0,
+                     (hipStream_t)stream, n, logw, ldw, ess);
   return lfs::launch_status();
 }
